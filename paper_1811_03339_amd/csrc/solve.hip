@@ -3,8 +3,8 @@
 //
 // Blocked right-looking Cholesky K = L L^T on a row-major matrix (lower
 // triangle), panel width NB = 64, two launches per panel:
-//   diag  : one workgroup factors the 64 x 64 diagonal block in 4-column
-//           strips and forms inv(L_kk); for every panel after the first this
+//   diag  : one workgroup factors the 64 x 64 diagonal block in 16-column
+//           panels and forms inv(L_kk); for every panel after the first this
 //           runs inside the previous trailing update (its tile (0, 0));
 //   panel : X = B inv(L_kk)^T for every 64-row strip below (a plain GEMM,
 //           no sequential dependency), one workgroup per strip;
@@ -125,8 +125,10 @@ __global__ void __launch_bounds__(256) k_panel(T *__restrict__ A, int64_t lda, i
 // of tile (0, 0) -- the next diagonal block -- keeps its updated tile in LDS
 // and factors it at once (diag_factor), so the next panel's diagonal
 // factorization runs beside the rest of this update instead of after it.
+// Held to 128 registers (four wavefronts per SIMD), which the strips of large
+// matrices need and the diagonal block fits without spilling.
 template <class T, int KD>
-__global__ void __launch_bounds__(256) k_syrk(T *__restrict__ A, int64_t lda, int64_t n, int64_t k0,
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) k_syrk(T *__restrict__ A, int64_t lda, int64_t n, int64_t k0,
                                               T *__restrict__ Linv_next, T *__restrict__ LinvT_next, int32_t *flag,
                                               int64_t *aux, int64_t sA, int64_t sL, int nz, int ncol) {
   // block b = tile * nz + system: the tiles (0, 0) of all systems, which
