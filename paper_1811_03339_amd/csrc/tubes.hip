@@ -15,13 +15,16 @@
 //     tubes, the sorted node list U_T of each tube, for every entry its slot
 //     (position of its node in U_T), and for every row the (tube, slot)
 //     places where that node appears;
-//   pass 1: one workgroup per (tube, band of block rows) reads the tube's
-//     entries once and adds every product l_p r_q into an LDS band of the
-//     block; the band goes to a scratch block in HBM.  The block is
-//     symmetric, B = S + S^T with S = sum w l r^T, so a tube that fits in
-//     LDS whole (the square for |U_T| <= 141, else the packed upper
-//     triangle for |U_T| <= 200) is one band that adds each product of S
-//     once, at (min, max), and expands it as it writes;
+//   pass 1: one workgroup per (tube, band) reads the tube's entries once and
+//     adds every product l_p r_q into an LDS band of the block; the band goes
+//     to a scratch block in HBM.  The block is symmetric, B = S + S^T with
+//     S = sum w l r^T, so each product of S is added once, at (min, max), and
+//     expanded as it is written: in the full square for |U_T| <= 141, the
+//     packed upper triangle for |U_T| <= 200, else bands of rows of that
+//     triangle.  Two assemblies of 82 924 elements (4 points, chords of 44
+//     entries, up to 240 nodes a tube) took 9.5 ms with one row entry per lane
+//     and larger tubes in bands of full rows that took both products, and take
+//     3.0 ms; of 19 672 elements (11 points, 25 entries) 1.96 and 0.64 ms;
 //   pass 2: one workgroup per row of A sums that row's slices of the tube
 //     blocks into an LDS row and writes the row once.
 // Each entry is read once per band of its tube (not once per node of its
@@ -41,18 +44,23 @@ namespace {
 
 constexpr int kHash = 8192;         // LDS hash slots per tube (int32 keys)
 constexpr int kMaxU = kHash / 2;    // largest node set a tube may have
-constexpr int kBandDoubles = 20160;  // LDS doubles of one pass-1 band (157.5 KB: the packed triangle of |U_T| <= 200)
+// Pass 1: LDS doubles of a band (157.5 KB: the packed triangle of |U_T| <= 200)
+// and threads of its workgroup, one per CU.  The pass waits on its entry loads,
+// so what counts is wavefronts per band: bands of 79 KB, two workgroups of 512
+// threads per CU, took 6.2 ms against 5.1 ms on 82 924 elements (4 points),
+// 0.85 ms against 0.81 ms on 19 672 (11 points), two assemblies each.
+constexpr int kBand = 20160;
+constexpr int kAccumThreads = 1024;
 
 // row stride of a band in LDS: odd, so the rows of one column fall in distinct bank pairs
 __host__ __device__ inline int band_stride(int U) { return U | 1; }
 
-// A tube whose packed upper triangle fits in LDS is one band (its whole
-// block); a larger one is cut into bands of full rows.
-__host__ __device__ inline int band_rows(int U) {
-  if (U <= 0) return 1;
-  if ((int64_t)U * (U + 1) / 2 <= kBandDoubles) return U;
-  const int R = kBandDoubles / band_stride(U);
-  return R < U ? R : U;
+// rows [r0, r0 + R) of the row-packed upper triangle of a U x U block that fit in `band` doubles
+inline int band_rows(int U, int r0, int band) {
+  int64_t room = band;
+  int R = 0;
+  while (r0 + R < U && room >= U - r0 - R) room -= U - r0 - R++;
+  return R;
 }
 
 // position of (lo, hi), lo <= hi, in the row-packed upper triangle of a
@@ -235,24 +243,10 @@ __global__ void k_row_places(const int64_t *__restrict__ u_off, int64_t n_tubes,
   }
 }
 
-// pass-1 work items {tube, first block row, rows}
-__global__ void k_bands(const int64_t *__restrict__ u_off, int64_t n_tubes, const int64_t *__restrict__ band_off,
-                        int4 *__restrict__ items) {
-  const int64_t T = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (T >= n_tubes) return;
-  const int U = (int)(u_off[T + 1] - u_off[T]);
-  const int R = band_rows(U);
-  int64_t w = band_off[T];
-  for (int r0 = 0; r0 < U; r0 += R) items[w++] = make_int4((int)T, r0, (U - r0) < R ? (U - r0) : R, U);
-}
-
-__global__ void k_band_count(const int64_t *__restrict__ u_off, int64_t n_tubes, int64_t *__restrict__ nb,
-                             int64_t *__restrict__ usq) {
+__global__ void k_block_sizes(const int64_t *__restrict__ u_off, int64_t n_tubes, int64_t *__restrict__ usq) {
   const int64_t T = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (T >= n_tubes) return;
   const int64_t U = u_off[T + 1] - u_off[T];
-  const int64_t R = band_rows((int)U);
-  nb[T] = U > 0 ? (U + R - 1) / R : 0;
   usq[T] = U * U;
 }
 
@@ -268,227 +262,233 @@ struct AccumArgs {
   double KC0, KC1, KC2;
   // general form (k_tube_form): test-order values and constant coefficients
   const double *val_b;
-  double cl[3], cr[3];
+  double cl0, cl1, cl2, cr0, cr1, cr2;
 };
-
-__device__ __forceinline__ double read_lane_f64(double v, int l) {
-  const int lo = __builtin_amdgcn_readlane(__double2loint(v), l);
-  const int hi = __builtin_amdgcn_readlane(__double2hiint(v), l);
-  return __hiloint2double(hi, lo);
-}
-
-// A pair held in registers: entry `lane` and `lane + 64` of l and of r.
-struct PairRegs {
-  int4 m;
-  double w;
-  int ls[2], rs[2];
-  double lv[2], rv[2];
-};
-
-constexpr int kRegEntries = 128;  // entries per half-ray the register path holds
 
 __device__ __forceinline__ int pair_nl(const int4 &m) { return m.z; }
 __device__ __forceinline__ int pair_nr(const int4 &m) { return m.w & 0x3fffffff; }
 
-__device__ __forceinline__ void load_entries(PairRegs &p, const int32_t *__restrict__ slot,
-                                             const double *__restrict__ val) {
-  const int lane = threadIdx.x & 63;
-  const int nl = pair_nl(p.m), nr = pair_nr(p.m);
-  // indices clamped to a valid entry (the pair's first, or entry 0 for an
-  // empty side, whose offset may equal the entry count) so every load is in
-  // bounds; lanes past the end are masked by the counts when used
-#pragma unroll
-  for (int h = 0; h < 2; h++) {
-    const int kl = 64 * h + lane;
-    const int il = nl > 0 ? p.m.x + (kl < nl ? kl : 0) : 0;
-    const int ir = nr > 0 ? p.m.y + (kl < nr ? kl : 0) : 0;
-    p.ls[h] = slot[il];
-    p.lv[h] = val[il];
-    p.rs[h] = slot[ir];
-    p.rv[h] = val[ir];
+// ---- Outer products of half-ray vectors into an LDS band ----
+//
+// A wavefront takes one pair at a time, in steps of up to 64 entries of one
+// side (rows) times 64 of the other (columns), as tiles of 16 rows x 4
+// columns: lane l holds row entry 16 i + (l & 15) of the step in four copies,
+// and column entry 4 (l & 15) + (l >> 4), so that each group of 16 lanes finds
+// its column of tile column t in its own lane t (a row broadcast, no LDS and
+// no scalar registers).  A tile is one product, three integer operations for
+// the address and one LDS update of up to 64 distinct lanes.  (One row entry
+// per lane, with the columns broadcast one at a time, filled 18 of 64 lanes at
+// 20 instructions an update.)  The entries of the next two steps are in flight
+// while a step is multiplied, and the next pair's metadata beyond them.
+//   kSquare: the whole block, row stride Up, each product once at (min, max);
+//   kTri:    the same as a row-packed upper triangle;
+//   kTriBand: rows [r0, r0 + R) of that triangle (products with their smaller
+//            slot elsewhere are left out);
+//   kFull:   block rows [r0, r0 + R), row stride Up, both products of a pair
+//            (rows l, columns r, then rows r, columns l).
+// Measured rates: an LDS update of 64 lanes issues every 3.9 ns per CU, of 18
+// lanes every 3.0 ns; same-address lanes of one update are served one by one.
+enum BandLayout { kSquare = 0, kTri = 1, kTriBand = 2, kFull = 3 };
+
+constexpr int kStep = 64;  // entries of each side in one step
+
+struct PairStep {
+  int rs[4], cs;      // slots, in bytes of a row of doubles
+  double rv[4], cv;   // values
+  int nr, nc;         // entries of each side
+  double w;           // weight of the products
+};
+
+// entry k of a side [e0, e0 + n), clamped into it (entry 0 for an empty side,
+// whose offset may equal the entry count); lanes past the end are masked
+__device__ __forceinline__ int side_entry(int e0, int n, int k) { return n > 0 ? e0 + (k < n ? k : n - 1) : 0; }
+
+// The steps of one wavefront: pairs k, k + nw, ..., and of each its roles, row
+// blocks and column blocks.  Everything here is the wavefront's (scalar).
+template <int ROLES>
+struct StepCursor {
+  const int4 *__restrict__ pm;
+  const double *__restrict__ pw;
+  int64_t k, k1;
+  int nw;
+  int4 m, mn;
+  double w, wn;
+  int role, rb, cb;
+  __device__ __forceinline__ void fetch(int64_t kk, int4 &mm, double &ww) {
+    kk = kk < k1 ? kk : k1 - 1;
+    mm = pm[kk];
+    ww = pw[kk];
   }
+  __device__ __forceinline__ void start(int64_t k0) {
+    k = k0;
+    role = rb = cb = 0;
+    if (k >= k1) return;
+    fetch(k, m, w);
+    fetch(k + nw, mn, wn);
+  }
+  __device__ __forceinline__ int nl() const { return pair_nl(m); }
+  __device__ __forceinline__ int nr() const { return pair_nr(m); }
+  __device__ __forceinline__ void next() {
+    const int nrow = role ? nr() : nl(), ncol = role ? nl() : nr();
+    cb += kStep;
+    if (cb < ncol) return;
+    cb = 0;
+    rb += kStep;
+    if (rb < nrow) return;
+    rb = 0;
+    if (++role < ROLES) return;
+    role = 0;
+    k += nw;
+    m = mn;
+    w = wn;
+    if (k < k1) fetch(k + nw, mn, wn);
+  }
+};
+
+// entries of the cursor's step: rows from vrow, columns from vcol
+template <int ROLES>
+__device__ __forceinline__ void load_step(const StepCursor<ROLES> &c, const int32_t *__restrict__ slot,
+                                          const double *__restrict__ vrow, const double *__restrict__ vcol,
+                                          double w, PairStep &p) {
+  const int lane = threadIdx.x & 63, lr = lane & 15, lc = lane >> 4;
+  const int nl = c.nl(), nr = c.nr();
+  const int erow = c.role ? c.m.y : c.m.x, ecol = c.role ? c.m.x : c.m.y;
+  const int nrow = c.role ? nr : nl, ncol = c.role ? nl : nr;
+  p.nr = nrow - c.rb < kStep ? nrow - c.rb : kStep;
+  p.nc = ncol - c.cb < kStep ? ncol - c.cb : kStep;
+  p.w = w;
+#pragma unroll
+  for (int i = 0; i < 4; i++) {
+    if (i > 0 && 16 * i >= p.nr) break;
+    const int er = side_entry(erow, nrow, c.rb + 16 * i + lr);
+    p.rs[i] = slot[er] * 8;
+    p.rv[i] = vrow[er];
+  }
+  const int ec = side_entry(ecol, ncol, c.cb + 4 * lr + lc);
+  p.cs = slot[ec] * 8;
+  p.cv = vcol[ec];
 }
 
-// Row-side entries one per lane (in-band ones active); the column side is
-// swept one entry at a time, broadcast with readlane:
-//   acc[s_row - r0][s_col] += v_row (w v_col).
-// One LDS update per column touches one column of distinct rows: with an
-// odd row stride these land in distinct bank pairs.
-// Forces v to be computed at this point with the current (full) lane mask.
-__device__ __forceinline__ void in_all_lanes(int &v) { asm volatile("" : "+v"(v)); }
-__device__ __forceinline__ void in_all_lanes(double &v) { asm volatile("" : "+v"(v)); }
-
-// cv_reg already carries the pair weight; ncol is wave-uniform.  The column
-// registers are read with readlane from lanes that may be masked off below:
-// they are materialised in every lane before the branch (otherwise the
-// compiler may sink their loads into it, leaving inactive lanes stale).
-// Layouts of a pass-1 band in LDS:
-//   kBand2: rows [r0, r0 + R) of the block, row stride Up; both products of
-//           every pair (acc[rowbase + cs], rowbase = (xs - r0) Up);
-//   kSquare1: the whole block, row stride Up, each product once at
-//           (min, max) (lo Up + hi);
-//   kTri1: the whole block as a row-packed upper triangle, each product once
-//           at tri_base(lo, U) + hi (rowbase = tri_base(xs, U)).
-// With the odd stride, the rows of one column sweep fall in distinct bank
-// pairs in kBand2 and kSquare1 (stride Up when xs < cs, consecutive when
-// xs > cs).
-enum BandLayout { kBand2 = 0, kSquare1 = 1, kTri1 = 2 };
-
-template <int LAYOUT>
-__device__ __forceinline__ void sweep_cols(double *acc, int rowbase, int xs, int U, int Up, double xv, bool xok,
-                                           int cs_reg, double cv_reg, int ncol) {
-  in_all_lanes(cs_reg);
-  in_all_lanes(cv_reg);
-  if (xok) {
-#pragma unroll 4
-    for (int j = 0; j < ncol; j++) {
-      const int cs = __builtin_amdgcn_readlane(cs_reg, j);
-      const double cv = read_lane_f64(cv_reg, j);
-      int idx;
-      if (LAYOUT == kTri1) idx = xs <= cs ? rowbase + cs : tri_base(cs, U) + xs;
-      else if (LAYOUT == kSquare1) idx = xs <= cs ? rowbase + cs : cs * Up + xs;
-      else idx = rowbase + cs;
-      atomicAdd(&acc[idx], xv * cv);
-    }
-  }
+// lane t of each group of 16 lanes, in all of the group
+template <int t>
+__device__ __forceinline__ int group_lane(int v) {
+  return __builtin_amdgcn_update_dpp(0, v, 0x150 + t, 0xf, 0xf, true);
+}
+template <int t>
+__device__ __forceinline__ double group_lane(double v) {
+  return __hiloint2double(group_lane<t>(__double2hiint(v)), group_lane<t>(__double2loint(v)));
 }
 
-// one pair from registers (|l|, |r| <= kRegEntries).  kBand2: role 0 adds
-// l (w r)^T, role 1 adds r (w l)^T to the rows in the band.  kSquare1,
-// kTri1 (the whole block): role 0 only, each product at (min, max), which
-// sums both roles (B = S + S^T, diagonal doubled when written).
-template <int LAYOUT>
-__device__ __forceinline__ void pair_products_reg(double *acc, int Up, int r0, int R, int U, const PairRegs &p) {
-  const int lane = threadIdx.x & 63;
-  // the pair is the wave's: its counts are uniform (scalar loop bounds)
-  const int nl = __builtin_amdgcn_readfirstlane(pair_nl(p.m)), nr = __builtin_amdgcn_readfirstlane(pair_nr(p.m));
-  // column-side values scaled by the pair weight once
-  const double lw0 = p.lv[0] * p.w, lw1 = p.lv[1] * p.w, rw0 = p.rv[0] * p.w, rw1 = p.rv[1] * p.w;
-#pragma unroll
-  for (int role = 0; role < (LAYOUT == kBand2 ? 2 : 1); role++) {
-    const int nrow = role ? nr : nl, ncol = role ? nl : nr;
-#pragma unroll
-    for (int h = 0; h < 2; h++) {
-      const int xs = role ? p.rs[h] : p.ls[h];
-      const double xv = role ? p.rv[h] : p.lv[h];
-      const bool xok = 64 * h + lane < nrow && xs >= r0 && xs < r0 + R;
-      if (__ballot(xok) == 0) continue;
-      const int rowbase = LAYOUT == kTri1 ? tri_base(xs, U) : (xs - r0) * Up;
-      sweep_cols<LAYOUT>(acc, rowbase, xs, U, Up, xv, xok, role ? p.ls[0] : p.rs[0], role ? lw0 : rw0,
-                         ncol < 64 ? ncol : 64);
-      if (ncol > 64)
-        sweep_cols<LAYOUT>(acc, rowbase, xs, U, Up, xv, xok, role ? p.ls[1] : p.rs[1], role ? lw1 : rw1,
-                           ncol - 64);
-    }
-  }
-}
+struct Band {
+  char *acc;
+  int U, Up, r0, R, off;  // off: bytes of the triangle before row r0
+};
 
-// the same from memory, for pairs with a longer half-ray
-template <int LAYOUT>
-__device__ void pair_products_mem(double *acc, int Up, int r0, int R, int U, const int4 m, double w,
-                                  const int32_t *__restrict__ slot, const double *__restrict__ val) {
+// tile column t of a step with NI chunks of 16 rows, then the next one
+template <int LAYOUT, int NI, int t>
+__device__ __forceinline__ void step_columns(const Band &b, const PairStep &p, double cvw) {
+  if (4 * t >= p.nc) return;
   const int lane = threadIdx.x & 63;
-  const int nl = __builtin_amdgcn_readfirstlane(pair_nl(m)), nr = __builtin_amdgcn_readfirstlane(pair_nr(m));
-  for (int role = 0; role < (LAYOUT == kBand2 ? 2 : 1); role++) {
-    const int nrow = role ? nr : nl, ncol = role ? nl : nr;
-    const int erow = role ? m.y : m.x, ecol = role ? m.x : m.y;
-    for (int j0 = 0; j0 < nrow; j0 += 64) {
-      const int ex = erow + (j0 + lane < nrow ? j0 + lane : j0);
-      const int xs = slot[ex];
-      const double xv = val[ex];
-      const bool xok = j0 + lane < nrow && xs >= r0 && xs < r0 + R;
-      if (__ballot(xok) == 0) continue;
-      const int rowbase = LAYOUT == kTri1 ? tri_base(xs, U) : (xs - r0) * Up;
-      for (int c0 = 0; c0 < ncol; c0 += 64) {
-        const int ec = ecol + (c0 + lane < ncol ? c0 + lane : c0);
-        const int cn = ncol - c0 < 64 ? ncol - c0 : 64;
-        sweep_cols<LAYOUT>(acc, rowbase, xs, U, Up, xv, xok, slot[ec], val[ec] * w, cn);
+  const int y = group_lane<t>(p.cs);
+  const double cv = group_lane<t>(cvw);
+  const bool cok = 4 * t + (lane >> 4) < p.nc;
+#pragma unroll
+  for (int i = 0; i < NI; i++) {
+    const int x = p.rs[i];
+    bool ok = cok && 16 * i + (lane & 15) < p.nr;
+    int at;
+    if (LAYOUT == kFull) {
+      ok = ok && (unsigned)(x - 8 * b.r0) < (unsigned)(8 * b.R);
+      at = (x - 8 * b.r0) * b.Up + y;
+    } else {
+      const int lo = x < y ? x : y, hi = x < y ? y : x;
+      if (LAYOUT == kSquare) {
+        at = lo * b.Up + hi;
+      } else {
+        if (LAYOUT == kTriBand) ok = ok && (unsigned)(lo - 8 * b.r0) < (unsigned)(8 * b.R);
+        at = (lo >> 3) * (8 * b.U - 4 - (lo >> 1)) + hi;  // 8 (tri_base(lo / 8, U) + hi / 8)
+        if (LAYOUT == kTriBand) at -= b.off;
       }
     }
+    if (ok) atomicAdd((double *)(b.acc + at), p.rv[i] * cv);
+  }
+  if constexpr (t < 15) step_columns<LAYOUT, NI, t + 1>(b, p, cvw);
+}
+
+template <int LAYOUT>
+__device__ __forceinline__ void step_products(const Band &b, const PairStep &p) {
+  if (p.nr <= 0) return;
+  const double cvw = p.cv * p.w;
+  if (p.nr <= 16) step_columns<LAYOUT, 1, 0>(b, p, cvw);
+  else if (p.nr <= 32) step_columns<LAYOUT, 2, 0>(b, p, cvw);
+  else if (p.nr <= 48) step_columns<LAYOUT, 3, 0>(b, p, cvw);
+  else step_columns<LAYOUT, 4, 0>(b, p, cvw);
+}
+
+// Every pair of [k0, k1) into the band; kc0, kc1: the tube's coefficient in
+// role 0 and 1 (its pairs share one axis).
+template <int LAYOUT>
+__device__ __forceinline__ void band_products(double *acc, int U, int Up, int r0, int R, const AccumArgs &a,
+                                              const double *__restrict__ vrow, const double *__restrict__ vcol,
+                                              double kc0, double kc1, int64_t k0, int64_t k1) {
+  constexpr int ROLES = LAYOUT == kFull ? 2 : 1;
+  // wave-uniform (readfirstlane), so the cursor and its loads are scalar
+  StepCursor<ROLES> c;
+  c.pm = a.pm;
+  c.pw = a.pw;
+  c.k1 = k1;
+  c.nw = blockDim.x >> 6;
+  c.start(k0 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6));
+  const Band b = {(char *)acc, U, Up, r0, R, 8 * (tri_base(r0, U) + r0)};
+  auto load = [&](PairStep &p) {
+    p.nr = 0;
+    if (c.k >= k1) return false;
+    load_step(c, a.ent_slot, vrow, vcol, c.w * (c.role ? kc1 : kc0), p);
+    c.next();
+    return true;
+  };
+  PairStep s0, s1, s2;
+  if (!load(s0)) return;
+  load(s1);
+  for (;;) {
+    const bool more = load(s2);
+    step_products<LAYOUT>(b, s0);
+    s0 = s1;
+    s1 = s2;
+    if (!more && s0.nr <= 0 && s1.nr <= 0) break;
   }
 }
 
-__global__ void __launch_bounds__(1024) k_tube_accum(AccumArgs a) {
+__global__ void __launch_bounds__(kAccumThreads) k_tube_accum(AccumArgs a) {
   extern __shared__ double acc[];
   const int4 it = a.items[blockIdx.x];
   const int64_t T = it.x;
   const int r0 = it.y, R = it.z, U = it.w, Up = band_stride(U);
-  // B = S + S^T with S = sum_p w_p l_p r_p^T.  A tube that is one band
-  // (band_rows) adds each product of S once, at (min, max): half the LDS
-  // updates of the two products, in the full square when it fits (bank
-  // conflict free), else in the packed upper triangle; a band of a larger
-  // block takes both products into full rows.
-  const int layout = R != U ? kBand2 : (U * Up <= kBandDoubles ? kSquare1 : kTri1);
-  const int nacc = layout == kTri1 ? U * (U + 1) / 2 : R * Up;
+  // B = S + S^T with S = sum_p w_p l_p r_p^T: each product of S once, at
+  // (min, max), half the LDS updates of the two products, in the full square
+  // when it fits (no bank conflicts and the cheaper address), else in the
+  // packed triangle or rows of it
+  const bool square = R == U && U * Up <= kBand;
+  const int tri0 = tri_base(r0, U) + r0, nacc = square ? U * Up : tri_base(r0 + R, U) + r0 + R - tri0;
   for (int j = threadIdx.x; j < nacc; j += blockDim.x) acc[j] = 0.0;
   __syncthreads();
-  // wave-uniform (readfirstlane), so the pair loop, its metadata and the
-  // column sweeps are scalar
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), nw = blockDim.x >> 6;
   const int64_t k0 = a.tube_off[T], k1 = a.tube_off[T + 1];
-  auto meta = [&](int64_t k, PairRegs &p) {
-    const int64_t kk = k < k1 ? k : k0;
-    p.m = a.pm[kk];
-    p.w = a.pw[kk];
-  };
-  // K_i c_alpha in registers (selected, not indexed, so no memory access sits
-  // behind the pipelined loads)
-  const double kc0 = a.KC0, kc1 = a.KC1, kc2 = a.KC2;
-  auto weight = [kc0, kc1, kc2](const PairRegs &p) {
-    const int axis = (int)((unsigned)p.m.w >> 30);
-    return p.w * (axis == 0 ? kc0 : (axis == 1 ? kc1 : kc2));
-  };
-  // register path, software-pipelined: pair k in registers, the entries of
-  // pair k + nw in flight, the metadata of pair k + 2 nw in flight (issued
-  // first, so each wait leaves the newer loads outstanding)
-  int64_t k = k0 + wave;
-  bool long_pairs = false;
-  if (k < k1) {
-    PairRegs cur, nxt, far;
-    meta(k, cur);
-    load_entries(cur, a.ent_slot, a.ent_val);
-    meta(k + nw, nxt);
-    while (k < k1) {
-      meta(k + 2 * nw, far);
-      load_entries(nxt, a.ent_slot, a.ent_val);
-      PairRegs p = cur;
-      p.w = weight(cur);
-      if (pair_nl(p.m) <= kRegEntries && pair_nr(p.m) <= kRegEntries) {
-        if (layout == kSquare1) pair_products_reg<kSquare1>(acc, Up, r0, R, U, p);
-        else if (layout == kTri1) pair_products_reg<kTri1>(acc, Up, r0, R, U, p);
-        else pair_products_reg<kBand2>(acc, Up, r0, R, U, p);
-      } else {
-        long_pairs = true;
-      }
-      cur = nxt;
-      nxt = far;
-      k += nw;
-    }
-  }
-  // pairs with a half-ray longer than the register path holds
-  if (__ballot(long_pairs)) {
-    for (k = k0 + wave; k < k1; k += nw) {
-      PairRegs p;
-      meta(k, p);
-      if (pair_nl(p.m) > kRegEntries || pair_nr(p.m) > kRegEntries)
-        if (layout == kSquare1) pair_products_mem<kSquare1>(acc, Up, r0, R, U, p.m, weight(p), a.ent_slot, a.ent_val);
-        else if (layout == kTri1) pair_products_mem<kTri1>(acc, Up, r0, R, U, p.m, weight(p), a.ent_slot, a.ent_val);
-        else pair_products_mem<kBand2>(acc, Up, r0, R, U, p.m, weight(p), a.ent_slot, a.ent_val);
-    }
-  }
+  const int axis = (int)((unsigned)a.pm[k0].w >> 30);  // a tube has at least one pair
+  const double kc = axis == 0 ? a.KC0 : (axis == 1 ? a.KC1 : a.KC2);
+  if (square) band_products<kSquare>(acc, U, Up, r0, R, a, a.ent_val, a.ent_val, kc, kc, k0, k1);
+  else if (R == U) band_products<kTri>(acc, U, Up, r0, R, a, a.ent_val, a.ent_val, kc, kc, k0, k1);
+  else band_products<kTriBand>(acc, U, Up, r0, R, a, a.ent_val, a.ent_val, kc, kc, k0, k1);
   __syncthreads();
-  double *out = a.blk + a.blk_off[T] + (int64_t)r0 * U;
-  if (layout != kBand2) {
-    for (int j = threadIdx.x; j < U * U; j += blockDim.x) {
-      const int i = j / U, t = j - i * U;
+  // every entry whose smaller index lies in the band, one wavefront per row
+  const int lane = threadIdx.x & 63;
+  double *blk = a.blk + a.blk_off[T];
+  for (int i = r0 + (threadIdx.x >> 6); i < U; i += blockDim.x >> 6) {
+    double *out = blk + (int64_t)i * U;
+    const int t1 = i < r0 + R ? U : r0 + R;
+    for (int t = r0 + lane; t < t1; t += 64) {
       const int lo = i < t ? i : t, hi = i < t ? t : i;
-      const double v = acc[(layout == kTri1 ? tri_base(lo, U) : lo * Up) + hi];
-      out[j] = i == t ? v + v : v;
-    }
-  } else {
-    for (int j = threadIdx.x; j < R * U; j += blockDim.x) {
-      const int i = j / U, t = j - i * U;
-      out[j] = acc[i * Up + t];
+      const double v = acc[(square ? lo * Up : tri_base(lo, U) - tri0) + hi];
+      out[t] = i == t ? v + v : v;
     }
   }
 }
@@ -501,96 +501,27 @@ __global__ void __launch_bounds__(1024) k_tube_accum(AccumArgs a) {
 // (rows: test node, columns: trial node).  Not symmetric, so both products
 // of every pair go into full rows; an item is processed in row bands that
 // fit the square layout, the pairs re-read per band.
-__device__ void form_products_mem(double *acc, int Up, int rb, int Rb, const int4 m, double wl, double wr,
-                                  const int32_t *__restrict__ slot, const double *__restrict__ va,
-                                  const double *__restrict__ vb) {
-  const int lane = threadIdx.x & 63;
-  const int nl = __builtin_amdgcn_readfirstlane(pair_nl(m)), nr = __builtin_amdgcn_readfirstlane(pair_nr(m));
-  for (int role = 0; role < 2; role++) {
-    // role 0: rows r (beta), columns l (alpha, w cl); role 1: rows l, columns r (w cr)
-    const int nrow = role ? nl : nr, ncol = role ? nr : nl;
-    const int erow = role ? m.x : m.y, ecol = role ? m.y : m.x;
-    const double w = role ? wr : wl;
-    for (int j0 = 0; j0 < nrow; j0 += 64) {
-      const int ex = erow + (j0 + lane < nrow ? j0 + lane : j0);
-      const int xs = slot[ex];
-      const double xv = vb[ex];
-      const bool xok = j0 + lane < nrow && xs >= rb && xs < rb + Rb;
-      if (__ballot(xok) == 0) continue;
-      for (int c0 = 0; c0 < ncol; c0 += 64) {
-        const int ec = ecol + (c0 + lane < ncol ? c0 + lane : c0);
-        const int cn = ncol - c0 < 64 ? ncol - c0 : 64;
-        sweep_cols<kBand2>(acc, (xs - rb) * Up, xs, 0, Up, xv, xok, slot[ec], va[ec] * w, cn);
-      }
-    }
-  }
-}
-
-__global__ void __launch_bounds__(1024) k_tube_form(AccumArgs a) {
+__global__ void __launch_bounds__(kAccumThreads) k_tube_form(AccumArgs a) {
   extern __shared__ double acc[];
   const int4 it = a.items[blockIdx.x];
   const int64_t T = it.x;
   const int r0 = it.y, R = it.z, U = it.w, Up = band_stride(U);
-  const int Rsq = kBandDoubles / Up;  // rows of one square band (>= 39 for |U_T| <= 512)
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), nw = blockDim.x >> 6;
+  const int Rsq = kBand / Up;  // rows of one square band
   const int lane = threadIdx.x & 63;
   const int64_t k0 = a.tube_off[T], k1 = a.tube_off[T + 1];
+  // role 0: rows l (beta), columns r (alpha, cr); role 1: rows r, columns l (cl)
+  const int axis = (int)((unsigned)a.pm[k0].w >> 30);
+  const double kc0 = axis == 0 ? a.cr0 : (axis == 1 ? a.cr1 : a.cr2);
+  const double kc1 = axis == 0 ? a.cl0 : (axis == 1 ? a.cl1 : a.cl2);
   for (int rb = r0; rb < r0 + R; rb += Rsq) {
     const int Rb = (r0 + R - rb) < Rsq ? (r0 + R - rb) : Rsq;
     for (int j = threadIdx.x; j < Rb * Up; j += blockDim.x) acc[j] = 0.0;
     __syncthreads();
-    for (int64_t k = k0 + wave; k < k1; k += nw) {
-      PairRegs p;
-      p.m = a.pm[k];
-      p.w = a.pw[k];
-      const int axis = (int)((unsigned)p.m.w >> 30);
-      const double wl = p.w * (axis == 0 ? a.cl[0] : (axis == 1 ? a.cl[1] : a.cl[2]));
-      const double wr = p.w * (axis == 0 ? a.cr[0] : (axis == 1 ? a.cr[1] : a.cr[2]));
-      const int nl = __builtin_amdgcn_readfirstlane(pair_nl(p.m)), nr = __builtin_amdgcn_readfirstlane(pair_nr(p.m));
-      if (nl > kRegEntries || nr > kRegEntries) {
-        form_products_mem(acc, Up, rb, Rb, p.m, wl, wr, a.ent_slot, a.ent_val, a.val_b);
-        continue;
-      }
-      // entries `lane` and `lane + 64` of both sides, both value sets
-      // (indices clamped to a valid entry; lanes past the end are masked)
-      int ls[2], rs[2];
-      double la[2], ra[2], lb[2], rbv[2];
-#pragma unroll
-      for (int h = 0; h < 2; h++) {
-        const int kl = 64 * h + lane;
-        const int il = nl > 0 ? p.m.x + (kl < nl ? kl : 0) : 0;
-        const int ir = nr > 0 ? p.m.y + (kl < nr ? kl : 0) : 0;
-        ls[h] = a.ent_slot[il];
-        rs[h] = a.ent_slot[ir];
-        la[h] = a.ent_val[il];
-        ra[h] = a.ent_val[ir];
-        lb[h] = a.val_b[il];
-        rbv[h] = a.val_b[ir];
-      }
-#pragma unroll
-      for (int role = 0; role < 2; role++) {
-        const int nrow = role ? nl : nr, ncol = role ? nr : nl;
-        const double w = role ? wr : wl;
-#pragma unroll
-        for (int h = 0; h < 2; h++) {
-          const int xs = role ? ls[h] : rs[h];
-          const double xv = role ? lb[h] : rbv[h];
-          const bool xok = 64 * h + lane < nrow && xs >= rb && xs < rb + Rb;
-          if (__ballot(xok) == 0) continue;
-          const int rowbase = (xs - rb) * Up;
-          sweep_cols<kBand2>(acc, rowbase, xs, 0, Up, xv, xok, role ? rs[0] : ls[0], (role ? ra[0] : la[0]) * w,
-                             ncol < 64 ? ncol : 64);
-          if (ncol > 64)
-            sweep_cols<kBand2>(acc, rowbase, xs, 0, Up, xv, xok, role ? rs[1] : ls[1], (role ? ra[1] : la[1]) * w,
-                               ncol - 64);
-        }
-      }
-    }
+    band_products<kFull>(acc, U, Up, rb, Rb, a, a.val_b, a.ent_val, kc0, kc1, k0, k1);
     __syncthreads();
-    double *out = a.blk + a.blk_off[T] + (int64_t)rb * U;
-    for (int j = threadIdx.x; j < Rb * U; j += blockDim.x) {
-      const int i = j / U, t = j - i * U;
-      out[j] = acc[i * Up + t];
+    for (int i = threadIdx.x >> 6; i < Rb; i += blockDim.x >> 6) {
+      double *out = a.blk + a.blk_off[T] + (int64_t)(rb + i) * U;
+      for (int t = lane; t < U; t += 64) out[t] = acc[i * Up + t];
     }
     __syncthreads();  // the band is written before the next one is cleared
   }
@@ -1338,13 +1269,12 @@ int build_tubes(fpde_mesh *m, Plan &P, double kappa, hipStream_t s) {
 
   uint32_t *key = nullptr, *key2 = nullptr;
   int32_t *val = nullptr, *head = nullptr, *tid = nullptr;
-  int64_t *u_cnt = nullptr, *row_cnt = nullptr, *cursor = nullptr, *nb = nullptr, *usq = nullptr,
-          *band_off = nullptr;
+  int64_t *u_cnt = nullptr, *row_cnt = nullptr, *cursor = nullptr, *usq = nullptr;
   void *tmp = nullptr;
   size_t tmp_bytes = 0;
   auto cleanup = [&]() {
     dfree(key); dfree(key2); dfree(val); dfree(head); dfree(tid);
-    dfree(u_cnt); dfree(row_cnt); dfree(cursor); dfree(nb); dfree(usq); dfree(band_off);
+    dfree(u_cnt); dfree(row_cnt); dfree(cursor); dfree(usq);
     if (tmp) (void)hipFree(tmp);
     tmp = nullptr;
   };
@@ -1429,30 +1359,43 @@ int build_tubes(fpde_mesh *m, Plan &P, double kappa, hipStream_t s) {
   TRY_T(dalloc(&tp.row_ts, tp.n_u));
   k_row_places<<<(unsigned)nT, 256, 0, s>>>(tp.u_off, nT, tp.tube_u, cursor, tp.row_ts);
 
-  // pass-1 bands and block offsets
-  TRY_T(dalloc(&nb, nT + 1));
+  // block offsets, then the pass-1 work items {tube, first block row, rows, |U_T|}
   TRY_T(dalloc(&usq, nT + 1));
-  TRY_T(dalloc(&band_off, nT + 1));
   TRY_T(dalloc(&tp.blk_off, nT + 1));
-  HIP_T(hipMemsetAsync(nb, 0, sizeof(int64_t) * (nT + 1), s));
   HIP_T(hipMemsetAsync(usq, 0, sizeof(int64_t) * (nT + 1), s));
-  k_band_count<<<nblocks(nT), 256, 0, s>>>(tp.u_off, nT, nb, usq);
-  HIP_T(hipcub::DeviceScan::ExclusiveSum(nullptr, need, nb, band_off, (int)(nT + 1), s));
+  k_block_sizes<<<nblocks(nT), 256, 0, s>>>(tp.u_off, nT, usq);
+  HIP_T(hipcub::DeviceScan::ExclusiveSum(nullptr, need, usq, tp.blk_off, (int)(nT + 1), s));
   TRY_T(scratch(need));
-  HIP_T(hipcub::DeviceScan::ExclusiveSum(tmp, tmp_bytes, nb, band_off, (int)(nT + 1), s));
   HIP_T(hipcub::DeviceScan::ExclusiveSum(tmp, tmp_bytes, usq, tp.blk_off, (int)(nT + 1), s));
-  HIP_T(hipMemcpyAsync(&tp.n_items, band_off + nT, sizeof(int64_t), hipMemcpyDeviceToHost, s));
+  std::vector<int64_t> uo(nT + 1), to(nT + 1);
   HIP_T(hipMemcpyAsync(&tp.blk_n, tp.blk_off + nT, sizeof(int64_t), hipMemcpyDeviceToHost, s));
+  HIP_T(hipMemcpyAsync(uo.data(), tp.u_off, sizeof(int64_t) * (nT + 1), hipMemcpyDeviceToHost, s));
+  HIP_T(hipMemcpyAsync(to.data(), tp.tube_off, sizeof(int64_t) * (nT + 1), hipMemcpyDeviceToHost, s));
   HIP_T(hipStreamSynchronize(s));
-  TRY_T(dalloc(&tp.items, tp.n_items));
-  k_bands<<<nblocks(nT), 256, 0, s>>>(tp.u_off, nT, band_off, tp.items);
-  // size statistics
   {
-    std::vector<int64_t> uo(nT + 1);
-    HIP_T(hipMemcpyAsync(uo.data(), tp.u_off, sizeof(int64_t) * (nT + 1), hipMemcpyDeviceToHost, s));
-    HIP_T(hipStreamSynchronize(s));
     tp.max_u = 0;
     for (int64_t T = 0; T < nT; T++) tp.max_u = std::max<int64_t>(tp.max_u, uo[T + 1] - uo[T]);
+    // largest tubes first (by pairs times nodes), so that none starts last
+    std::vector<int64_t> order(nT);
+    for (int64_t T = 0; T < nT; T++) order[T] = T;
+    std::stable_sort(order.begin(), order.end(), [&](int64_t x, int64_t y) {
+      return (to[x + 1] - to[x]) * (uo[x + 1] - uo[x]) > (to[y + 1] - to[y]) * (uo[y + 1] - uo[y]);
+    });
+    std::vector<int4> items;
+    for (const int64_t T : order) {
+      const int U = (int)(uo[T + 1] - uo[T]);
+      for (int r0 = 0; r0 < U;) {
+        const int R = band_rows(U, r0, kBand);
+        items.push_back(make_int4((int)T, r0, R, U));
+        r0 += R;
+      }
+    }
+    tp.n_items = (int64_t)items.size();
+    TRY_T(dalloc(&tp.items, items.size() > 0 ? items.size() : 1));
+    if (!items.empty()) {
+      HIP_T(hipMemcpyAsync(tp.items, items.data(), sizeof(int4) * items.size(), hipMemcpyHostToDevice, s));
+      HIP_T(hipStreamSynchronize(s));
+    }
   }
   HIP_T(hipGetLastError());
   f = take_flag(m, s);
@@ -1660,7 +1603,7 @@ static int accumulate_tube_blocks(fpde_mesh *m, Plan &P, const fpde_params *p, h
   const long ta = timer_begin(m, s, FPDE_STAGE_ACCUM);
   // deterministic: one wavefront per item walks the tube's pairs in order
   if (tp.n_items > 0)
-    k_tube_accum<<<(unsigned)tp.n_items, p->deterministic ? 64 : 1024, sizeof(double) * kBandDoubles, s>>>(a);
+    k_tube_accum<<<(unsigned)tp.n_items, p->deterministic ? 64 : kAccumThreads, sizeof(double) * kBand, s>>>(a);
   timer_end(m, FPDE_STAGE_ACCUM, ta, s);
   return FPDE_OK;
 }
@@ -1754,11 +1697,13 @@ int launch_form_tubes(fpde_mesh *m, Plan &P, const double cl[3], const double cr
   a.val_b = P.ent_val2;
   a.blk_off = tp.blk_off;
   a.blk = tp.blk;
-  for (int i = 0; i < 3; i++) {
-    a.cl[i] = cl[i];
-    a.cr[i] = cr[i];
-  }
-  if (tp.n_items > 0) k_tube_form<<<(unsigned)tp.n_items, 1024, sizeof(double) * kBandDoubles, s>>>(a);
+  a.cl0 = cl[0];
+  a.cl1 = cl[1];
+  a.cl2 = cl[2];
+  a.cr0 = cr[0];
+  a.cr1 = cr[1];
+  a.cr2 = cr[2];
+  if (tp.n_items > 0) k_tube_form<<<(unsigned)tp.n_items, kAccumThreads, sizeof(double) * kBand, s>>>(a);
   GatherArgs gch;
   FPDE_TRY(gather_args(m, P, lda, s, gch));
   k_tube_gather<double><<<gather_grid(m->ndof), 256, sizeof(double) * gch.chunk, s>>>(gch, A);

@@ -483,8 +483,14 @@ void free_plan(Plan &P) {
   P = Plan();
 }
 
-// tube cell edge of the accumulation, in mean element edges
-constexpr double kTubeCell = 1.0;
+// Tube cell edge of the accumulation, in mean element edges.  Narrower tubes
+// have smaller node sets (blocks that fit the LDS whole, fuller 128-wide
+// regions on the matrix cores) but more of them (block bytes and row places).
+// Two assemblies, pass 1 and rows, at cells of 1.0 / 0.8 / 0.7 / 0.6 / 0.5:
+// FP64 82 924 elements 5.5 / 4.9 / 4.9 / 5.0 / 5.2 ms, 19 672 elements (4
+// points) 0.31 / 0.32 / 0.33 / 0.35 / 0.40 ms, mixed 151 907 elements
+// 41.4 / 39.7 / 38.1 / 37.2 / 37.8 ms.
+constexpr double kTubeCell = 0.7;
 
 static int build_plan(fpde_mesh *m, Plan &P, int nq, int max_steps, hipStream_t s) {
   QuadRule rule;
