@@ -1,12 +1,10 @@
-// Load vector, matrix-free product and adjoint sums (Sec. 2.1: K = sum_E K_E
-// with element quadrature); the dense accumulation of K itself is in the
-// tube pass (one block per group of parallel chords).
+// Load vector, adjoint sums and the assembly calls (Sec. 2.1: K = sum_E K_E
+// with element quadrature); the dense accumulation of K itself and the
+// matrix-free product are in the tube passes (one block per group of parallel
+// chords).
 //
 //   K_jk = sum_i K_i c_alpha sum_g w_g [R_gi(j) L_gi(k) + L_gi(j) R_gi(k)]
 //
-// The matrix-free product y = K x takes the dots of every half-ray vector
-// with x and then, row by row, gathers W * value * (partner's dot) over the
-// node -> entry transpose built once per mesh and rule.
 #include <cmath>
 
 #include "fpde_internal.h"
@@ -14,19 +12,6 @@
 namespace fpde {
 
 int walk_adjoint(fpde_mesh *m, Plan *P, double alpha, const double *u, const double *lam, hipStream_t s);
-
-struct ContractArgs {
-  const int64_t *row_off;
-  const int4 *meta;       // per incidence: entry, partner offset, partner length << 2 | axis, partner
-  const double *w;        // per incidence: Gauss weight w_g
-  const double *wv;       // per incidence: w_g times its entry's value (matrix-free product)
-  const int32_t *ent_dof;
-  const double *ent_val;
-  int64_t ndof, lda;
-  int chunk;
-  double KC0, KC1, KC2;   // K_i c_alpha
-  __device__ __forceinline__ double KC(int i) const { return i == 0 ? KC0 : (i == 1 ? KC1 : KC2); }
-};
 
 struct LoadArgs {
   const int32_t *vert_of_dof, *vt_off, *vt_tet, *tet;
@@ -92,46 +77,6 @@ __global__ void __launch_bounds__(256) k_load(LoadArgs a, double *__restrict__ b
   if (lane == 0) b[j] = sum;
 }
 
-// d[h] = sum over entries of half-ray h of value * x[dof]; 16 lanes per
-// half-ray, so a load instruction reads 16 consecutive entries of each of
-// four half-rays
-__global__ void __launch_bounds__(256) k_ray_dot(const int64_t *__restrict__ off, const int32_t *__restrict__ dof,
-                                                 const double *__restrict__ val, const double *__restrict__ x,
-                                                 int64_t n_half, double *__restrict__ d) {
-  const int gl = threadIdx.x & 15;
-  const int64_t h = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 4;
-  if (h >= n_half) return;  // the whole group of 16 shares h
-  double s = 0.0;
-  for (int64_t e = off[h] + gl; e < off[h + 1]; e += 16) s = fma(val[e], x[dof[e]], s);
-#pragma unroll
-  for (int o = 8; o > 0; o >>= 1) s += __shfl_xor(s, o, 16);
-  if (gl == 0) d[h] = s;
-}
-
-// wv[p] = w_g value_e for incidence p (entry e = meta[p].x): the entry
-// values in the node -> entry order, so the product streams them
-__global__ void k_inc_wv(const int4 *__restrict__ meta, const double *__restrict__ w,
-                         const double *__restrict__ ent_val, int64_t n, double *__restrict__ wv) {
-  const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (p < n) wv[p] = w[p] * ent_val[meta[p].x];
-}
-
-// y_j = sum over entries e on node j of W(h_e) value_e d[partner(h_e)];
-// one wavefront per row, lanes stride over the row's entries
-__global__ void __launch_bounds__(256) k_apply_rows(ContractArgs c, const double *__restrict__ d,
-                                                    double *__restrict__ y) {
-  const int lane = threadIdx.x & 63;
-  const int64_t j = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (j >= c.ndof) return;
-  double s = 0.0;
-  for (int64_t p = c.row_off[j] + lane; p < c.row_off[j + 1]; p += 64) {
-    const int4 mt = c.meta[p];
-    s += c.wv[p] * c.KC(mt.z & 3) * d[mt.w];
-  }
-  for (int o = 32; o > 0; o >>= 1) s += __shfl_down(s, o, 64);
-  if (lane == 0) y[j] = s;
-}
-
 // Per-block partial sums of S_i, T_i (6 values) over Gauss points.
 __global__ void __launch_bounds__(256) k_adjoint_partial(const double *__restrict__ adj, const double *__restrict__ vol,
                                                          int64_t G, int nq, const double *__restrict__ wq,
@@ -162,23 +107,6 @@ __global__ void __launch_bounds__(256) k_adjoint_partial(const double *__restric
 
 static inline unsigned nblk(int64_t n, int b = 256) { return (unsigned)((n + b - 1) / b); }
 
-static ContractArgs contract_args(fpde_mesh *m, const Plan &P, const fpde_params *p, int64_t lda) {
-  Order o = order_scalars(p->alpha);
-  ContractArgs c{};
-  c.row_off = P.row_off;
-  c.meta = P.inc_meta;
-  c.w = P.inc_w;
-  c.ent_dof = P.ent_dof;
-  c.ent_val = P.ent_val;
-  c.ndof = m->ndof;
-  c.lda = lda;
-  c.chunk = (int)(m->ndof < 8192 ? (m->ndof > 0 ? m->ndof : 1) : 8192);
-  c.KC0 = p->K[0] * o.c_alpha;
-  c.KC1 = p->K[1] * o.c_alpha;
-  c.KC2 = p->K[2] * o.c_alpha;
-  return c;
-}
-
 int launch_load(fpde_mesh *m, const fpde_params *p, double *b, const double *f_gauss, hipStream_t s) {
   if (m->ndof == 0) return FPDE_OK;
   LoadArgs a{};
@@ -204,33 +132,6 @@ int launch_load(fpde_mesh *m, const fpde_params *p, double *b, const double *f_g
   k_load<<<nblk(m->ndof * 64), 256, 0, s>>>(a, b);
   timer_end(m, FPDE_STAGE_LOAD, t, s);
   FPDE_HIP(hipGetLastError());
-  return FPDE_OK;
-}
-
-// y = K x from the stored derivative vectors (plan + values for p->alpha)
-int apply_matfree(fpde_mesh *m, Plan *P, const fpde_params *p, const double *x, double *y, double *dscratch,
-                  hipStream_t s) {
-  // the merged entries of the mixed-precision plan, when they hold these values
-  if (m->ndof > 0 && merged_apply_ready(*P)) return apply_merged(m, *P, p, x, y, s);
-  if (!P->inc_wv) FPDE_TRY(dalloc(&P->inc_wv, P->n_ent > 0 ? P->n_ent : 1));
-  ContractArgs c = contract_args(m, *P, p, 0);
-  c.wv = P->inc_wv;
-  const long t = timer_begin(m, s, FPDE_STAGE_APPLY);
-  if (P->inc_wv_version != P->values_version) {
-    if (P->n_ent > 0) k_inc_wv<<<nblk(P->n_ent), 256, 0, s>>>(P->inc_meta, P->inc_w, P->ent_val, P->n_ent, P->inc_wv);
-    P->inc_wv_version = P->values_version;
-  }
-  k_ray_dot<<<nblk(16 * P->n_half), 256, 0, s>>>(P->off, P->ent_dof, P->ent_val, x, P->n_half, dscratch);
-  k_apply_rows<<<nblk(m->ndof, 4), 256, 0, s>>>(c, dscratch, y);
-  timer_end(m, FPDE_STAGE_APPLY, t, s);
-  FPDE_HIP(hipGetLastError());
-  return FPDE_OK;
-}
-
-int apply_scratch(fpde_mesh *m, Plan *P, double **d) {
-  // the adjoint buffer (4 per half-ray) doubles as the per-half-ray dot scratch
-  if (!P->adj) FPDE_TRY(dalloc(&P->adj, 4 * P->n_half));
-  *d = P->adj;
   return FPDE_OK;
 }
 
@@ -324,9 +225,7 @@ extern "C" int fpde_apply(fpde_mesh *m, const fpde_params *p, const double *x, d
   Plan *P = nullptr;
   FPDE_TRY(plan_for(m, p->quad_points, p->max_steps, s, &P));
   FPDE_TRY(ensure_values(m, P, p->alpha, s));
-  double *d = nullptr;
-  FPDE_TRY(apply_scratch(m, P, &d));
-  FPDE_TRY(apply_matfree(m, P, p, x, y, d, s));
+  FPDE_TRY(apply_matfree(m, P, p, x, y, s));
   int f = take_flag(m, s);
   return f < 0 ? f : (f > 0 ? FPDE_EHIP : FPDE_OK);
 }

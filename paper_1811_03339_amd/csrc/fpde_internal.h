@@ -65,25 +65,20 @@ struct TubePlan {
   // index within its pair, and per sorted pair its tube
   bool mfma_planned = false, mfma_ok = false;
   int4 *mitems = nullptr;
-  int64_t n_mitems = 0, n_mk = 0;
+  int64_t n_mitems = 0;
   int2 *texp = nullptr;
   int64_t *mk_pair = nullptr;
   uint32_t *mk_meta = nullptr;
   float *mk_val = nullptr;
   uint16_t *mg_idx = nullptr;
   int32_t *pk_tube = nullptr;
-  // the FP64 matrix-free product on the merged entries: per merged entry
-  // its node, FP64 value and position in node order (mpos); per node its
-  // merged entries (mrow_off; ascending merged index), per such incidence
-  // the partner's dot index | axis << 30 and w_g v; the per-pair-side
-  // dots.  The values are rebuilt at every assembly (version mk_version of
-  // the plan's values); mg_pair and mrow_q serve the plan only.
-  bool mapply_ok = false;
-  int32_t *mg_node = nullptr, *mg_pair = nullptr, *mrow_q = nullptr, *mpos = nullptr;
-  int64_t *mrow_off = nullptr;
-  uint32_t *mpart = nullptr;
-  double *mk_val64 = nullptr, *mwv = nullptr, *mdp = nullptr;
-  int64_t mk_version = -1;
+  // the matrix-free product: segments {tube, first pair, past the last pair,
+  // segment of the tube}, per tube the first double of its segments' parts of
+  // y (n_tubes + 1), and those parts (allocated on first use)
+  int64_t n_aitems = 0, n_part = 0;
+  int4 *aitems = nullptr;
+  int64_t *seg_off = nullptr;
+  double *part = nullptr;
 };
 
 // Symbolic phase of one rule: derivative-vector sizes and the row transpose.
@@ -107,10 +102,6 @@ struct Plan {
   // partner half-ray} and the quadrature weight w_g of its Gauss point
   int4 *inc_meta = nullptr;
   double *inc_w = nullptr;
-  // per incidence: w_g times its entry's value (first value set), built by
-  // the matrix-free product when the values changed since (versions)
-  double *inc_wv = nullptr;
-  int64_t values_version = 0, inc_wv_version = -1;
   double *adj = nullptr;      // 4 n_half scratch for the adjoint dots
   int64_t pairs = 0;          // sum over (g, i) of |L| |R|
   int64_t max_ent = 0;        // largest entry count of one half-ray
@@ -236,14 +227,9 @@ int launch_form_tubes(fpde_mesh *m, Plan &P, const double cl[3], const double cr
                       hipStream_t s);
 int launch_contract_tubes_csr(fpde_mesh *m, Plan &P, const fpde_params *p, const int64_t *row_ptr,
                               const int32_t *col, double *val, hipStream_t s);
-// matrix-free y = K x and its scratch (assemble.hip)
-// y = K x on the merged entries of the mixed-precision tube plan, when they
-// hold the plan's current values (merged_apply_ready); FPDE_OK or an error.
-bool merged_apply_ready(const Plan &P);
-int apply_merged(fpde_mesh *m, Plan &P, const fpde_params *p, const double *x, double *y, hipStream_t s);
-int apply_matfree(fpde_mesh *m, Plan *P, const fpde_params *p, const double *x, double *y, double *dscratch,
-                  hipStream_t s);
-int apply_scratch(fpde_mesh *m, Plan *P, double **d);
+// matrix-free y = K x from the plan's values, and the diagonal of K
+int apply_matfree(fpde_mesh *m, Plan *P, const fpde_params *p, const double *x, double *y, hipStream_t s);
+int matfree_diagonal(fpde_mesh *m, Plan *P, const fpde_params *p, double *d, hipStream_t s);
 // load vector b for the Riesz problem (assemble.hip)
 int launch_load(fpde_mesh *m, const fpde_params *p, double *b, const double *f_gauss, hipStream_t s);
 // dense SPD solve with a workspace handle (solve.hip); a workspace handle

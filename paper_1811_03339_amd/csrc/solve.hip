@@ -28,10 +28,6 @@
 
 namespace fpde {
 
-int apply_matfree(fpde_mesh *m, Plan *P, const fpde_params *p, const double *x, double *y, double *dscratch,
-                  hipStream_t s);
-int apply_scratch(fpde_mesh *m, Plan *P, double **d);
-
 // inverse of the lower-triangular L held in LDS (rows >= nb are identity);
 // lane j builds column j of inv(L) in X by forward substitution (L reads
 // are broadcasts, X accesses are one column per lane) and stores it to Linv
@@ -675,9 +671,7 @@ static int solve_with_factor(fpde_mesh *m, const fpde_params *p, const void *L, 
       Plan *P = nullptr;
       FPDE_TRY(plan_for(m, p->quad_points, p->max_steps, s, &P));
       FPDE_TRY(ensure_values(m, P, p->alpha, s));
-      double *d = nullptr;
-      FPDE_TRY(apply_scratch(m, P, &d));
-      FPDE_TRY(apply_matfree(m, P, p, u, y, d, s));
+      FPDE_TRY(apply_matfree(m, P, p, u, y, s));
       k_sub<<<nblk(n), 256, 0, s>>>(b, y, r, n);
       double rn = 0, bn = 0;
       FPDE_TRY(norm2(m, r, &rn, s));
@@ -695,14 +689,12 @@ static int solve_with_factor(fpde_mesh *m, const fpde_params *p, const void *L, 
   Plan *P = nullptr;
   FPDE_TRY(plan_for(m, p->quad_points, p->max_steps, s, &P));
   FPDE_TRY(ensure_values(m, P, p->alpha, s));
-  double *d = nullptr;
-  FPDE_TRY(apply_scratch(m, P, &d));
   double bn = 0;
   FPDE_TRY(norm2(m, bb, &bn, s));
   double rel = 0;
   int it = 0;
   for (;;) {
-    FPDE_TRY(apply_matfree(m, P, p, u, y, d, s));
+    FPDE_TRY(apply_matfree(m, P, p, u, y, s));
     k_sub<<<nblk(n), 256, 0, s>>>(bb, y, r, n);
     double rn = 0;
     FPDE_TRY(norm2(m, r, &rn, s));

@@ -17,9 +17,8 @@
 //                             either the CSR matrix or the matrix-free
 //                             product of the derivative vectors (no N^2
 //                             storage at all); the diagonal of K comes from
-//                             the CSR row or, matrix-free, from each node's
-//                             entries and the matching entries of their
-//                             partner half-rays.
+//                             the CSR row or, matrix-free, from the pairs of
+//                             half-rays that both meet a node.
 #include <cmath>
 #include <vector>
 
@@ -121,40 +120,6 @@ __global__ void k_csr_diag(const int64_t *__restrict__ row_ptr, const int32_t *_
     else hi = mid;
   }
   d[j] = v;
-}
-
-// d_j = K_jj matrix-free: K_jj = sum_i K_i c_alpha sum_g w_g 2 L_gi(j) R_gi(j);
-// over the incidences of node j (entry e of half-ray h, partner half-ray h'
-// on the other side of the same (g, i)): W v_e (sum of h' entries at j).
-// Every (g, i) in which j has entries on both sides is seen from both sides,
-// which gives the factor 2.
-struct DiagArgs {
-  const int64_t *row_off;
-  const int4 *meta;
-  const double *w;
-  const int32_t *ent_dof;
-  const double *ent_val;
-  int64_t ndof;
-  double KC0, KC1, KC2;
-};
-
-__global__ void __launch_bounds__(256) k_matfree_diag(DiagArgs a, double *__restrict__ d) {
-  const int lane = threadIdx.x & 63;
-  const int64_t j = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (j >= a.ndof) return;
-  double s = 0.0;
-  for (int64_t p = a.row_off[j] + lane; p < a.row_off[j + 1]; p += 64) {
-    const int4 mt = a.meta[p];
-    const int64_t po = mt.y, pl = mt.z >> 2;
-    const int ax = mt.z & 3;
-    double pv = 0.0;
-    for (int64_t q = po; q < po + pl; q++)
-      if (a.ent_dof[q] == (int32_t)j) pv += a.ent_val[q];
-    const double kc = ax == 0 ? a.KC0 : (ax == 1 ? a.KC1 : a.KC2);
-    s += a.w[p] * kc * a.ent_val[mt.x] * pv;
-  }
-  for (int o = 32; o > 0; o >>= 1) s += __shfl_down(s, o, 64);
-  if (lane == 0) d[j] = s;
 }
 
 // Per-block partial sums of x.y (blocks of 256 threads, grid-stride)
@@ -359,12 +324,9 @@ extern "C" int fpde_cg_solve(fpde_mesh *m, const fpde_params *p, const int64_t *
   CgWork w;
   FPDE_TRY(ensure_cg(m, &w));
   Plan *P = nullptr;
-  double *dsc = nullptr;
-  const Order o = order_scalars(p->alpha);
   if (!csr) {
     FPDE_TRY(plan_for(m, p->quad_points, p->max_steps, s, &P));
     FPDE_TRY(ensure_values(m, P, p->alpha, s));
-    FPDE_TRY(apply_scratch(m, P, &dsc));
   }
   auto op = [&](const double *x, double *y) -> int {
     if (csr) {
@@ -373,24 +335,14 @@ extern "C" int fpde_cg_solve(fpde_mesh *m, const fpde_params *p, const int64_t *
       timer_end(m, FPDE_STAGE_SPMV, t, s);
       return hipGetLastError() == hipSuccess ? FPDE_OK : FPDE_EHIP;
     }
-    return apply_matfree(m, P, p, x, y, dsc, s);
+    return apply_matfree(m, P, p, x, y, s);
   };
   const long t_all = timer_begin(m, s, FPDE_STAGE_CG);
   // diagonal of K for the Jacobi preconditioner
   if (csr) {
     k_csr_diag<<<blocks_of(n), 256, 0, s>>>(row_ptr, col, val, n, w.d);
   } else {
-    DiagArgs da{};
-    da.row_off = P->row_off;
-    da.meta = P->inc_meta;
-    da.w = P->inc_w;
-    da.ent_dof = P->ent_dof;
-    da.ent_val = P->ent_val;
-    da.ndof = n;
-    da.KC0 = p->K[0] * o.c_alpha;
-    da.KC1 = p->K[1] * o.c_alpha;
-    da.KC2 = p->K[2] * o.c_alpha;
-    k_matfree_diag<<<blocks_of(n, 4), 256, 0, s>>>(da, w.d);
+    FPDE_TRY(matfree_diagonal(m, P, p, w.d, s));
   }
   k_zero1<<<1, 1, 0, s>>>(w.bad);
   k_cg_start<<<blocks_of(n), 256, 0, s>>>(b, w.d, u, w.r, w.z, w.p, w.dinv, n, w.bad);

@@ -711,16 +711,13 @@ __global__ void __launch_bounds__(64) k_merge_pairs(const int64_t *__restrict__ 
                                                     const int32_t *__restrict__ ent_slot, int64_t *__restrict__ cnt,
                                                     const int64_t *__restrict__ mk_pair, uint16_t *__restrict__ midx,
                                                     uint32_t *__restrict__ mk_meta, int32_t *__restrict__ pk_tube,
-                                                    int *__restrict__ maxc, const int64_t *__restrict__ u_off,
-                                                    const int32_t *__restrict__ tube_u, int32_t *__restrict__ mg_node,
-                                                    int32_t *__restrict__ mg_pair) {
+                                                    int *__restrict__ maxc) {
   __shared__ int tbl[kMergeSlots];
   const int lane = threadIdx.x;
   const int64_t k = blockIdx.x;
   if (k >= n_pairs) return;  // the whole block (one wavefront)
   const int4 m = pm[k];
   uint32_t col0 = 0;
-  int64_t u0 = 0;
   if (FILL) {
     int64_t lo = 0, hi = n_tubes - 1;  // the pair's tube: the last T with tube_off[T] <= k
     while (lo < hi) {
@@ -730,7 +727,6 @@ __global__ void __launch_bounds__(64) k_merge_pairs(const int64_t *__restrict__ 
     }
     col0 = 2u * (uint32_t)((k - tube_off[lo]) % kChunkPairs);
     if (lane == 0) pk_tube[k] = (int32_t)lo;
-    u0 = u_off[lo];
   }
   int merged = 0;
   for (int side = 0; side < 2; side++) {
@@ -753,8 +749,6 @@ __global__ void __launch_bounds__(64) k_merge_pairs(const int64_t *__restrict__ 
         if (FILL) {
           const int64_t q = mk_pair[k] + r;
           mk_meta[q] = (uint32_t)sl | ((col0 + (uint32_t)side) << 16);
-          mg_node[q] = tube_u[u0 + sl];
-          mg_pair[q] = (int32_t)k;
         }
       }
       merged += __popcll(bal);
@@ -798,9 +792,7 @@ __global__ void __launch_bounds__(256) k_merge_vals(const int4 *__restrict__ pm,
                                                     const int32_t *__restrict__ pk_tube,
                                                     const uint16_t *__restrict__ midx, int64_t n_pairs,
                                                     const double *__restrict__ val, double KC0, double KC1, double KC2,
-                                                    float *__restrict__ mk_val, double *__restrict__ mk_val64,
-                                                    const int32_t *__restrict__ mpos, double *__restrict__ mwv,
-                                                    int2 *__restrict__ texp) {
+                                                    float *__restrict__ mk_val, int2 *__restrict__ texp) {
   __shared__ double acc[4][kMergeMax];
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const int64_t waves = (int64_t)gridDim.x * 4;
@@ -858,11 +850,8 @@ __global__ void __launch_bounds__(256) k_merge_vals(const int4 *__restrict__ pm,
     wave_lds_sync();
     float vm = 0.f;
     for (int j = lane; j < nm; j += 64) {
-      const double dv = a[j];
-      const float fv = (float)dv;
-      mk_val64[b0 + j] = dv;
+      const float fv = (float)a[j];
       mk_val[b0 + j] = fv;
-      if (mwv) mwv[mpos[b0 + j]] = wk * dv;
       vm = fmaxf(vm, fabsf(fv));
     }
     wave_lds_sync();
@@ -891,150 +880,198 @@ __device__ __forceinline__ int tube_scale_exp(int e) {
   return e < -120 ? -120 : (e > 120 ? 120 : e);
 }
 
-// ---- The FP64 matrix-free product on the merged entries ----
-// With d(k, s) = sum over the merged entries m of side s of pair k of
-// v_m x[node_m], (K x)_j = sum over the merged entries m at node j of
-// K_i c_alpha w_g v_m d(k_m, 1 - s_m): the quadrature of the element
-// products over the half-ray pairs, with the entries of one node in a
-// half-ray summed first (a third of the plan's entries at C5).  The
-// node -> merged entry lists keep increasing merged index (a stable sort),
-// so every sum has a fixed order.
+// ---- The matrix-free product by tubes ----
+//
+// y = K x from the half-ray vectors: per pair the dots l.x and r.x, then
+//   y += w K_i c_alpha ((r.x) l + (l.x) r).
+// A tube's pairs touch only U_T, so a workgroup takes a segment of one tube's
+// pairs with x on U_T and its part of y in LDS, and every entry (slot and
+// value, 12 bytes) is read once, coalesced, and held in registers between its
+// dot and its addition.  Groups of 16 lanes take one pair each; the groups of
+// a segment start at different quarters of it, so that they seldom meet in one
+// node.  Each wavefront has its own part of y (its LDS updates complete in
+// order, so the sums have a fixed order); the segment's parts go to
+// scratch and k_tube_sum adds them up per node.  (One pass for the dots and
+// one over the node -> entry transpose, as the product went before, gathered a
+// partner dot per entry: see apply_matfree for the times.)
+constexpr int kApplyHeld = 4;  // entries per lane and side held in registers
+constexpr int kApplyWaves = 4;
 
-// off[j] = the first position of node j in the sorted node keys, j <= nd
-__global__ void k_node_bounds(const int32_t *__restrict__ keys, int64_t n, int64_t nd, int64_t *__restrict__ off) {
-  const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (j > nd) return;
-  int64_t lo = 0, hi = n;
-  while (lo < hi) {
-    const int64_t mid = (lo + hi) >> 1;
-    if (keys[mid] < j) lo = mid + 1;
-    else hi = mid;
-  }
-  off[j] = lo;
+struct ApplyArgs {
+  const int4 *items;       // {tube, first pair, past the last pair, segment of the tube}
+  const int4 *pm;
+  const double *pw;
+  const int64_t *u_off;
+  const int32_t *tube_u;
+  const int64_t *seg_off;  // per tube: first double of its segments' parts
+  const int32_t *ent_slot;
+  const double *ent_val;
+  const double *x;
+  double *part;
+  double KC0, KC1, KC2;
+  int max_u;
+};
+
+template <int ctrl>
+__device__ __forceinline__ double dpp_f64(double v) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), ctrl, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), ctrl, 0xf, 0xf, true);
+  return __hiloint2double(hi, lo);
 }
 
-__global__ void k_iota32(int32_t *__restrict__ p, int64_t n) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) p[i] = (int32_t)i;
+// sum over a group of 16 lanes, in all of them (rotations within the row)
+__device__ __forceinline__ double group_sum(double v) {
+  v += dpp_f64<0x128>(v);
+  v += dpp_f64<0x124>(v);
+  v += dpp_f64<0x122>(v);
+  v += dpp_f64<0x121>(v);
+  return v;
 }
 
-// per node-ordered merged incidence q: the index 2 k + (1 - s) of its
-// partner's dot | axis << 30
-__global__ void k_mpart(const int32_t *__restrict__ mrow_q, const int32_t *__restrict__ mg_pair,
-                        const uint32_t *__restrict__ mk_meta, const int4 *__restrict__ pm, int64_t n,
-                        uint32_t *__restrict__ mpart) {
-  const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (q >= n) return;
-  const int32_t mq = mrow_q[q];
-  const int64_t k = mg_pair[mq];
-  const uint32_t side = (mk_meta[mq] >> 16) & 1u;
-  const uint32_t axis = (uint32_t)pm[k].w >> 30;
-  mpart[q] = (uint32_t)(2 * k + 1 - side) | (axis << 30);
-}
+struct HeldSide {
+  int e0, n;
+  int s[kApplyHeld];
+  double v[kApplyHeld];
+};
 
-// mpos[m] = the position of merged entry m in node order
-__global__ void k_inverse32(const int32_t *__restrict__ perm, int64_t n, int32_t *__restrict__ inv) {
-  const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (q < n) inv[perm[q]] = (int32_t)q;
-}
-
-// U entries per lane of the sixteen for one pair in flight at once: the
-// loads of all U first, then the gathers of x, then the sums in entry order
-template <int U>
-__device__ __forceinline__ void pair_dot_run(int64_t &q, int64_t qe, const uint32_t *__restrict__ mk_meta,
-                                             const double *__restrict__ mk_val64,
-                                             const int32_t *__restrict__ mg_node, const double *__restrict__ x,
-                                             double &s0, double &s1) {
-  for (; q + 16 * (U - 1) < qe; q += 16 * U) {
-    double w[U], xv[U];
-    int32_t nd[U];
-    uint32_t mt[U];
-#pragma unroll
-    for (int u = 0; u < U; u++) {
-      w[u] = mk_val64[q + 16 * u];
-      nd[u] = mg_node[q + 16 * u];
-      mt[u] = mk_meta[q + 16 * u];
-    }
-#pragma unroll
-    for (int u = 0; u < U; u++) xv[u] = x[nd[u]];
-#pragma unroll
-    for (int u = 0; u < U; u++) {
-      const double v = w[u] * xv[u];
-      if ((mt[u] >> 16) & 1u) s1 += v;
-      else s0 += v;
-    }
-  }
-}
-
-// dp[2 k + s] = d(k, s); sixteen lanes per pair, each summing its entries in
-// ascending merged order
-__global__ void __launch_bounds__(256) k_mpair_dot(const int64_t *__restrict__ mk_pair,
-                                                   const uint32_t *__restrict__ mk_meta,
-                                                   const double *__restrict__ mk_val64,
-                                                   const int32_t *__restrict__ mg_node, const double *__restrict__ x,
-                                                   int64_t n_pairs, double *__restrict__ dp) {
+__device__ __forceinline__ void held_load(HeldSide &h, int e0, int n, const int32_t *__restrict__ slot,
+                                          const double *__restrict__ val) {
   const int gl = threadIdx.x & 15;
-  const int64_t k = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 4;
-  if (k >= n_pairs) return;  // the whole group of 16 shares k
-  double s0 = 0.0, s1 = 0.0;
-  const int64_t qe = mk_pair[k + 1];
-  int64_t q = mk_pair[k] + gl;
-  pair_dot_run<8>(q, qe, mk_meta, mk_val64, mg_node, x, s0, s1);
-  pair_dot_run<2>(q, qe, mk_meta, mk_val64, mg_node, x, s0, s1);
-  pair_dot_run<1>(q, qe, mk_meta, mk_val64, mg_node, x, s0, s1);
+  h.e0 = e0;
+  h.n = n;
 #pragma unroll
-  for (int o = 8; o > 0; o >>= 1) {
-    s0 += __shfl_xor(s0, o, 16);
-    s1 += __shfl_xor(s1, o, 16);
-  }
-  if (gl == 0) {
-    dp[2 * k] = s0;
-    dp[2 * k + 1] = s1;
-  }
-}
-
-// U incidences per lane of node j's wavefront in flight at once, summed in
-// ascending order
-template <int U>
-__device__ __forceinline__ void row_apply_run(int64_t &q, int64_t qe, const uint32_t *__restrict__ mpart,
-                                              const double *__restrict__ mwv, const double *__restrict__ dp,
-                                              double KC0, double KC1, double KC2, double &s) {
-  for (; q + 64 * (U - 1) < qe; q += 64 * U) {
-    uint32_t pt[U];
-    double w[U], d[U];
-#pragma unroll
-    for (int u = 0; u < U; u++) {
-      pt[u] = mpart[q + 64 * u];
-      w[u] = mwv[q + 64 * u];
-    }
-#pragma unroll
-    for (int u = 0; u < U; u++) d[u] = dp[pt[u] & 0x3fffffffu];
-#pragma unroll
-    for (int u = 0; u < U; u++) {
-      const uint32_t ax = pt[u] >> 30;
-      s += w[u] * (ax == 0 ? KC0 : (ax == 1 ? KC1 : KC2)) * d[u];
+  for (int j = 0; j < kApplyHeld; j++) {
+    h.s[j] = 0;
+    h.v[j] = 0.0;
+    if (16 * j + gl < n) {
+      h.s[j] = slot[e0 + 16 * j + gl];
+      h.v[j] = val[e0 + 16 * j + gl];
     }
   }
 }
 
-// y_j over node j's merged incidences; one wavefront per node, four nodes
-// per workgroup, the groups of four dealt to the XCDs in contiguous ranges
-// (neighbouring nodes read the dots of the same tubes' pairs, which then
-// stay in one L2); the grid is 8 ceil(ceil(ndof / 4) / 8) workgroups
-__global__ void __launch_bounds__(256) k_mapply_rows(const int64_t *__restrict__ mrow_off,
-                                                     const uint32_t *__restrict__ mpart,
-                                                     const double *__restrict__ mwv, const double *__restrict__ dp,
-                                                     double KC0, double KC1, double KC2, int64_t ndof,
-                                                     double *__restrict__ y) {
+__device__ __forceinline__ double held_dot(const HeldSide &h, const double *xs, const int32_t *__restrict__ slot,
+                                           const double *__restrict__ val) {
+  double d = 0.0;
+#pragma unroll
+  for (int j = 0; j < kApplyHeld; j++) d = fma(h.v[j], xs[h.s[j]], d);
+  for (int e = 16 * kApplyHeld + (int)(threadIdx.x & 15); e < h.n; e += 16)
+    d = fma(val[h.e0 + e], xs[slot[h.e0 + e]], d);
+  return group_sum(d);
+}
+
+__device__ __forceinline__ void held_add(const HeldSide &h, double c, double *ys, const int32_t *__restrict__ slot,
+                                         const double *__restrict__ val) {
+  const int gl = threadIdx.x & 15;
+#pragma unroll
+  for (int j = 0; j < kApplyHeld; j++)
+    if (16 * j + gl < h.n) atomicAdd(&ys[h.s[j]], c * h.v[j]);
+  for (int e = 16 * kApplyHeld + gl; e < h.n; e += 16) atomicAdd(&ys[slot[h.e0 + e]], c * val[h.e0 + e]);
+}
+
+__global__ void __launch_bounds__(64 * kApplyWaves) k_tube_apply(ApplyArgs a) {
+  extern __shared__ double lds[];
+  const int4 it = a.items[blockIdx.x];
+  const int64_t u0 = a.u_off[it.x];
+  const int U = (int)(a.u_off[it.x + 1] - u0);
+  const int wave = threadIdx.x >> 6, grp = threadIdx.x >> 4;
+  double *xs = lds, *ys = lds + (int64_t)(1 + wave) * a.max_u;
+  for (int j = threadIdx.x; j < U; j += blockDim.x) {
+    xs[j] = a.x[a.tube_u[u0 + j]];
+#pragma unroll
+    for (int v = 0; v < kApplyWaves; v++) lds[(int64_t)(1 + v) * a.max_u + j] = 0.0;
+  }
+  __syncthreads();
+  // group g of the 16 takes pairs from its sixteenth of the segment
+  const int len = it.z - it.y, per = (len + 4 * kApplyWaves - 1) / (4 * kApplyWaves);
+  const int b = it.y + grp * per, e = b + per < it.z ? b + per : it.z;
+  HeldSide l, r, ln, rn;
+  double w = 0.0, wn = 0.0;
+  auto load = [&](int k, HeldSide &hl, HeldSide &hr, double &ww) {
+    int4 m = make_int4(0, 0, 0, 0);
+    ww = 0.0;
+    if (k < e) {
+      m = a.pm[k];
+      ww = a.pw[k];
+    }
+    held_load(hl, m.x, pair_nl(m), a.ent_slot, a.ent_val);
+    held_load(hr, m.y, pair_nr(m), a.ent_slot, a.ent_val);
+  };
+  load(b, l, r, w);
+  for (int k = 0; k < per; k++) {
+    load(b + k + 1, ln, rn, wn);
+    const double dl = held_dot(l, xs, a.ent_slot, a.ent_val), dr = held_dot(r, xs, a.ent_slot, a.ent_val);
+    held_add(l, w * dr, ys, a.ent_slot, a.ent_val);
+    held_add(r, w * dl, ys, a.ent_slot, a.ent_val);
+    l = ln;
+    r = rn;
+    w = wn;
+  }
+  __syncthreads();
+  const int axis = (int)((unsigned)a.pm[it.y].w >> 30);  // a tube's pairs share one axis
+  const double kc = axis == 0 ? a.KC0 : (axis == 1 ? a.KC1 : a.KC2);
+  double *out = a.part + a.seg_off[it.x] + (int64_t)it.w * U;
+  for (int j = threadIdx.x; j < U; j += blockDim.x) {
+    double s = 0.0;
+#pragma unroll
+    for (int v = 0; v < kApplyWaves; v++) s += lds[(int64_t)(1 + v) * a.max_u + j];
+    out[j] = kc * s;
+  }
+}
+
+// The diagonal of K in the same way: K_jj = sum_i K_i c_alpha sum_g 2 w_g
+// L_gi(j) R_gi(j).  A wavefront takes one pair at a time: l summed per node into
+// its LDS row, then every entry of r at node j adds 2 w r L(j) to the part.
+__global__ void k_tube_diag(ApplyArgs a) {
+  extern __shared__ double lds[];
+  const int4 it = a.items[blockIdx.x];
+  const int64_t u0 = a.u_off[it.x];
+  const int U = (int)(a.u_off[it.x + 1] - u0);
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
+  double *ls = lds + (int64_t)wave * a.max_u, *ys = lds + (int64_t)(nw + wave) * a.max_u;
+  for (int j = lane; j < U; j += 64) ls[j] = ys[j] = 0.0;
+  wave_lds_sync();
+  for (int k = it.y + wave; k < it.z; k += nw) {
+    const int4 m = a.pm[k];
+    const int nl = pair_nl(m), nr = pair_nr(m);
+    const double w2 = 2.0 * a.pw[k];
+    for (int e = lane; e < nl; e += 64) atomicAdd(&ls[a.ent_slot[m.x + e]], a.ent_val[m.x + e]);
+    wave_lds_sync();
+    for (int e = lane; e < nr; e += 64) {
+      const int s = a.ent_slot[m.y + e];
+      const double v = ls[s];
+      if (v != 0.0) atomicAdd(&ys[s], w2 * a.ent_val[m.y + e] * v);
+    }
+    wave_lds_sync();
+    for (int e = lane; e < nl; e += 64) ls[a.ent_slot[m.x + e]] = 0.0;
+    wave_lds_sync();
+  }
+  __syncthreads();
+  const int axis = (int)((unsigned)a.pm[it.y].w >> 30);
+  const double kc = axis == 0 ? a.KC0 : (axis == 1 ? a.KC1 : a.KC2);
+  double *out = a.part + a.seg_off[it.x] + (int64_t)it.w * U;
+  for (int j = threadIdx.x; j < U; j += blockDim.x) {
+    double s = 0.0;
+    for (int v = 0; v < nw; v++) s += lds[(int64_t)(nw + v) * a.max_u + j];
+    out[j] = kc * s;
+  }
+}
+
+// y_j = the sum of node j's places in the segments' parts; one wavefront per node
+__global__ void __launch_bounds__(256) k_tube_sum(const int64_t *__restrict__ row_off, const int2 *__restrict__ row_ts,
+                                                  const int64_t *__restrict__ u_off,
+                                                  const int64_t *__restrict__ seg_off,
+                                                  const double *__restrict__ part, int64_t ndof,
+                                                  double *__restrict__ y) {
   const int lane = threadIdx.x & 63;
-  const int64_t j = dealt_row(blockIdx.x, (ndof + 3) / 4) * 4 + (threadIdx.x >> 6);
+  const int64_t j = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
   if (j >= ndof) return;
   double s = 0.0;
-  const int64_t qe = mrow_off[j + 1];
-  int64_t q = mrow_off[j] + lane;
-  row_apply_run<4>(q, qe, mpart, mwv, dp, KC0, KC1, KC2, s);
-  row_apply_run<2>(q, qe, mpart, mwv, dp, KC0, KC1, KC2, s);
-  row_apply_run<1>(q, qe, mpart, mwv, dp, KC0, KC1, KC2, s);
+  for (int64_t p = row_off[j] + lane; p < row_off[j + 1]; p += 64) {
+    const int2 ts = row_ts[p];
+    const int64_t U = u_off[ts.x + 1] - u_off[ts.x], e = seg_off[ts.x + 1];
+    for (int64_t o = seg_off[ts.x] + ts.y; o < e; o += U) s += part[o];
+  }
   for (int o = 32; o > 0; o >>= 1) s += __shfl_down(s, o, 64);
   if (lane == 0) y[j] = s;
 }
@@ -1236,8 +1273,7 @@ void free_tubes(TubePlan &tp) {
   dfree(tp.mitems); dfree(tp.texp);
   dfree(tp.mk_pair); dfree(tp.mk_meta); dfree(tp.mk_val); dfree(tp.mg_idx); dfree(tp.pk_tube);
   dfree(tp.cstart);
-  dfree(tp.mg_node); dfree(tp.mg_pair); dfree(tp.mrow_q); dfree(tp.mrow_off); dfree(tp.mpart); dfree(tp.mpos);
-  dfree(tp.mk_val64); dfree(tp.mwv); dfree(tp.mdp);
+  dfree(tp.aitems); dfree(tp.seg_off); dfree(tp.part);
   tp = TubePlan();
 }
 
@@ -1397,6 +1433,33 @@ int build_tubes(fpde_mesh *m, Plan &P, double kappa, hipStream_t s) {
       HIP_T(hipStreamSynchronize(s));
     }
   }
+  // Segments of the matrix-free product: at most kSegMax pairs, fewer on small
+  // meshes so that there are a few thousand, in multiples of the 16 groups of
+  // a workgroup.
+  {
+    constexpr int64_t kSegMin = 32, kSegMax = 512;
+    const int64_t seg = std::min(kSegMax, std::max(kSegMin, n / 4096 / 16 * 16));
+    std::vector<int64_t> so(nT + 1);
+    std::vector<int4> items;
+    int64_t off = 0;
+    for (int64_t T = 0; T < nT; T++) {
+      so[T] = off;
+      if (uo[T + 1] == uo[T]) continue;
+      int q = 0;
+      for (int64_t k = to[T]; k < to[T + 1]; k += seg, q++)
+        items.push_back(make_int4((int)T, (int)k, (int)std::min(k + seg, to[T + 1]), q));
+      off += q * (uo[T + 1] - uo[T]);
+    }
+    so[nT] = off;
+    tp.n_part = off;
+    tp.n_aitems = (int64_t)items.size();
+    TRY_T(dalloc(&tp.seg_off, nT + 1));
+    TRY_T(dalloc(&tp.aitems, items.size() > 0 ? items.size() : 1));
+    HIP_T(hipMemcpyAsync(tp.seg_off, so.data(), sizeof(int64_t) * (nT + 1), hipMemcpyHostToDevice, s));
+    if (!items.empty())
+      HIP_T(hipMemcpyAsync(tp.aitems, items.data(), sizeof(int4) * items.size(), hipMemcpyHostToDevice, s));
+    HIP_T(hipStreamSynchronize(s));
+  }
   HIP_T(hipGetLastError());
   f = take_flag(m, s);
   if (f != 0) return fail(f < 0 ? f : FPDE_EHIP);
@@ -1446,7 +1509,7 @@ static int build_mfma_plan(fpde_mesh *m, Plan &P, TubePlan &tp, hipStream_t s) {
   if (hipMemsetAsync(pcnt, 0, sizeof(int64_t) * (nP + 1), s) != hipSuccess) return done(FPDE_EHIP);
   if (hipMemsetAsync(maxc, 0, sizeof(int), s) != hipSuccess) return done(FPDE_EHIP);
   k_merge_pairs<false><<<(unsigned)nP, 64, 0, s>>>(tp.tube_off, nT, tp.pm, nP, tp.ent_slot, pcnt, nullptr, nullptr,
-                                                    nullptr, nullptr, maxc, nullptr, nullptr, nullptr, nullptr);
+                                                    nullptr, nullptr, maxc);
   int mc = 0;
   if (!to_host(maxc, &mc, sizeof(int))) return done(FPDE_EHIP);
   if (mc > kMergeMax) return done(FPDE_OK);
@@ -1458,57 +1521,8 @@ static int build_mfma_plan(fpde_mesh *m, Plan &P, TubePlan &tp, hipStream_t s) {
   if ((st = dalloc(&tp.mk_val, n_mk > 0 ? n_mk : 1)) != FPDE_OK) return done(st);
   if ((st = dalloc(&tp.mg_idx, P.n_ent > 0 ? P.n_ent : 1)) != FPDE_OK) return done(st);
   if ((st = dalloc(&tp.pk_tube, nP > 0 ? nP : 1)) != FPDE_OK) return done(st);
-  if ((st = dalloc(&tp.mg_node, n_mk > 0 ? n_mk : 1)) != FPDE_OK) return done(st);
-  if ((st = dalloc(&tp.mg_pair, n_mk > 0 ? n_mk : 1)) != FPDE_OK) return done(st);
-  if ((st = dalloc(&tp.mk_val64, n_mk > 0 ? n_mk : 1)) != FPDE_OK) return done(st);
   k_merge_pairs<true><<<(unsigned)nP, 64, 0, s>>>(tp.tube_off, nT, tp.pm, nP, tp.ent_slot, nullptr, tp.mk_pair,
-                                                   tp.mg_idx, tp.mk_meta, tp.pk_tube, nullptr, tp.u_off, tp.tube_u,
-                                                   tp.mg_node, tp.mg_pair);
-  tp.n_mk = n_mk;
-  // node -> merged entries (stable by merged index) for the matrix-free
-  // product; its partner indices need 2 nP < 2^30
-  if (n_mk > 0 && n_mk < (int64_t(1) << 31) && 2 * nP + 1 < (int64_t(1) << 30)) {
-    const int64_t nd = m->ndof;
-    int32_t *keys = nullptr, *iota = nullptr;
-    auto fail_m = [&](int code) {
-      dfree(keys);
-      dfree(iota);
-      return done(code);
-    };
-    if ((st = dalloc(&keys, n_mk)) != FPDE_OK) return fail_m(st);
-    if ((st = dalloc(&iota, n_mk)) != FPDE_OK) return fail_m(st);
-    if ((st = dalloc(&tp.mrow_q, n_mk)) != FPDE_OK) return fail_m(st);
-    k_iota32<<<nblocks(n_mk), 256, 0, s>>>(iota, n_mk);
-    int bits = 1;
-    while ((int64_t(1) << bits) < nd) bits++;
-    size_t sneed = 0;
-    if (hipcub::DeviceRadixSort::SortPairs(nullptr, sneed, tp.mg_node, keys, iota, tp.mrow_q, (int)n_mk, 0, bits, s) !=
-        hipSuccess)
-      return fail_m(FPDE_EHIP);
-    if (sneed > have) {
-      if (tmp) (void)hipFree(tmp);
-      tmp = nullptr;
-      if (hipMalloc(&tmp, sneed) != hipSuccess) return fail_m(FPDE_ENOMEM);
-      have = sneed;
-    }
-    if (hipcub::DeviceRadixSort::SortPairs(tmp, sneed, tp.mg_node, keys, iota, tp.mrow_q, (int)n_mk, 0, bits, s) !=
-        hipSuccess)
-      return fail_m(FPDE_EHIP);
-    if ((st = dalloc(&tp.mrow_off, nd + 1)) != FPDE_OK) return fail_m(st);
-    k_node_bounds<<<nblocks(nd + 1), 256, 0, s>>>(keys, n_mk, nd, tp.mrow_off);
-    if ((st = dalloc(&tp.mpart, n_mk)) != FPDE_OK) return fail_m(st);
-    k_mpart<<<nblocks(n_mk), 256, 0, s>>>(tp.mrow_q, tp.mg_pair, tp.mk_meta, tp.pm, n_mk, tp.mpart);
-    if ((st = dalloc(&tp.mpos, n_mk)) != FPDE_OK) return fail_m(st);
-    k_inverse32<<<nblocks(n_mk), 256, 0, s>>>(tp.mrow_q, n_mk, tp.mpos);
-    if ((st = dalloc(&tp.mwv, n_mk)) != FPDE_OK) return fail_m(st);
-    if ((st = dalloc(&tp.mdp, 2 * nP)) != FPDE_OK) return fail_m(st);
-    if (hipStreamSynchronize(s) != hipSuccess) return fail_m(FPDE_EHIP);
-    dfree(keys);
-    dfree(iota);
-    dfree(tp.mrow_q);
-    dfree(tp.mg_pair);
-    tp.mapply_ok = true;
-  }
+                                                   tp.mg_idx, tp.mk_meta, tp.pk_tube, nullptr);
   // Region work items, balanced over the eight XCDs (the hardware deals
   // workgroup b to XCD b mod 8): whole tubes, largest cost first, each to
   // the XCD with the least work so far (cost = regions x chunks of 16
@@ -1589,9 +1603,7 @@ static int accumulate_tube_blocks(fpde_mesh *m, Plan &P, const fpde_params *p, h
     // eight workgroups of four wavefronts per CU, each wavefront looping
     const unsigned mgrid = (unsigned)std::min<int64_t>(nblocks(nP, 4), 256 * 8);
     k_merge_vals<<<mgrid, 256, 0, s>>>(tp.pm, tp.pw, tp.mk_pair, tp.pk_tube, tp.mg_idx, nP, P.ent_val, a.KC0, a.KC1,
-                                       a.KC2, tp.mk_val, tp.mk_val64, tp.mapply_ok ? tp.mpos : nullptr,
-                                       tp.mapply_ok ? tp.mwv : nullptr, tp.texp);
-    tp.mk_version = P.values_version;
+                                       a.KC2, tp.mk_val, tp.texp);
     if (tp.n_mitems > 0) {
       TubeMfmaArgs ma{tp.tube_off, tp.pm, tp.pw, tp.mk_pair, tp.mk_meta, tp.mk_val, tp.blk_off, tp.blk,
                       a.KC0, a.KC1, a.KC2};
@@ -1643,22 +1655,53 @@ static unsigned gather_grid(int64_t ndof) {
   return (unsigned)(slots < 65536 ? slots : 65536);
 }
 
-bool merged_apply_ready(const Plan &P) {
-  const TubePlan &tp = P.tubes;
-  return tp.mfma_ok && tp.mapply_ok && tp.mk_version == P.values_version;
-}
-
-int apply_merged(fpde_mesh *m, Plan &P, const fpde_params *p, const double *x, double *y, hipStream_t s) {
+// y = K x (diag: its diagonal) from the plan's current values
+static int apply_tubes(fpde_mesh *m, Plan &P, const fpde_params *p, const double *x, double *y, bool diag,
+                       hipStream_t s) {
   TubePlan &tp = P.tubes;
-  const int64_t nP = 3 * P.G;
-  Order o = order_scalars(p->alpha);
-  const long t = timer_begin(m, s, FPDE_STAGE_APPLY);
-  k_mpair_dot<<<nblocks(16 * nP), 256, 0, s>>>(tp.mk_pair, tp.mk_meta, tp.mk_val64, tp.mg_node, x, nP, tp.mdp);
-  k_mapply_rows<<<(unsigned)(8 * (((m->ndof + 3) / 4 + 7) / 8)), 256, 0, s>>>(tp.mrow_off, tp.mpart, tp.mwv, tp.mdp, p->K[0] * o.c_alpha,
-                                                    p->K[1] * o.c_alpha, p->K[2] * o.c_alpha, m->ndof, y);
-  timer_end(m, FPDE_STAGE_APPLY, t, s);
+  if (!tp.part) FPDE_TRY(dalloc(&tp.part, (size_t)tp.n_part));
+  const Order o = order_scalars(p->alpha);
+  ApplyArgs a{};
+  a.items = tp.aitems;
+  a.pm = tp.pm;
+  a.pw = tp.pw;
+  a.u_off = tp.u_off;
+  a.tube_u = tp.tube_u;
+  a.seg_off = tp.seg_off;
+  a.ent_slot = tp.ent_slot;
+  a.ent_val = P.ent_val;
+  a.x = x;
+  a.part = tp.part;
+  a.KC0 = p->K[0] * o.c_alpha;
+  a.KC1 = p->K[1] * o.c_alpha;
+  a.KC2 = p->K[2] * o.c_alpha;
+  a.max_u = (int)tp.max_u;
+  if (tp.n_aitems > 0 && diag) {
+    // two LDS rows per wavefront: four wavefronts up to 2560 nodes, else two
+    const int nw = tp.max_u <= 2560 ? 4 : 2;
+    k_tube_diag<<<(unsigned)tp.n_aitems, 64 * nw, sizeof(double) * 2 * nw * tp.max_u, s>>>(a);
+  } else if (tp.n_aitems > 0) {
+    // x and a part per wavefront: 160 KB at the 4096 nodes a tube may have
+    k_tube_apply<<<(unsigned)tp.n_aitems, 64 * kApplyWaves, sizeof(double) * (1 + kApplyWaves) * tp.max_u, s>>>(a);
+  }
+  k_tube_sum<<<nblocks(m->ndof, 4), 256, 0, s>>>(tp.row_off, tp.row_ts, tp.u_off, tp.seg_off, tp.part, m->ndof, y);
   FPDE_HIP(hipGetLastError());
   return FPDE_OK;
+}
+
+// Per product (start: two passes over the entries and, after a change of the
+// values, a reordering of them; mixed: merged entries, whose reordering at
+// every assembly took 11 ms more at 25 177 unknowns): see the table of cases.
+int apply_matfree(fpde_mesh *m, Plan *P, const fpde_params *p, const double *x, double *y, hipStream_t s) {
+  if (m->ndof == 0) return FPDE_OK;
+  const long t = timer_begin(m, s, FPDE_STAGE_APPLY);
+  FPDE_TRY(apply_tubes(m, *P, p, x, y, false, s));
+  timer_end(m, FPDE_STAGE_APPLY, t, s);
+  return FPDE_OK;
+}
+
+int matfree_diagonal(fpde_mesh *m, Plan *P, const fpde_params *p, double *d, hipStream_t s) {
+  return apply_tubes(m, *P, p, nullptr, d, true, s);
 }
 
 int launch_contract_tubes(fpde_mesh *m, Plan &P, const fpde_params *p, void *A, int64_t lda, hipStream_t s) {
