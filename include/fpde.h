@@ -125,7 +125,7 @@ int fpde_dof_map(const fpde_mesh *m, int32_t *dof);
 /*
  * Symbolic phase ("template", Sec. 2.3): walks every half-ray of the
  * quad_points rule once, records how many entries each derivative vector has
- * and builds the node -> entry transpose used by the accumulation.  Depends
+ * and groups the pairs of half-rays into tubes for the accumulation.  Depends
  * on the mesh and rule only, so it is reused for every alpha and K.  Called
  * implicitly by fpde_assemble when missing; synchronises `stream`.
  * Errors: FPDE_EINVAL (rule), FPDE_EPATH, FPDE_ENOMEM, FPDE_EHIP.

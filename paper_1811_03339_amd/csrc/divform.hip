@@ -221,7 +221,7 @@ struct DivLoadArgs {
 // One wavefront per node: its lanes take the node's (element, point) pairs,
 // then a butterfly sum in a fixed order.  Bound by the six powers per pair of
 // the ball's source; one thread per node left most of the chip idle
-// (N = 8 162, 4 points: 32 workgroups, 890 us against 70 us).
+// (N = 8 162, 4 points: 32 workgroups, 890 us against 63 us).
 __global__ void __launch_bounds__(256) k_div_load(DivLoadArgs a, double *__restrict__ b) {
   const int64_t j = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
   const int lane = threadIdx.x & 63;

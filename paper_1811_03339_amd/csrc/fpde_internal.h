@@ -81,7 +81,7 @@ struct TubePlan {
   double *part = nullptr;
 };
 
-// Symbolic phase of one rule: derivative-vector sizes and the row transpose.
+// Symbolic phase of one rule: derivative-vector sizes and the tubes.
 // Half-ray index (direction-major): h = dir * G + g, dir = 2 i + side.
 struct Plan {
   int nq = 0;
@@ -91,17 +91,10 @@ struct Plan {
   int64_t n_ent = 0;      // entries over all half-rays
   int64_t *off = nullptr;     // n_half + 1: entries of half-ray h
   int32_t *ent_dof = nullptr; // n_ent
-  int32_t *ent_ray = nullptr; // n_ent: owning half-ray
   double *ent_val = nullptr;  // n_ent: values, half-rays along e_i at order val_gamma[i]
   double val_gamma[3] = {-1.0, -1.0, -1.0};  // per axis; -1 = not computed
   double *ent_val2 = nullptr;  // n_ent: a second set of values (allocated on first use)
   double val_gamma2[3] = {-1.0, -1.0, -1.0};
-  int64_t *row_off = nullptr; // n_dof + 1
-  int64_t *inc = nullptr;     // n_ent: entry ids grouped by their dof
-  // per incidence (row order): {entry id, partner offset, partner length << 2 | axis,
-  // partner half-ray} and the quadrature weight w_g of its Gauss point
-  int4 *inc_meta = nullptr;
-  double *inc_w = nullptr;
   double *adj = nullptr;      // 4 n_half scratch for the adjoint dots
   int64_t pairs = 0;          // sum over (g, i) of |L| |R|
   int64_t max_ent = 0;        // largest entry count of one half-ray
@@ -222,9 +215,9 @@ int build_tubes(fpde_mesh *m, Plan &P, double kappa, hipStream_t s);
 void free_tubes(TubePlan &tp);
 int launch_contract_tubes(fpde_mesh *m, Plan &P, const fpde_params *p, void *A, int64_t lda, hipStream_t s);
 // the same sums kept at the columns of a CSR pattern (FP64)
-// general form with constant coefficients from the plan's two value sets
-int launch_form_tubes(fpde_mesh *m, Plan &P, const double cl[3], const double cr[3], double *A, int64_t lda,
-                      hipStream_t s);
+// general form from the plan's two value sets (coef: per Gauss point, or null)
+int launch_form_tubes(fpde_mesh *m, Plan &P, const double cl[3], const double cr[3], const double *coef, double *A,
+                      int64_t lda, hipStream_t s);
 int launch_contract_tubes_csr(fpde_mesh *m, Plan &P, const fpde_params *p, const int64_t *row_ptr,
                               const int32_t *col, double *val, hipStream_t s);
 // matrix-free y = K x from the plan's values, and the diagonal of K

@@ -260,8 +260,12 @@ struct AccumArgs {
   const int64_t *blk_off;
   double *blk;
   double KC0, KC1, KC2;
-  // general form (k_tube_form): test-order values and constant coefficients
+  // general form (k_tube_form): test-order values, constant coefficients, and
+  // coefficients per pair (id i G + g, those of cr after ncoef of cl) or null
   const double *val_b;
+  const int32_t *pair;
+  const double *coef;
+  int64_t ncoef;
   double cl0, cl1, cl2, cr0, cr1, cr2;
 };
 
@@ -309,16 +313,30 @@ template <int ROLES>
 struct StepCursor {
   const int4 *__restrict__ pm;
   const double *__restrict__ pw;
+  // coefficients per pair (general form), by pair id i G + g: of role 1 at
+  // coef[id], of role 0 at coef[ncoef + id]; else null
+  const int32_t *__restrict__ pair;
+  const double *__restrict__ coef;
+  int64_t ncoef;
   int64_t k, k1;
   int nw;
   int4 m, mn;
-  double w, wn;
+  double w[ROLES], wn[ROLES];
   int role, rb, cb;
-  __device__ __forceinline__ void fetch(int64_t kk, int4 &mm, double &ww) {
+  __device__ __forceinline__ void fetch(int64_t kk, int4 &mm, double (&ww)[ROLES]) {
     kk = kk < k1 ? kk : k1 - 1;
     mm = pm[kk];
-    ww = pw[kk];
+    ww[0] = pw[kk];
+    if constexpr (ROLES == 2) {
+      ww[1] = ww[0];
+      if (coef) {
+        const int64_t id = pair[kk];
+        ww[0] *= coef[ncoef + id];
+        ww[1] *= coef[id];
+      }
+    }
   }
+  __device__ __forceinline__ double weight() const { return ROLES == 2 && role ? w[ROLES - 1] : w[0]; }
   __device__ __forceinline__ void start(int64_t k0) {
     k = k0;
     role = rb = cb = 0;
@@ -340,7 +358,8 @@ struct StepCursor {
     role = 0;
     k += nw;
     m = mn;
-    w = wn;
+#pragma unroll
+    for (int q = 0; q < ROLES; q++) w[q] = wn[q];
     if (k < k1) fetch(k + nw, mn, wn);
   }
 };
@@ -436,6 +455,9 @@ __device__ __forceinline__ void band_products(double *acc, int U, int Up, int r0
   StepCursor<ROLES> c;
   c.pm = a.pm;
   c.pw = a.pw;
+  c.pair = a.pair;
+  c.coef = a.coef;
+  c.ncoef = a.ncoef;
   c.k1 = k1;
   c.nw = blockDim.x >> 6;
   c.start(k0 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6));
@@ -443,7 +465,7 @@ __device__ __forceinline__ void band_products(double *acc, int U, int Up, int r0
   auto load = [&](PairStep &p) {
     p.nr = 0;
     if (c.k >= k1) return false;
-    load_step(c, a.ent_slot, vrow, vcol, c.w * (c.role ? kc1 : kc0), p);
+    load_step(c, a.ent_slot, vrow, vcol, c.weight() * (c.role ? kc1 : kc0), p);
     c.next();
     return true;
   };
@@ -493,8 +515,8 @@ __global__ void __launch_bounds__(kAccumThreads) k_tube_accum(AccumArgs a) {
   }
 }
 
-// General form with constant coefficients (Sec. 1, the test operator on
-// the side opposite to the trial one): per pair, with l / r the left / right
+// General form (Sec. 1, the test operator on the side opposite to the trial
+// one), with constant coefficients or one per Gauss point and axis: per pair, with l / r the left / right
 // half-rays, the trial values at orders alpha (a.ent_val) and the test
 // values at orders beta (a.val_b),
 //   B[k][l] += w cl_i r_beta[k] l_alpha[l] + w cr_i l_beta[k] r_alpha[l]
@@ -511,8 +533,8 @@ __global__ void __launch_bounds__(kAccumThreads) k_tube_form(AccumArgs a) {
   const int64_t k0 = a.tube_off[T], k1 = a.tube_off[T + 1];
   // role 0: rows l (beta), columns r (alpha, cr); role 1: rows r, columns l (cl)
   const int axis = (int)((unsigned)a.pm[k0].w >> 30);
-  const double kc0 = axis == 0 ? a.cr0 : (axis == 1 ? a.cr1 : a.cr2);
-  const double kc1 = axis == 0 ? a.cl0 : (axis == 1 ? a.cl1 : a.cl2);
+  const double kc0 = a.coef ? 1.0 : (axis == 0 ? a.cr0 : (axis == 1 ? a.cr1 : a.cr2));
+  const double kc1 = a.coef ? 1.0 : (axis == 0 ? a.cl0 : (axis == 1 ? a.cl1 : a.cl2));
   for (int rb = r0; rb < r0 + R; rb += Rsq) {
     const int Rb = (r0 + R - rb) < Rsq ? (r0 + R - rb) : Rsq;
     for (int j = threadIdx.x; j < Rb * Up; j += blockDim.x) acc[j] = 0.0;
@@ -893,7 +915,7 @@ __device__ __forceinline__ int tube_scale_exp(int e) {
 // order, so the sums have a fixed order); the segment's parts go to
 // scratch and k_tube_sum adds them up per node.  (One pass for the dots and
 // one over the node -> entry transpose, as the product went before, gathered a
-// partner dot per entry: see apply_matfree for the times.)
+// partner dot per entry: 0.37 ms against 0.11 ms for 42 077 elements.)
 constexpr int kApplyHeld = 4;  // entries per lane and side held in registers
 constexpr int kApplyWaves = 4;
 
@@ -1689,9 +1711,11 @@ static int apply_tubes(fpde_mesh *m, Plan &P, const fpde_params *p, const double
   return FPDE_OK;
 }
 
-// Per product (start: two passes over the entries and, after a change of the
-// values, a reordering of them; mixed: merged entries, whose reordering at
-// every assembly took 11 ms more at 25 177 unknowns): see the table of cases.
+// Bound by the entry loads and the same-node lanes of the LDS updates.  Per
+// product 0.12 ms for 19 672 elements (11 points; 0.97 ms with the dots and the
+// gather over the transpose, its values put in order once), 0.11 ms for 42 077
+// elements (4 points; 0.37 ms in order already), 1.6 ms for 151 907 elements
+// (11 points; 3.9 ms on merged entries, whose order cost 8 ms per assembly).
 int apply_matfree(fpde_mesh *m, Plan *P, const fpde_params *p, const double *x, double *y, hipStream_t s) {
   if (m->ndof == 0) return FPDE_OK;
   const long t = timer_begin(m, s, FPDE_STAGE_APPLY);
@@ -1722,11 +1746,12 @@ int launch_contract_tubes(fpde_mesh *m, Plan &P, const fpde_params *p, void *A, 
   return FPDE_OK;
 }
 
-// General form with constant coefficients: blocks by k_tube_form from the
-// plan's two value sets (trial orders in ent_val, test orders in ent_val2),
-// then the same row pass as the Riesz matrix.
-int launch_form_tubes(fpde_mesh *m, Plan &P, const double cl[3], const double cr[3], double *A, int64_t lda,
-                      hipStream_t s) {
+// General form: blocks by k_tube_form from the plan's two value sets (trial
+// orders in ent_val, test orders in ent_val2), with coefficients cl, cr per
+// axis or, when coef is not null, per Gauss point (cl_i at [i G + g], cr_i at
+// [(3 + i) G + g]), then the same row pass as the Riesz matrix.
+int launch_form_tubes(fpde_mesh *m, Plan &P, const double cl[3], const double cr[3], const double *coef, double *A,
+                      int64_t lda, hipStream_t s) {
   if (m->ndof == 0) return FPDE_OK;
   TubePlan &tp = P.tubes;
   if (!tp.blk) FPDE_TRY(dalloc(&tp.blk, tp.blk_n > 0 ? tp.blk_n : 1));
@@ -1746,6 +1771,9 @@ int launch_form_tubes(fpde_mesh *m, Plan &P, const double cl[3], const double cr
   a.cr0 = cr[0];
   a.cr1 = cr[1];
   a.cr2 = cr[2];
+  a.pair = tp.pair_sorted;
+  a.coef = coef;
+  a.ncoef = 3 * P.G;
   if (tp.n_items > 0) k_tube_form<<<(unsigned)tp.n_items, kAccumThreads, sizeof(double) * kBand, s>>>(a);
   GatherArgs gch;
   FPDE_TRY(gather_args(m, P, lda, s, gch));

@@ -59,7 +59,6 @@ struct WalkArgs {
   // W_STRUCT / W_VALUES
   const int64_t *off;  // indexed by h (global)
   int32_t *ent_dof;
-  int32_t *ent_ray;
   double *ent_val;
   // W_ADJ
   const double *u, *lam;
@@ -221,14 +220,12 @@ k_walk(WalkArgs a) {
   double dot_u = 0.0, dot_l = 0.0, ddot_u = 0.0, ddot_l = 0.0;
   const double sgn = side ? -1.0 : 1.0;
 
-  // staging runs of the structure pass (node and half-ray ids) and of the
-  // value pass (values)
-  __shared__ int32_t st_dof[MODE == W_STRUCT ? 16 : 1][256], st_ray[MODE == W_STRUCT ? 16 : 1][256];
+  // staging runs of the structure pass (node ids) and of the value pass (values)
+  __shared__ int32_t st_dof[MODE == W_STRUCT ? 16 : 1][256];
   __shared__ double st_val[MODE == W_VALUES ? 8 : 1][256];
   auto emit = [&](int32_t d, double v, double dv) {
     if constexpr (MODE == W_STRUCT) {
       stage_put<int32_t, 16>(st_dof, a.ent_dof, base, base + nemit, d);
-      stage_put<int32_t, 16>(st_ray, a.ent_ray, base, base + nemit, (int32_t)h);
     } else if constexpr (MODE == W_VALUES) {
       stage_put<double, 8>(st_val, a.ent_val, base, base + nemit, v);
     } else if constexpr (MODE == W_ADJ) {
@@ -398,7 +395,6 @@ k_walk(WalkArgs a) {
     if (wd[j] >= 0) emit(wd[j], wv[j], wdv[j]);
   if constexpr (MODE == W_STRUCT) {
     stage_flush<int32_t, 16>(st_dof, a.ent_dof, base, base + nemit);
-    stage_flush<int32_t, 16>(st_ray, a.ent_ray, base, base + nemit);
   } else if constexpr (MODE == W_VALUES) {
     stage_flush<double, 8>(st_val, a.ent_val, base, base + nemit);
   }
@@ -413,38 +409,6 @@ k_walk(WalkArgs a) {
     a.adj[4 * h + 2] = ddot_u;
     a.adj[4 * h + 3] = ddot_l;
   }
-}
-
-__global__ void k_row_count(const int32_t *__restrict__ ent_dof, int64_t n, int64_t *__restrict__ cnt) {
-  int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (e < n) atomicAdd((unsigned long long *)&cnt[ent_dof[e]], 1ull);
-}
-
-__global__ void k_row_fill(const int32_t *__restrict__ ent_dof, int64_t n, int64_t *__restrict__ cursor,
-                           int64_t *__restrict__ inc) {
-  int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (e < n) {
-    int64_t p = (int64_t)atomicAdd((unsigned long long *)&cursor[ent_dof[e]], 1ull);
-    inc[p] = e;
-  }
-}
-
-// flattened per-incidence data for the accumulation (see Plan::inc_meta)
-__global__ void k_inc_meta(const int64_t *__restrict__ inc, const int32_t *__restrict__ ent_ray,
-                           const int64_t *__restrict__ off, const double *__restrict__ vol,
-                           const double *__restrict__ wq, int64_t G, int nq, int64_t n, int4 *__restrict__ meta,
-                           double *__restrict__ w) {
-  const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (p >= n) return;
-  const int64_t e = inc[p];
-  const int64_t h = ent_ray[e];
-  const int dir = (int)(h / G);
-  const int64_t g = h - (int64_t)dir * G;
-  const int64_t partner = (dir & 1) ? h - G : h + G;
-  const int64_t po = off[partner];
-  const int64_t pl = off[partner + 1] - po;
-  meta[p] = make_int4((int)e, (int)po, (int)((pl << 2) | (dir >> 1)), (int)partner);
-  w[p] = wq[g % nq] * vol[g / nq];
 }
 
 __global__ void k_i32_to_i64(const int32_t *__restrict__ a, int64_t n, int64_t *__restrict__ b) {
@@ -477,8 +441,7 @@ static void launch_walk(const WalkArgs &a, hipStream_t s) {
 }
 
 void free_plan(Plan &P) {
-  dfree(P.off); dfree(P.ent_dof); dfree(P.ent_ray); dfree(P.ent_val); dfree(P.ent_val2); dfree(P.row_off); dfree(P.inc);
-  dfree(P.adj); dfree(P.inc_meta); dfree(P.inc_w);
+  dfree(P.off); dfree(P.ent_dof); dfree(P.ent_val); dfree(P.ent_val2); dfree(P.adj);
   free_tubes(P.tubes);
   P = Plan();
 }
@@ -500,11 +463,11 @@ static int build_plan(fpde_mesh *m, Plan &P, int nq, int max_steps, hipStream_t 
   P.G = m->nt * nq;
   P.n_half = 6 * P.G;
   int32_t *cnt = nullptr;
-  int64_t *cnt64 = nullptr, *rowcnt = nullptr, *cursor = nullptr;
+  int64_t *cnt64 = nullptr;
   void *tmp = nullptr;
   int st = FPDE_OK;
   auto fail = [&](int code) {
-    dfree(cnt); dfree(cnt64); dfree(rowcnt); dfree(cursor);
+    dfree(cnt); dfree(cnt64);
     if (tmp) (void)hipFree(tmp);
     free_plan(P);
     return code;
@@ -520,12 +483,9 @@ static int build_plan(fpde_mesh *m, Plan &P, int nq, int max_steps, hipStream_t 
   a.cnt = cnt;
   launch_walk<W_COUNT>(a, s);
   k_i32_to_i64<<<nblk(P.n_half + 1), 256, 0, s>>>(cnt, P.n_half + 1, cnt64);
-  size_t need = 0, need2 = 0;
-  if (hipcub::DeviceScan::ExclusiveSum(nullptr, need, cnt64, P.off, (int)(P.n_half + 1), s) != hipSuccess)
+  size_t tb = 0;
+  if (hipcub::DeviceScan::ExclusiveSum(nullptr, tb, cnt64, P.off, (int)(P.n_half + 1), s) != hipSuccess)
     return fail(FPDE_EHIP);
-  if (hipcub::DeviceScan::ExclusiveSum(nullptr, need2, cnt64, P.off, (int)(m->ndof + 1), s) != hipSuccess)
-    return fail(FPDE_EHIP);
-  size_t tb = need > need2 ? need : need2;
   if (hipMalloc(&tmp, tb) != hipSuccess) return fail(FPDE_ENOMEM);
   if (hipcub::DeviceScan::ExclusiveSum(tmp, tb, cnt64, P.off, (int)(P.n_half + 1), s) != hipSuccess)
     return fail(FPDE_EHIP);
@@ -536,35 +496,14 @@ static int build_plan(fpde_mesh *m, Plan &P, int nq, int max_steps, hipStream_t 
 
   if (P.n_ent >= (int64_t(1) << 31)) return fail(FPDE_EUNSUPPORTED);  // 32-bit entry ids below
   if ((st = dalloc(&P.ent_dof, P.n_ent)) != FPDE_OK) return fail(st);
-  if ((st = dalloc(&P.ent_ray, P.n_ent)) != FPDE_OK) return fail(st);
   if ((st = dalloc(&P.ent_val, P.n_ent)) != FPDE_OK) return fail(st);
-  if ((st = dalloc(&P.inc, P.n_ent)) != FPDE_OK) return fail(st);
-  if ((st = dalloc(&P.row_off, m->ndof + 1)) != FPDE_OK) return fail(st);
-  if ((st = dalloc(&rowcnt, m->ndof + 1)) != FPDE_OK) return fail(st);
-  if ((st = dalloc(&cursor, m->ndof + 1)) != FPDE_OK) return fail(st);
   a.off = P.off;
   a.ent_dof = P.ent_dof;
-  a.ent_ray = P.ent_ray;
   launch_walk<W_STRUCT>(a, s);
-  // node -> entries transpose (counting sort)
-  if (hipMemsetAsync(rowcnt, 0, sizeof(int64_t) * (m->ndof + 1), s) != hipSuccess) return fail(FPDE_EHIP);
-  if (P.n_ent > 0) k_row_count<<<nblk(P.n_ent), 256, 0, s>>>(P.ent_dof, P.n_ent, rowcnt);
-  if (hipcub::DeviceScan::ExclusiveSum(tmp, tb, rowcnt, P.row_off, (int)(m->ndof + 1), s) != hipSuccess)
-    return fail(FPDE_EHIP);
-  if (hipMemcpyAsync(cursor, P.row_off, sizeof(int64_t) * (m->ndof + 1), hipMemcpyDeviceToDevice, s) !=
-      hipSuccess)
-    return fail(FPDE_EHIP);
-  if (P.n_ent > 0) k_row_fill<<<nblk(P.n_ent), 256, 0, s>>>(P.ent_dof, P.n_ent, cursor, P.inc);
-  if ((st = dalloc(&P.inc_meta, P.n_ent)) != FPDE_OK) return fail(st);
-  if ((st = dalloc(&P.inc_w, P.n_ent)) != FPDE_OK) return fail(st);
-  if (P.n_ent > 0)
-    k_inc_meta<<<nblk(P.n_ent), 256, 0, s>>>(P.inc, P.ent_ray, P.off, m->vol,
-                                             m->rules + rule_offset(nq) + 4 * nq, P.G, nq, P.n_ent,
-                                             P.inc_meta, P.inc_w);
   if (hipGetLastError() != hipSuccess) return fail(FPDE_EHIP);
   f = take_flag(m, s);
   if (f != 0) return fail(f < 0 ? f : FPDE_EHIP);
-  dfree(cnt); dfree(cnt64); dfree(rowcnt); dfree(cursor);
+  dfree(cnt); dfree(cnt64);
   (void)hipFree(tmp);
   // sizes for reporting: entry pairs the accumulation multiplies
   {
