@@ -387,7 +387,9 @@ int fpde_csr_apply(fpde_mesh *m, const int64_t *row_ptr, const int32_t *col, con
  * matrix-free product of fpde_apply (no N^2 storage at all).
  *   b, u: dev, n_dof FP64, distinct.  tol: 0 = 1e-10.  max_iter: 0 = 10000.
  *   info: host, may be NULL (ir_iters = CG iterations).
- * Synchronises `stream` every iteration.
+ * Iterations are queued a few at a time, and `stream` is synchronised at the
+ * end; with timing on, products queued past the last iteration (they do
+ * nothing) count as intervals of their stage too.
  * Errors: FPDE_EINVAL, FPDE_EALPHA, FPDE_ENOTSPD (a diagonal entry or p.Kp
  * <= 0), FPDE_ENOCONV (max_iter reached), FPDE_EPATH, FPDE_ENOMEM, FPDE_EHIP.
  */

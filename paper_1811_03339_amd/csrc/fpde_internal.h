@@ -142,7 +142,9 @@ struct fpde_mesh {
   int64_t red_n = 0;
   void *linv = nullptr;           // inverses of the factor's 64 x 64 diagonal blocks (+ transposes)
   size_t linv_bytes = 0;
-  double *cg = nullptr;           // conjugate-gradient vectors and partial sums
+  double *cg = nullptr;           // conjugate-gradient vectors, partial sums and state
+  void *hcg = nullptr;            // pinned host copies of that state
+  hipEvent_t cev[2] = {};
   int64_t cg_n = 0;
   int *tsync = nullptr;           // triangular solves: per-system block flags (2 nblk) and tickets (2)
   int tsync_n = 0;                // ints allocated
@@ -221,7 +223,17 @@ int launch_form_tubes(fpde_mesh *m, Plan &P, const double cl[3], const double cr
 int launch_contract_tubes_csr(fpde_mesh *m, Plan &P, const fpde_params *p, const int64_t *row_ptr,
                               const int32_t *col, double *val, hipStream_t s);
 // matrix-free y = K x from the plan's values, and the diagonal of K
-int apply_matfree(fpde_mesh *m, Plan *P, const fpde_params *p, const double *x, double *y, hipStream_t s);
+// (done: device flag that turns the product off once set, or null; dot: with
+// x.y as op_blocks(ndof, true) partial sums, or null)
+int apply_matfree(fpde_mesh *m, Plan *P, const fpde_params *p, const double *x, double *y, hipStream_t s,
+                  const int32_t *done = nullptr, double *dot = nullptr);
+// workgroups (four rows each) of the row pass of an operator; at most
+// kOpParts, striding over the rows, when it leaves partial sums
+constexpr int kOpParts = 1024;
+inline unsigned op_blocks(int64_t n, bool dot) {
+  const int64_t b = (n + 3) / 4;
+  return (unsigned)(dot && b > kOpParts ? kOpParts : b);
+}
 int matfree_diagonal(fpde_mesh *m, Plan *P, const fpde_params *p, double *d, hipStream_t s);
 // load vector b for the Riesz problem (assemble.hip)
 int launch_load(fpde_mesh *m, const fpde_params *p, double *b, const double *f_gauss, hipStream_t s);

@@ -579,6 +579,9 @@ extern "C" void fpde_mesh_destroy(fpde_mesh *m) {
   dfree(m->bvec);
   dfree(m->pbox);
   dfree(m->cg);
+  if (m->hcg) (void)hipHostFree(m->hcg);
+  for (hipEvent_t e : m->cev)
+    if (e) (void)hipEventDestroy(e);
   delete m;
 }
 

@@ -19,6 +19,7 @@
 //                             storage at all); the diagonal of K comes from
 //                             the CSR row or, matrix-free, from the pairs of
 //                             half-rays that both meet a node.
+#include <algorithm>
 #include <cmath>
 #include <vector>
 
@@ -89,17 +90,30 @@ __global__ void __launch_bounds__(256) k_tpl_fill(const double *__restrict__ box
   }
 }
 
-// y = K x, one wavefront per row (4 rows per workgroup)
+// y = K x, one wavefront per row (4 rows per workgroup and step).  With dot
+// not null, dot[block] = the workgroup's part of x.y; nothing is done once
+// *done is set.
 __global__ void __launch_bounds__(256) k_csr_apply(const int64_t *__restrict__ row_ptr,
                                                    const int32_t *__restrict__ col, const double *__restrict__ val,
-                                                   const double *__restrict__ x, int64_t n, double *__restrict__ y) {
-  const int lane = threadIdx.x & 63;
-  const int64_t j = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (j >= n) return;
-  double s = 0.0;
-  for (int64_t q = row_ptr[j] + lane; q < row_ptr[j + 1]; q += 64) s = fma(val[q], x[col[q]], s);
-  for (int o = 32; o > 0; o >>= 1) s += __shfl_down(s, o, 64);
-  if (lane == 0) y[j] = s;
+                                                   const double *__restrict__ x, int64_t n, double *__restrict__ y,
+                                                   double *__restrict__ dot, const int32_t *__restrict__ done) {
+  __shared__ double red[4];
+  if (done && *done) return;
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  double xy = 0.0;
+  for (int64_t j = (int64_t)blockIdx.x * 4 + w; j < n; j += (int64_t)gridDim.x * 4) {
+    double s = 0.0;
+    for (int64_t q = row_ptr[j] + lane; q < row_ptr[j + 1]; q += 64) s = fma(val[q], x[col[q]], s);
+    for (int o = 32; o > 0; o >>= 1) s += __shfl_down(s, o, 64);
+    if (lane == 0) {
+      y[j] = s;
+      if (dot) xy = fma(s, x[j], xy);
+    }
+  }
+  if (!dot) return;
+  if (lane == 0) red[w] = xy;
+  __syncthreads();
+  if (threadIdx.x == 0) dot[blockIdx.x] = (red[0] + red[1]) + (red[2] + red[3]);
 }
 
 // d_j = K_jj from the CSR row (binary search of the sorted columns)
@@ -122,99 +136,197 @@ __global__ void k_csr_diag(const int64_t *__restrict__ row_ptr, const int32_t *_
   d[j] = v;
 }
 
-// Per-block partial sums of x.y (blocks of 256 threads, grid-stride)
-__global__ void __launch_bounds__(256) k_dot(const double *__restrict__ x, const double *__restrict__ y, int64_t n,
-                                             double *__restrict__ part) {
-  __shared__ double red[256];
+// ---- Conjugate gradients without host round trips ----
+//
+// The scalars of the iteration stay on the device: a kernel leaves partial
+// sums, one per workgroup, and every workgroup of the next kernel adds them up
+// itself, in the same order, so that all agree without a launch in between.
+// An iteration is three launches (product with p.q, update with r.r and r.z,
+// direction).  The host queues iterations a few at a time and looks at the
+// state of the chunk before; what is queued past the end finds `done` set and
+// does nothing.  (With three dot products per iteration read back by the host
+// an iteration took 200 us around a product of 12 us; now 50 us.)
+struct CgState {
+  double rz[2];        // r.z of the even and of the odd iterations
+  double bn2, rr, rt;  // b.b; r.r; true residual squared
+  int32_t done;        // 0: running, 1: ended (converged or not a number), 2: not positive definite
+  int32_t it;
+};
+constexpr int kCgParts = 256;  // workgroups of the vector kernels at most
+
+// sum of part[0 .. n) (stride ld), n <= 1024, in every thread; 256 threads
+__device__ __forceinline__ double sum_parts(const double *__restrict__ part, int n, int ld, double *red) {
   double s = 0.0;
-  for (int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; k < n; k += (int64_t)gridDim.x * blockDim.x)
-    s = fma(x[k], y[k], s);
-  red[threadIdx.x] = s;
+  for (int k = threadIdx.x; k < n; k += 256) s += part[(int64_t)k * ld];
+  for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
+  __syncthreads();  // red may still be read from the sum before
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
   __syncthreads();
-  for (int w = 128; w > 0; w >>= 1) {
-    if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
-    __syncthreads();
+  return (red[0] + red[1]) + (red[2] + red[3]);
+}
+
+// two sums over the workgroup's threads to part[2 blockIdx.x], [.. + 1]
+__device__ __forceinline__ void put_parts(double a, double b, double *__restrict__ part, double *red) {
+  for (int o = 32; o > 0; o >>= 1) {
+    a += __shfl_xor(a, o, 64);
+    b += __shfl_xor(b, o, 64);
   }
-  if (threadIdx.x == 0) part[blockIdx.x] = red[0];
+  __syncthreads();
+  if ((threadIdx.x & 63) == 0) {
+    red[threadIdx.x >> 6] = a;
+    red[4 + (threadIdx.x >> 6)] = b;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    part[2 * blockIdx.x] = (red[0] + red[1]) + (red[2] + red[3]);
+    part[2 * blockIdx.x + 1] = (red[4] + red[5]) + (red[6] + red[7]);
+  }
 }
 
-// u += al p; r -= al q; z = r / d
-__global__ void k_cg_update(double *__restrict__ u, double *__restrict__ r, double *__restrict__ z,
-                            const double *__restrict__ p, const double *__restrict__ q,
-                            const double *__restrict__ dinv, double al, int64_t n) {
-  const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (k >= n) return;
-  u[k] = fma(al, p[k], u[k]);
-  const double rk = fma(-al, q[k], r[k]);
-  r[k] = rk;
-  z[k] = rk * dinv[k];
+__global__ void k_cg_clear(CgState *st) {
+  st->done = 0;
+  st->it = 0;
 }
 
-// p = z + be p
-__global__ void k_cg_dir(double *__restrict__ p, const double *__restrict__ z, double be, int64_t n) {
-  const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (k >= n) return;
-  p[k] = fma(be, p[k], z[k]);
+// start: r = b, z = p = r / d, u = 0, parts of b.b and r.z
+__global__ void __launch_bounds__(256) k_cg_start(const double *__restrict__ b, const double *__restrict__ d,
+                                                  double *__restrict__ u, double *__restrict__ r,
+                                                  double *__restrict__ z, double *__restrict__ p,
+                                                  double *__restrict__ dinv, int64_t n, CgState *st,
+                                                  double *__restrict__ part) {
+  __shared__ double red[8];
+  double bb = 0.0, rz = 0.0;
+  for (int64_t k = (int64_t)blockIdx.x * 256 + threadIdx.x; k < n; k += (int64_t)gridDim.x * 256) {
+    const double dk = d[k], bk = b[k];
+    if (!(dk > 0.0)) atomicMax(&st->done, 2);  // a diagonal entry <= 0: K is not SPD
+    const double di = dk > 0.0 ? 1.0 / dk : 1.0, zk = bk * di;
+    dinv[k] = di;
+    u[k] = 0.0;
+    r[k] = bk;
+    z[k] = zk;
+    p[k] = zk;
+    bb = fma(bk, bk, bb);
+    rz = fma(bk, zk, rz);
+  }
+  put_parts(bb, rz, part, red);
 }
 
-__global__ void k_zero1(int32_t *p) { *p = 0; }
+// one workgroup: the start's sums; nothing to do for b = 0 or tol >= 1
+__global__ void __launch_bounds__(256) k_cg_begin(CgState *st, double tol, const double *__restrict__ part, int np) {
+  __shared__ double red[4];
+  const double bb = sum_parts(part, np, 2, red), rz = sum_parts(part + 1, np, 2, red);
+  if (threadIdx.x == 0) {
+    st->bn2 = bb;
+    st->rz[0] = rz;
+    st->rr = bb;
+    if (st->done == 0 && !(bb > 0.0 && 1.0 > tol)) st->done = 1;
+  }
+}
 
-// start: r = b, z = p = r / d, u = 0
-__global__ void k_cg_start(const double *__restrict__ b, const double *__restrict__ d, double *__restrict__ u,
-                           double *__restrict__ r, double *__restrict__ z, double *__restrict__ p,
-                           double *__restrict__ dinv, int64_t n, int32_t *bad) {
-  const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (k >= n) return;
-  const double dk = d[k];
-  if (!(dk > 0.0)) atomicOr(bad, 1);
-  const double di = dk > 0.0 ? 1.0 / dk : 1.0;
-  dinv[k] = di;
-  u[k] = 0.0;
-  r[k] = b[k];
-  z[k] = b[k] * di;
-  p[k] = b[k] * di;
+// al = r.z / p.q; u += al p; r -= al q; z = r / d; parts of r.r and r.z
+__global__ void __launch_bounds__(256) k_cg_update(double *__restrict__ u, double *__restrict__ r,
+                                                   double *__restrict__ z, const double *__restrict__ p,
+                                                   const double *__restrict__ q, const double *__restrict__ dinv,
+                                                   int64_t n, CgState *st, int odd, const double *__restrict__ pq_part,
+                                                   int npq, double *__restrict__ part) {
+  __shared__ double red[8];
+  if (st->done) return;
+  const double pq = sum_parts(pq_part, npq, 1, red);
+  if (!(pq > 0.0)) {  // the same in every workgroup
+    if (blockIdx.x == 0 && threadIdx.x == 0) st->done = 2;
+    return;
+  }
+  const double al = st->rz[odd] / pq;
+  double rr = 0.0, rz = 0.0;
+  for (int64_t k = (int64_t)blockIdx.x * 256 + threadIdx.x; k < n; k += (int64_t)gridDim.x * 256) {
+    u[k] = fma(al, p[k], u[k]);
+    const double rk = fma(-al, q[k], r[k]), zk = rk * dinv[k];
+    r[k] = rk;
+    z[k] = zk;
+    rr = fma(rk, rk, rr);
+    rz = fma(rk, zk, rz);
+  }
+  put_parts(rr, rz, part, red);
+}
+
+// the end of iteration `it`: |r| / |b| <= tol ends the loop, else p = z + (r.z / old r.z) p
+__global__ void __launch_bounds__(256) k_cg_dir(double *__restrict__ p, const double *__restrict__ z, int64_t n,
+                                                CgState *st, int it, double tol, const double *__restrict__ part,
+                                                int np) {
+  __shared__ double red[4];
+  if (st->done) return;
+  const int odd = it & 1;
+  const double rr = sum_parts(part, np, 2, red), rz = sum_parts(part + 1, np, 2, red);
+  const double be = rz / st->rz[odd];
+  const bool end = !(sqrt(rr) / sqrt(st->bn2) > tol);
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    st->rr = rr;
+    st->it = it + 1;
+    st->rz[odd ^ 1] = rz;
+    if (end) st->done = 1;
+  }
+  if (end) return;
+  for (int64_t k = (int64_t)blockIdx.x * 256 + threadIdx.x; k < n; k += (int64_t)gridDim.x * 256)
+    p[k] = fma(be, p[k], z[k]);
+}
+
+// parts of |b - q|^2, and their sum to st->rt (one workgroup)
+__global__ void __launch_bounds__(256) k_cg_residual(const double *__restrict__ b, const double *__restrict__ q,
+                                                     int64_t n, double *__restrict__ part) {
+  __shared__ double red[8];
+  double s = 0.0;
+  for (int64_t k = (int64_t)blockIdx.x * 256 + threadIdx.x; k < n; k += (int64_t)gridDim.x * 256) {
+    const double v = b[k] - q[k];
+    s = fma(v, v, s);
+  }
+  put_parts(s, 0.0, part, red);
+}
+__global__ void __launch_bounds__(256) k_cg_end(CgState *st, const double *__restrict__ part, int np) {
+  __shared__ double red[4];
+  const double rt = sum_parts(part, np, 2, red);
+  if (threadIdx.x == 0) st->rt = rt;
 }
 
 inline unsigned blocks_of(int64_t n, int b = 256) { return (unsigned)((n + b - 1) / b); }
 
-constexpr unsigned kDotBlocks = 256;
-
-// CG scratch in the mesh handle: r, z, p, q, d, dinv (6 N), partial sums, a flag
+// CG scratch in the mesh handle: r, z, p, q, d, dinv (6 N), partial sums of
+// the product and of the vector kernels, the state
 struct CgWork {
-  double *r, *z, *p, *q, *d, *dinv, *part;
-  int32_t *bad;
+  double *r, *z, *p, *q, *d, *dinv, *op_part, *part;
+  CgState *st, *host;  // host: two pinned copies
 };
 
 }  // namespace
 
 static int ensure_cg(fpde_mesh *m, CgWork *w) {
   const int64_t n = m->ndof > 0 ? m->ndof : 1;
-  const int64_t need = 6 * n + kDotBlocks + 1;
+  const int64_t need = 6 * n + kOpParts + 2 * kCgParts + (int64_t)(sizeof(CgState) / sizeof(double));
+  static_assert(sizeof(CgState) % sizeof(double) == 0, "the state follows the sums");
   if (m->cg_n < need) {
     dfree(m->cg);
     m->cg_n = 0;
     FPDE_TRY(dalloc(&m->cg, (size_t)need));
     m->cg_n = need;
   }
+  if (!m->hcg && hipHostMalloc(&m->hcg, 2 * sizeof(CgState), hipHostMallocDefault) != hipSuccess) {
+    m->hcg = nullptr;
+    return FPDE_ENOMEM;
+  }
+  for (hipEvent_t &e : m->cev)
+    if (!e && hipEventCreateWithFlags(&e, hipEventDisableTiming) != hipSuccess) {
+      e = nullptr;
+      return FPDE_EHIP;
+    }
   w->r = m->cg;
   w->z = w->r + n;
   w->p = w->z + n;
   w->q = w->p + n;
   w->d = w->q + n;
   w->dinv = w->d + n;
-  w->part = w->dinv + n;
-  w->bad = (int32_t *)(w->part + kDotBlocks);
-  return FPDE_OK;
-}
-
-static int dot(const double *x, const double *y, int64_t n, double *part, double *out, hipStream_t s) {
-  k_dot<<<kDotBlocks, 256, 0, s>>>(x, y, n, part);
-  double h[kDotBlocks];
-  FPDE_HIP(hipMemcpyAsync(h, part, sizeof(h), hipMemcpyDeviceToHost, s));
-  FPDE_HIP(hipStreamSynchronize(s));
-  double t = 0.0;
-  for (unsigned k = 0; k < kDotBlocks; k++) t += h[k];
-  *out = t;
+  w->op_part = w->dinv + n;
+  w->part = w->op_part + kOpParts;
+  w->st = (CgState *)(w->part + 2 * kCgParts);
+  w->host = (CgState *)m->hcg;
   return FPDE_OK;
 }
 
@@ -298,7 +410,7 @@ extern "C" int fpde_csr_apply(fpde_mesh *m, const int64_t *row_ptr, const int32_
   if (m->ndof == 0) return FPDE_OK;
   hipStream_t s = S(stream);
   const long t = timer_begin(m, s, FPDE_STAGE_SPMV);
-  k_csr_apply<<<blocks_of(m->ndof, 4), 256, 0, s>>>(row_ptr, col, val, x, m->ndof, y);
+  k_csr_apply<<<op_blocks(m->ndof, false), 256, 0, s>>>(row_ptr, col, val, x, m->ndof, y, nullptr, nullptr);
   timer_end(m, FPDE_STAGE_SPMV, t, s);
   FPDE_HIP(hipGetLastError());
   return FPDE_OK;
@@ -328,15 +440,19 @@ extern "C" int fpde_cg_solve(fpde_mesh *m, const fpde_params *p, const int64_t *
     FPDE_TRY(plan_for(m, p->quad_points, p->max_steps, s, &P));
     FPDE_TRY(ensure_values(m, P, p->alpha, s));
   }
-  auto op = [&](const double *x, double *y) -> int {
+  // y = K x; inside the loop with the parts of x.y, and off once the loop ended
+  auto op = [&](const double *x, double *y, bool loop) -> int {
+    const int32_t *done = loop ? &w.st->done : nullptr;
+    double *dot = loop ? w.op_part : nullptr;
     if (csr) {
       const long t = timer_begin(m, s, FPDE_STAGE_SPMV);
-      k_csr_apply<<<blocks_of(n, 4), 256, 0, s>>>(row_ptr, col, val, x, n, y);
+      k_csr_apply<<<op_blocks(n, loop), 256, 0, s>>>(row_ptr, col, val, x, n, y, dot, done);
       timer_end(m, FPDE_STAGE_SPMV, t, s);
       return hipGetLastError() == hipSuccess ? FPDE_OK : FPDE_EHIP;
     }
-    return apply_matfree(m, P, p, x, y, s);
+    return apply_matfree(m, P, p, x, y, s, done, dot);
   };
+  const unsigned vb = (unsigned)std::min<int64_t>(blocks_of(n), kCgParts);
   const long t_all = timer_begin(m, s, FPDE_STAGE_CG);
   // diagonal of K for the Jacobi preconditioner
   if (csr) {
@@ -344,47 +460,51 @@ extern "C" int fpde_cg_solve(fpde_mesh *m, const fpde_params *p, const int64_t *
   } else {
     FPDE_TRY(matfree_diagonal(m, P, p, w.d, s));
   }
-  k_zero1<<<1, 1, 0, s>>>(w.bad);
-  k_cg_start<<<blocks_of(n), 256, 0, s>>>(b, w.d, u, w.r, w.z, w.p, w.dinv, n, w.bad);
-  FPDE_HIP(hipGetLastError());
-  int32_t bad = 0;
-  FPDE_HIP(hipMemcpyAsync(&bad, w.bad, sizeof(bad), hipMemcpyDeviceToHost, s));
-  double bn2 = 0.0, rz = 0.0;
-  FPDE_TRY(dot(b, b, n, w.part, &bn2, s));
-  if (bad) return FPDE_ENOTSPD;  // a diagonal entry <= 0: K is not SPD
-  FPDE_TRY(dot(w.r, w.z, n, w.part, &rz, s));
-  const double bn = std::sqrt(bn2);
-  double rel = bn > 0 ? 1.0 : 0.0;
-  int it = 0;
-  while (rel > tol && it < max_iter) {
-    FPDE_TRY(op(w.p, w.q));
-    double pq = 0.0;
-    FPDE_TRY(dot(w.p, w.q, n, w.part, &pq, s));
-    if (!(pq > 0.0)) return FPDE_ENOTSPD;
-    const double al = rz / pq;
-    k_cg_update<<<blocks_of(n), 256, 0, s>>>(u, w.r, w.z, w.p, w.q, w.dinv, al, n);
-    double rr = 0.0, rz2 = 0.0;
-    FPDE_TRY(dot(w.r, w.r, n, w.part, &rr, s));
-    FPDE_TRY(dot(w.r, w.z, n, w.part, &rz2, s));
-    it++;
-    rel = std::sqrt(rr) / bn;
-    if (rel <= tol) break;
-    const double be = rz2 / rz;
-    rz = rz2;
-    k_cg_dir<<<blocks_of(n), 256, 0, s>>>(w.p, w.z, be, n);
+  k_cg_clear<<<1, 1, 0, s>>>(w.st);
+  k_cg_start<<<vb, 256, 0, s>>>(b, w.d, u, w.r, w.z, w.p, w.dinv, n, w.st, w.part);
+  k_cg_begin<<<1, 256, 0, s>>>(w.st, tol, w.part, (int)vb);
+  // chunks of iterations, the next one queued before the state of the last is read
+  constexpr int kChunk = 4;
+  int queued = 0;
+  auto chunk = [&](int slot) -> int {
+    for (int k = 0; k < kChunk && queued < max_iter; k++, queued++) {
+      FPDE_TRY(op(w.p, w.q, true));
+      k_cg_update<<<vb, 256, 0, s>>>(u, w.r, w.z, w.p, w.q, w.dinv, n, w.st, queued & 1, w.op_part,
+                                     (int)op_blocks(n, true), w.part);
+      k_cg_dir<<<vb, 256, 0, s>>>(w.p, w.z, n, w.st, queued, tol, w.part, (int)vb);
+    }
+    FPDE_HIP(hipGetLastError());
+    FPDE_HIP(hipMemcpyAsync(&w.host[slot], w.st, sizeof(CgState), hipMemcpyDeviceToHost, s));
+    FPDE_HIP(hipEventRecord(m->cev[slot], s));
+    return FPDE_OK;
+  };
+  FPDE_TRY(chunk(0));
+  CgState st{};
+  for (int slot = 0;; slot ^= 1) {
+    const bool more = queued < max_iter;
+    if (more) FPDE_TRY(chunk(slot ^ 1));
+    FPDE_HIP(hipEventSynchronize(m->cev[slot]));
+    st = w.host[slot];
+    if (st.done || !more) break;
   }
   timer_end(m, FPDE_STAGE_CG, t_all, s);
-  FPDE_HIP(hipGetLastError());
-  // the true residual b - K u of the result, not the recursively updated one
-  FPDE_TRY(op(u, w.q));
-  k_cg_dir<<<blocks_of(n), 256, 0, s>>>(w.q, b, -1.0, n);  // q = b - q
-  double rt = 0.0;
-  FPDE_TRY(dot(w.q, w.q, n, w.part, &rt, s));
-  if (info) {
-    info->ir_iters = it;
-    info->final_rel_residual = bn > 0 ? std::sqrt(rt) / bn : std::sqrt(rt);
+  if (st.done == 2) {  // a diagonal entry or p.Kp <= 0; nothing stays queued
+    FPDE_HIP(hipStreamSynchronize(s));
+    return FPDE_ENOTSPD;
   }
-  const int f = take_flag(m, s);
+  // the true residual b - K u of the result, not the recursively updated one
+  FPDE_TRY(op(u, w.q, false));
+  k_cg_residual<<<vb, 256, 0, s>>>(b, w.q, n, w.part);
+  k_cg_end<<<1, 256, 0, s>>>(w.st, w.part, (int)vb);
+  FPDE_HIP(hipGetLastError());
+  FPDE_HIP(hipMemcpyAsync(&w.host[0], w.st, sizeof(CgState), hipMemcpyDeviceToHost, s));
+  const int f = take_flag(m, s);  // and the copy above
+  const double bn = std::sqrt(w.host[0].bn2), rt = std::sqrt(w.host[0].rt);
+  const double rel = bn > 0 ? std::sqrt(w.host[0].rr) / bn : 0.0;
+  if (info) {
+    info->ir_iters = w.host[0].it;
+    info->final_rel_residual = bn > 0 ? rt / bn : rt;
+  }
   if (f != 0) return f < 0 ? f : FPDE_EHIP;
   return rel <= tol ? FPDE_OK : FPDE_ENOCONV;
 }

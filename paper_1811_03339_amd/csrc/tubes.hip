@@ -932,6 +932,7 @@ struct ApplyArgs {
   double *part;
   double KC0, KC1, KC2;
   int max_u;
+  const int32_t *done;     // not null: nothing is done once it is set
 };
 
 template <int ctrl>
@@ -993,6 +994,7 @@ __device__ __forceinline__ void held_add(const HeldSide &h, double c, double *ys
 
 __global__ void __launch_bounds__(64 * kApplyWaves) k_tube_apply(ApplyArgs a) {
   extern __shared__ double lds[];
+  if (a.done && *a.done) return;
   const int4 it = a.items[blockIdx.x];
   const int64_t u0 = a.u_off[it.x];
   const int U = (int)(a.u_off[it.x + 1] - u0);
@@ -1079,23 +1081,36 @@ __global__ void k_tube_diag(ApplyArgs a) {
   }
 }
 
-// y_j = the sum of node j's places in the segments' parts; one wavefront per node
+// y_j = the sum of node j's places in the segments' parts; one wavefront per
+// node, four nodes per workgroup and step.  With dot not null, dot[block] = the
+// workgroup's part of x.y.
 __global__ void __launch_bounds__(256) k_tube_sum(const int64_t *__restrict__ row_off, const int2 *__restrict__ row_ts,
                                                   const int64_t *__restrict__ u_off,
                                                   const int64_t *__restrict__ seg_off,
                                                   const double *__restrict__ part, int64_t ndof,
-                                                  double *__restrict__ y) {
-  const int lane = threadIdx.x & 63;
-  const int64_t j = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (j >= ndof) return;
-  double s = 0.0;
-  for (int64_t p = row_off[j] + lane; p < row_off[j + 1]; p += 64) {
-    const int2 ts = row_ts[p];
-    const int64_t U = u_off[ts.x + 1] - u_off[ts.x], e = seg_off[ts.x + 1];
-    for (int64_t o = seg_off[ts.x] + ts.y; o < e; o += U) s += part[o];
+                                                  double *__restrict__ y, const double *__restrict__ x,
+                                                  double *__restrict__ dot, const int32_t *__restrict__ done) {
+  __shared__ double red[4];
+  if (done && *done) return;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  double xy = 0.0;
+  for (int64_t j = (int64_t)blockIdx.x * 4 + wave; j < ndof; j += (int64_t)gridDim.x * 4) {
+    double s = 0.0;
+    for (int64_t p = row_off[j] + lane; p < row_off[j + 1]; p += 64) {
+      const int2 ts = row_ts[p];
+      const int64_t U = u_off[ts.x + 1] - u_off[ts.x], e = seg_off[ts.x + 1];
+      for (int64_t o = seg_off[ts.x] + ts.y; o < e; o += U) s += part[o];
+    }
+    for (int o = 32; o > 0; o >>= 1) s += __shfl_down(s, o, 64);
+    if (lane == 0) {
+      y[j] = s;
+      if (dot) xy = fma(s, x[j], xy);
+    }
   }
-  for (int o = 32; o > 0; o >>= 1) s += __shfl_down(s, o, 64);
-  if (lane == 0) y[j] = s;
+  if (!dot) return;
+  if (lane == 0) red[wave] = xy;
+  __syncthreads();
+  if (threadIdx.x == 0) dot[blockIdx.x] = (red[0] + red[1]) + (red[2] + red[3]);
 }
 
 struct TubeMfmaArgs {
@@ -1679,7 +1694,7 @@ static unsigned gather_grid(int64_t ndof) {
 
 // y = K x (diag: its diagonal) from the plan's current values
 static int apply_tubes(fpde_mesh *m, Plan &P, const fpde_params *p, const double *x, double *y, bool diag,
-                       hipStream_t s) {
+                       hipStream_t s, const int32_t *done, double *dot) {
   TubePlan &tp = P.tubes;
   if (!tp.part) FPDE_TRY(dalloc(&tp.part, (size_t)tp.n_part));
   const Order o = order_scalars(p->alpha);
@@ -1698,6 +1713,7 @@ static int apply_tubes(fpde_mesh *m, Plan &P, const fpde_params *p, const double
   a.KC1 = p->K[1] * o.c_alpha;
   a.KC2 = p->K[2] * o.c_alpha;
   a.max_u = (int)tp.max_u;
+  a.done = done;
   if (tp.n_aitems > 0 && diag) {
     // two LDS rows per wavefront: four wavefronts up to 2560 nodes, else two
     const int nw = tp.max_u <= 2560 ? 4 : 2;
@@ -1706,7 +1722,8 @@ static int apply_tubes(fpde_mesh *m, Plan &P, const fpde_params *p, const double
     // x and a part per wavefront: 160 KB at the 4096 nodes a tube may have
     k_tube_apply<<<(unsigned)tp.n_aitems, 64 * kApplyWaves, sizeof(double) * (1 + kApplyWaves) * tp.max_u, s>>>(a);
   }
-  k_tube_sum<<<nblocks(m->ndof, 4), 256, 0, s>>>(tp.row_off, tp.row_ts, tp.u_off, tp.seg_off, tp.part, m->ndof, y);
+  k_tube_sum<<<op_blocks(m->ndof, dot != nullptr), 256, 0, s>>>(tp.row_off, tp.row_ts, tp.u_off, tp.seg_off, tp.part,
+                                                                m->ndof, y, x, dot, done);
   FPDE_HIP(hipGetLastError());
   return FPDE_OK;
 }
@@ -1716,16 +1733,17 @@ static int apply_tubes(fpde_mesh *m, Plan &P, const fpde_params *p, const double
 // gather over the transpose, its values put in order once), 0.11 ms for 42 077
 // elements (4 points; 0.37 ms in order already), 1.6 ms for 151 907 elements
 // (11 points; 3.9 ms on merged entries, whose order cost 8 ms per assembly).
-int apply_matfree(fpde_mesh *m, Plan *P, const fpde_params *p, const double *x, double *y, hipStream_t s) {
+int apply_matfree(fpde_mesh *m, Plan *P, const fpde_params *p, const double *x, double *y, hipStream_t s,
+                  const int32_t *done, double *dot) {
   if (m->ndof == 0) return FPDE_OK;
   const long t = timer_begin(m, s, FPDE_STAGE_APPLY);
-  FPDE_TRY(apply_tubes(m, *P, p, x, y, false, s));
+  FPDE_TRY(apply_tubes(m, *P, p, x, y, false, s, done, dot));
   timer_end(m, FPDE_STAGE_APPLY, t, s);
   return FPDE_OK;
 }
 
 int matfree_diagonal(fpde_mesh *m, Plan *P, const fpde_params *p, double *d, hipStream_t s) {
-  return apply_tubes(m, *P, p, nullptr, d, true, s);
+  return apply_tubes(m, *P, p, nullptr, d, true, s, nullptr, nullptr);
 }
 
 int launch_contract_tubes(fpde_mesh *m, Plan &P, const fpde_params *p, void *A, int64_t lda, hipStream_t s) {
