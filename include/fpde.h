@@ -286,7 +286,7 @@ int fpde_adjoint(fpde_mesh *m, const fpde_params *p, const double *u, const doub
  * stage launch (no extra synchronisation while recording).
  * Stages: walk + closed-form evaluation, accumulation (both tube passes),
  * load vector, Cholesky factorisation (all panels), triangular solves,
- * matrix-free product, symbolic plan, adjoint re-walk, the tube products
+ * matrix-free product, symbolic plan, adjoint sums, the tube products
  * pass timed again on its own inside CONTRACT, for the problem of Sec. 3
  * its LU factorisation and its accumulation, and the sparse products and
  * conjugate-gradient solves.

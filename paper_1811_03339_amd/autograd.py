@@ -2,8 +2,8 @@
 
 forward(alpha, K) -> u = K(alpha, K)^{-1} b on the device (fpde_assemble +
 fpde_solve).  backward(gbar) -> lam = K^{-1} gbar with the stored factor
-(K is symmetric; fpde_solve_factored), then the adjoint kernel re-walks every
-path and returns dJ/dalpha and dJ/dK (fpde_adjoint).
+(K is symmetric; fpde_solve_factored), then the adjoint kernel sums over every
+path's segments and returns dJ/dalpha and dJ/dK (fpde_adjoint).
 
 The adjoint sums hold for a load vector that does not depend on alpha or K
 (f = 1 or source values given at the Gauss points).  The manufactured source

@@ -175,7 +175,7 @@ extern "C" int fpde_assemble_batch(fpde_mesh *m, int count, const fpde_params *p
   // rule (another plan, another value buffer).  Systems are taken with the
   // rules alternating; a walk waits for the caller's earlier work and for
   // the last accumulation that read its plan's values, an accumulation for
-  // its walk (events; the values are re-walked only when the orders
+  // its values (events; they are computed anew only when the orders
   // changed, as in fpde_assemble).
   if (!m->side && hipStreamCreateWithFlags(&m->side, hipStreamNonBlocking) != hipSuccess) m->side = nullptr;
   for (int k = 0; k < 2 * count + 1 && m->side; k++)

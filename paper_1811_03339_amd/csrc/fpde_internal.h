@@ -83,6 +83,15 @@ struct TubePlan {
 
 // Symbolic phase of one rule: derivative-vector sizes and the tubes.
 // Half-ray index (direction-major): h = dir * G + g, dir = 2 i + side.
+// One segment of a half-ray as the walk leaves it.  code: bits 2 j, 2 j + 1:
+// the slot of local vertex j; bit 8 + j: vertex j ends here as an entry;
+// bit 12 + k: slot k has a new vertex.
+struct alignas(16) SegRec {
+  double r;     // its end; negative on a half-ray's first segment
+  int32_t tet;
+  uint32_t code;
+};
+
 struct Plan {
   int nq = 0;
   int max_steps = 0;
@@ -90,6 +99,9 @@ struct Plan {
   int64_t n_half = 0;     // 6 G half-rays
   int64_t n_ent = 0;      // entries over all half-rays
   int64_t *off = nullptr;     // n_half + 1: entries of half-ray h
+  SegRec *seg = nullptr;      // segments of all half-rays
+  int64_t *strip = nullptr;   // 6 strips + 1: first segment of each strip of half-rays
+  int64_t strips = 0;         // per direction
   int32_t *ent_dof = nullptr; // n_ent
   double *ent_val = nullptr;  // n_ent: values, half-rays along e_i at order val_gamma[i]
   double val_gamma[3] = {-1.0, -1.0, -1.0};  // per axis; -1 = not computed
@@ -123,6 +135,7 @@ struct fpde_mesh {
   double *xyz = nullptr;          // nv*3
   int32_t *tet = nullptr;         // nt*4
   fpde::TetRec *rec = nullptr;    // nt
+  double4 *slope = nullptr;       // 3 nt: slopes of the volume coordinates per axis (with the first plan)
   double *vol = nullptr;          // nt
   int32_t *vt_off = nullptr;      // nv+1
   int32_t *vt_tet = nullptr;      // 4 nt

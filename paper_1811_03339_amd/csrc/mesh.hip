@@ -578,6 +578,7 @@ extern "C" void fpde_mesh_destroy(fpde_mesh *m) {
   dfree(m->xsplit);
   dfree(m->bvec);
   dfree(m->pbox);
+  dfree(m->slope);
   dfree(m->cg);
   if (m->hcg) (void)hipHostFree(m->hcg);
   for (hipEvent_t e : m->cev)
