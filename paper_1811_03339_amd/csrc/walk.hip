@@ -119,12 +119,6 @@ __device__ __forceinline__ TetRec load_rec(const TetRec *rec, int64_t t) {
   return R;
 }
 
-// r^e for r > 0 as exp(e ln r): the exponent e = 1 - gamma lies in (0, 1]
-// and r is a chord length (well inside (0, 1e3)), so |e ln r| is small and
-// the result is within a few ulp of the correctly rounded power -- the
-// values need 1e-10, not bit equality (only the element ids are bit-exact)
-__device__ __forceinline__ double powr(double r, double e) { return r > 0.0 ? exp(e * log(r)) : 0.0; }
-
 // Per-thread staging of a half-ray's consecutive outputs.  A thread writes
 // its entries one at a time as the walk proceeds, and its neighbours in the
 // wavefront write other half-rays' ranges, so plain stores leave every
@@ -380,19 +374,19 @@ __global__ void __launch_bounds__(256) k_walk(WalkArgs a) {
 
 // ---- Values from the segments ----
 //
-// A wavefront takes the segments of kStripRays half-rays of one direction, 64
+// A wavefront takes the segments of kStripRays half-rays of one direction, kStep
 // at a time, one per lane: the power at the segment's end (the one at its start
 // comes from the lane below), and the contribution of each of the element's
 // vertices to LDS, in the row of the slot that the vertex stands in while it
 // stays in the window.  An entry is then the sum of a run of its slot's row, one
 // lane per entry, in path order, and the entries leave coalesced.  What a run
-// has summed up by the end of the 64 segments is carried in front of the row.
+// has summed up by the end of the step is carried in front of the row.
 //
-// Bound by the FP64 instructions of the power and by 16 bytes read per segment
-// and 8 written per entry.  (Walking again for every order, one thread per
+// Bound by instruction issue (some 350 per step), at 2.1 of the 4.7 TB/s of a
+// copy (16 bytes read per segment, 8 written per entry).  (Walking again for every order, one thread per
 // half-ray, was bound by the intersections, three divisions each, and by lanes
-// waiting for the longest path of their wavefront: 0.76 against 0.39 ms for
-// 216 392 points, 9.2 against 5.7 ms for 1 670 977.)
+// waiting for the longest path of their wavefront: 0.76 against 0.30 ms for
+// 216 392 points, 9.2 against 4.6 ms for 1 670 977.)
 constexpr int kStripRays = 16;
 
 struct ValArgs {
@@ -446,15 +440,62 @@ __device__ __forceinline__ SegRec load_seg(const SegRec *p) {
   return r;
 }
 
+// r^e = 2^(e log2 r) for normal r > 0 and e in [0, 1], and log2 r.  With
+// m = r 2^-k in [1/sqrt 2, sqrt 2): log2 m = (2 / ln 2) atanh(q), q = (m - 1) /
+// (m + 1), |q| < 0.1716, the series up to q^19 (rest below 2^-57 of it); k +
+// log2 m and its product with e are kept as unevaluated sums of two doubles, and
+// 2^f on [-1/2, 1/2] is its series up to f^13 (rest below 2^-57).  At most 1.8
+// units of 2^-53 off over r in [1e-8, 1e4], where exp(e log(r)) has 4 to 32, in
+// a third of its instructions: the coefficients stand in scalar registers.
+__constant__ double kAtanh[10] = {0x1.71547652b82fep+1, 0x1.ec709dc3a03fdp-1, 0x1.2776c50ef9bfep-1,
+                                  0x1.a61762a7aded9p-2, 0x1.484b13d7c02a9p-2, 0x1.0c9a84994022dp-2,
+                                  0x1.c68f568d3176p-3,  0x1.89f3b1694cffep-3, 0x1.5b9ac9b743f0dp-3,
+                                  0x1.3703c1f4d0ffep-3};  // 2 / ((2 n + 1) ln 2)
+__constant__ double kExp2[14] = {0x1p+0,                0x1.62e42fefa39efp-1,  0x1.ebfbdff82c58fp-3,
+                                 0x1.c6b08d704a0cp-5,   0x1.3b2ab6fba4e77p-7,  0x1.5d87fe78a6731p-10,
+                                 0x1.430912f86c787p-13, 0x1.ffcbfc588b0c7p-17, 0x1.62c0223a5c824p-20,
+                                 0x1.b5253d395e7c4p-24, 0x1.e4cf5158b8ecap-28, 0x1.e8cac7351bb25p-32,
+                                 0x1.c3bd650fc2986p-36, 0x1.816193166d0f9p-40};  // ln 2^n / n!
+__device__ __forceinline__ double pow_unit(double r, double e, double *log2r = nullptr) {
+  int k = __builtin_amdgcn_frexp_exp(r);
+  double m = __builtin_amdgcn_frexp_mant(r);  // [1/2, 1)
+  const bool low = m < 0.70710678118654752;
+  m = low ? m + m : m;
+  k = low ? k - 1 : k;
+  const double f = m - 1.0, d = m + 1.0;
+  double x = __builtin_amdgcn_rcp(d);
+  x = fma(fma(-d, x, 1.0), x, x);
+  x = fma(fma(-d, x, 1.0), x, x);
+  double q = f * x;
+  q = fma(fma(-d, q, f), x, q);
+  const double z = q * q;
+  double p = kAtanh[9];
+#pragma unroll
+  for (int n = 8; n >= 0; n--) p = fma(p, z, kAtanh[n]);
+  const double t = p * q, kd = (double)k, hi = kd + t, lo = t - (hi - kd);
+  if (log2r) *log2r = hi;
+  const double y = e * hi, yl = fma(e, lo, fma(e, hi, -y));
+  const double n = __builtin_rint(y), g = (y - n) + yl;
+  double w = kExp2[13];
+#pragma unroll
+  for (int c = 12; c >= 0; c--) w = fma(w, g, kExp2[c]);
+  return __builtin_amdgcn_ldexp(w, (int)n);
+}
+
 constexpr int kValWaves = 4;
+// Segments per step of k_values: about as many entries end as segments are
+// taken, and four lanes are wanted for the carried sums, so that 60 mostly leave
+// one round of the entry loop (48 / 52 / 56 / 60 / 64: 0.35 / 0.33 / 0.31 / 0.30 /
+// 0.31 ms for 216 392 points).
+constexpr int kStep = 60;
 
 __global__ void __launch_bounds__(64 * kValWaves) k_values(ValArgs a) {
-  __shared__ double row_[kValWaves][4][65];       // [slot][0]: carried sum; [1 + lane]
+  __shared__ double row_[kValWaves * 4 * 65 + 4];  // per wavefront [slot][0]: carried sum; [1 + lane]
   __shared__ uint16_t list_[kValWaves][4 * 64];   // entries of the step: slot, last lane
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int64_t q = (int64_t)blockIdx.x * kValWaves + wave;
   if (q >= a.n_strip) return;
-  double(*row)[65] = row_[wave];
+  double(*row)[65] = reinterpret_cast<double(*)[65]>(row_ + wave * 4 * 65);
   uint16_t *list = list_[wave];
   const int64_t strip = a.strip0 + q;
   const int dir = (int)(strip / a.strips_per_dir), i = dir >> 1;
@@ -467,18 +508,18 @@ __global__ void __launch_bounds__(64 * kValWaves) k_values(ValArgs a) {
   double P_last = 0.0;
   SegRec nx{};
   int64_t s = a.strip[strip];
-  if (s + lane < s1) nx = load_seg(a.seg + s + lane);
-  for (; s < s1; s += 64) {
+  if (lane < kStep && s + lane < s1) nx = load_seg(a.seg + s + lane);
+  for (; s < s1; s += kStep) {
     const SegRec sr = nx;  // lanes past the end: r = 0, nothing new, nothing emitted
-    const bool act = s + lane < s1;
+    const bool act = lane < kStep && s + lane < s1;
     const double4 sl = slope[sr.tet];
     nx = SegRec{};
-    if (s + 64 + lane < s1) nx = load_seg(a.seg + s + 64 + lane);
-    const double P_hi = act ? powr(fabs(sr.r), ei) : 0.0;
+    if (lane < kStep && s + kStep + lane < s1) nx = load_seg(a.seg + s + kStep + lane);
+    const double P_hi = act ? pow_unit(fabs(sr.r), ei) : 0.0;
     double P_lo = __shfl_up(P_hi, 1, 64);
     if (lane == 0) P_lo = P_last;
     if (sr.r < 0.0) P_lo = 0.0;  // the half-ray's first segment
-    P_last = __shfl(P_hi, 63, 64);
+    P_last = __shfl(P_hi, kStep - 1, 64);
     const double dP = gi * (P_hi - P_lo);
     row[sr.code & 3][1 + lane] = (sgn * sl.x) * dP;
     row[(sr.code >> 2) & 3][1 + lane] = (sgn * sl.y) * dP;
@@ -506,13 +547,23 @@ __global__ void __launch_bounds__(64 * kValWaves) k_values(ValArgs a) {
         last = list[k] & 63;
       } else {
         slot = cs = k - total;
-        last = 63;
+        last = kStep - 1;
       }
       uint64_t m = slot < 2 ? (slot == 0 ? new0 : new1) : (slot == 2 ? new2 : new3);
       m &= ~0ull >> (63 - last);
       int x = m ? 64 - __clzll((long long)m) : 0;
-      double v = row[slot][x];
-      while (++x <= last + 1) v += row[slot][x];
+      const double *c = &row[slot][x];  // up to four cells past the run are read and left out
+      int left = last + 1 - x;          // cells after the first
+      double v = *c;
+      do {
+        const double c1 = c[1], c2 = c[2], c3 = c[3], c4 = c[4];
+        v += left > 0 ? c1 : 0.0;
+        v += left > 1 ? c2 : 0.0;
+        v += left > 2 ? c3 : 0.0;
+        v += left > 3 ? c4 : 0.0;
+        c += 4;
+        left -= 4;
+      } while (left > 0);
       if (k < total)
         out[k] = v;
       else
@@ -549,7 +600,7 @@ __global__ void k_elem_grad(const TetRec *__restrict__ rec, const double4 *__res
 // all of an element's vertices share the power's difference, so the sum over
 // the entries is one over the segments with the element's derivative of u (of
 // lam).  Strips as in k_values; each lane sums one of the four for one half-ray.
-// (Walking again with a gather of u and lam per entry: 1.13 against 0.41 ms for
+// (Walking again with a gather of u and lam per entry: 1.13 against 0.31 ms for
 // 168 308 points.)
 __global__ void __launch_bounds__(64 * kValWaves) k_adjoint_rays(ValArgs a) {
   __shared__ double row_[kValWaves][4][64];
@@ -579,9 +630,9 @@ __global__ void __launch_bounds__(64 * kValWaves) k_adjoint_rays(ValArgs a) {
     const double2 gr = grad[sr.tet];
     double P_hi = 0.0, Q_hi = 0.0;
     if (act) {
-      const double l = log(fabs(sr.r));
-      P_hi = exp(ei * l);
-      Q_hi = l * P_hi;
+      double l;
+      P_hi = pow_unit(fabs(sr.r), ei, &l);
+      Q_hi = (l * 0.69314718055994531) * P_hi;
     }
     double P_lo = __shfl_up(P_hi, 1, 64), Q_lo = __shfl_up(Q_hi, 1, 64);
     if (lane == 0) {
