@@ -81,8 +81,6 @@ struct TubePlan {
   double *part = nullptr;
 };
 
-// Symbolic phase of one rule: derivative-vector sizes and the tubes.
-// Half-ray index (direction-major): h = dir * G + g, dir = 2 i + side.
 // One segment of a half-ray as the walk leaves it.  code: bits 2 j, 2 j + 1:
 // the slot of local vertex j; bit 8 + j: vertex j ends here as an entry;
 // bit 12 + k: slot k has a new vertex.
@@ -92,15 +90,17 @@ struct alignas(16) SegRec {
   uint32_t code;
 };
 
+// Symbolic phase of one rule: derivative-vector sizes and the tubes.
+// Half-ray index (direction-major): h = dir * G + g, dir = 2 i + side.
 struct Plan {
   int nq = 0;
   int max_steps = 0;
   int64_t G = 0;          // Gauss points
-  int64_t n_half = 0;     // 6 G half-rays
+  int64_t n_half = 0;     // 6 G half-rays (two-dimensional: 4 G)
   int64_t n_ent = 0;      // entries over all half-rays
   int64_t *off = nullptr;     // n_half + 1: entries of half-ray h
   SegRec *seg = nullptr;      // segments of all half-rays
-  int64_t *strip = nullptr;   // 6 strips + 1: first segment of each strip of half-rays
+  int64_t *strip = nullptr;   // per direction, + 1: first segment of each strip of half-rays
   int64_t strips = 0;         // per direction
   int32_t *ent_dof = nullptr; // n_ent
   double *ent_val = nullptr;  // n_ent: values, half-rays along e_i at order val_gamma[i]
@@ -226,7 +226,19 @@ inline void invalidate_values(Plan *P) {
 int check_params(const fpde_mesh *m, const fpde_params *p);
 void free_plan(Plan &P);
 // tube plan of a rule whose entries exist (cell edge = kappa x mean element edge)
-int build_tubes(fpde_mesh *m, Plan &P, double kappa, hipStream_t s);
+// Mesh and rule of a plan's pairs (all device): vertex coordinates, elements of
+// dim + 1 vertices, their volumes, and the rule's nq x (dim + 1) barycentric
+// coordinates followed by its weights.
+struct TubeGeom {
+  int dim;
+  int64_t nv, nt;
+  const double *xyz;
+  const int32_t *elem;
+  const double *vol, *rule;
+};
+int build_tubes(fpde_mesh *m, Plan &P, const TubeGeom &q, double kappa, hipStream_t s);
+// strips of half-rays for the value pass from the first segment of every half-ray
+int plan_strips(Plan &P, const int64_t *soff, hipStream_t s);
 void free_tubes(TubePlan &tp);
 int launch_contract_tubes(fpde_mesh *m, Plan &P, const fpde_params *p, void *A, int64_t lda, hipStream_t s);
 // the same sums kept at the columns of a CSR pattern (FP64)

@@ -12,14 +12,17 @@
 //   k2_walk       one thread per half-ray (h = dir G + g, dir = 2 i + side):
 //                 the path (edge go-out: the triangle across it; vertex
 //                 go-out: the smallest-id triangle around the vertex in which
-//                 the ray advances), fused with the closed-form order-gamma
-//                 derivatives of the P1 basis (a 3-slot window over the
-//                 current triangle's vertices); the same IEEE arithmetic as
-//                 the reference definition, no FMA contraction, so element
-//                 ids are reproducible bit for bit;
-//   plan          entry counts and offsets, node -> entry transpose with the
-//                 partner half-ray of every incidence;
-//   k2_rows       one workgroup per (row, column chunk): row j adds, for each
+//                 the ray advances); the same IEEE arithmetic as the reference
+//                 definition, no FMA contraction, so element ids are
+//                 reproducible bit for bit;
+//   plan          the paths' segments, entry counts and offsets, and the tubes
+//                 of the three-dimensional accumulation (cells are intervals of
+//                 the other axis here);
+//   values        from the segments, as in three dimensions (the fourth volume
+//                 coordinate's slope is zero);
+//   accumulation  tube blocks and the row pass of the three-dimensional path;
+//                 where a chord has too many nodes for that, k2_rows: one
+//                 workgroup per (row, column chunk): row j adds, for each
 //                 incidence of node j, W value times the partner half-ray's
 //                 vector into an LDS row chunk (16 lanes per vector); the
 //                 chunk is written once;
@@ -43,13 +46,8 @@ struct TriRec {
   int32_t dof[3];
 };
 
-struct Plan2 {
-  int nq = 0, max_steps = 0;
-  int64_t G = 0, n_half = 0, n_ent = 0;
-  int64_t *off = nullptr;
-  int32_t *ent_dof = nullptr, *ent_ray = nullptr;
-  double *ent_val = nullptr;
-  double val_alpha = -1.0;
+struct Plan2 : Plan {
+  // node -> entry transpose for k2_rows, when the tubes are not used
   int64_t *row_off = nullptr;
   int4 *inc_meta = nullptr;  // entry, partner offset, partner length << 1 | axis, partner
   double *inc_w = nullptr;
@@ -227,7 +225,7 @@ int bits2(uint64_t v) {
 // ---------------------------------------------------------------------------
 // walk + closed-form derivatives
 // ---------------------------------------------------------------------------
-enum Walk2Mode { W2_COUNT = 0, W2_STRUCT = 1, W2_VALUES = 2 };
+enum Walk2Mode { W2_COUNT = 0, W2_STRUCT = 1 };
 
 struct Walk2Args {
   const TriRec *rec;
@@ -238,14 +236,13 @@ struct Walk2Args {
   int64_t G, h0, n;
   int cap, nq;
   const double *qbary;  // nq x 3
-  double e, inv_g2;     // 1 - gamma, 1/Gamma(2 - gamma)
   int32_t *cnt, *len;   // W2_COUNT
   uint64_t *hash;
   int32_t *ids;
   double *rend;
-  const int64_t *off;   // W2_STRUCT / W2_VALUES
-  int32_t *ent_dof, *ent_ray;
-  double *ent_val;
+  const int64_t *off, *soff;  // W2_STRUCT: first entry and segment of half-ray h
+  int32_t *ent_dof;
+  SegRec *seg;
 };
 
 struct Isect2 {
@@ -280,14 +277,17 @@ __device__ __forceinline__ void isect2(const TriRec &R, const double *u0, int i,
   o.jexit = je;
 }
 
-__device__ __forceinline__ double slope2(const TriRec &R, int j, int i) {
-  if (j > 0) return mcol2(R, j - 1, i);
-  return -(mcol2(R, 0, i) + mcol2(R, 1, i));
+// slopes of the area coordinates along the axes, as the value pass reads them
+__global__ void k2_slopes(const TriRec *__restrict__ rec, int64_t nt, double4 *__restrict__ slope) {
+  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (t >= nt) return;
+  const TriRec R = rec[t];
+#pragma unroll
+  for (int i = 0; i < 2; i++) {
+    const double a = R.M[i], b = R.M[2 + i];
+    slope[i * nt + t] = make_double4(-(a + b), a, b, 0.0);
+  }
 }
-
-// r^e for r > 0 as exp(e ln r) (e in (0, 1], r a chord length): a few ulp
-// from the correctly rounded power; the values need 1e-10, not bit equality
-__device__ __forceinline__ double powr2(double r, double e) { return r > 0.0 ? exp(e * log(r)) : 0.0; }
 
 template <int MODE>
 __global__ void __launch_bounds__(256) k2_walk(Walk2Args a) {
@@ -309,22 +309,21 @@ __global__ void __launch_bounds__(256) k2_walk(Walk2Args a) {
     u0[d] = acc;
   }
   int32_t wd[3] = {-1, -1, -1};
-  double wv[3] = {0.0, 0.0, 0.0};
+  int ws[3] = {0, 0, 0};  // slots of the window's vertices
   int64_t nemit = 0, base = 0;
-  if (MODE != W2_COUNT) base = a.off[h];
-  const double sgn = side ? -1.0 : 1.0;
-  auto emit = [&](int32_t d, double v) {
-    if (MODE == W2_STRUCT) {
-      a.ent_dof[base + nemit] = d;
-      a.ent_ray[base + nemit] = (int32_t)h;
-    } else if (MODE == W2_VALUES) {
-      a.ent_val[base + nemit] = v;
-    }
+  SegRec *seg = nullptr;
+  if (MODE == W2_STRUCT) {
+    base = a.off[h];
+    seg = a.seg + a.soff[h];
+  }
+  SegRec sr{};  // the last segment, written once it is known which vertices end there
+  auto emit = [&](int32_t d) {
+    if (MODE == W2_STRUCT) a.ent_dof[base + nemit] = d;
     nemit++;
   };
   uint64_t hsh = 14695981039346656037ull;
   int64_t t = t0;
-  double r_cur = 0.0, P_lo = 0.0;
+  double r_cur = 0.0;
   int nseg = 0;
   int status = FPDE_EPATH;
   for (int step = 0; step < a.cap + 64; step++) {
@@ -346,7 +345,8 @@ __global__ void __launch_bounds__(256) k2_walk(Walk2Args a) {
       }
       {
         const int32_t nd[3] = {R.dof[0], R.dof[1], R.dof[2]};
-        double na[3] = {0.0, 0.0, 0.0};
+        int ns[3] = {-1, -1, -1};
+        int used = 0;
 #pragma unroll
         for (int j = 0; j < 3; j++) {
           if (wd[j] < 0) continue;
@@ -354,24 +354,33 @@ __global__ void __launch_bounds__(256) k2_walk(Walk2Args a) {
 #pragma unroll
           for (int m = 0; m < 3; m++)
             if (nd[m] == wd[j]) {
-              na[m] = wv[j];
+              ns[m] = ws[j];
+              used |= 1 << ws[j];
               kept = true;
             }
-          if (!kept) emit(wd[j], wv[j]);
+          if (!kept) {
+            emit(wd[j]);
+            sr.code |= 256u << j;
+          }
+        }
+        if (MODE == W2_STRUCT) {
+          if (nseg > 0) seg[nseg - 1] = sr;
+          sr.r = nseg > 0 ? o.r_max : -o.r_max;
+          sr.tet = (int32_t)t;
+          sr.code = 3u << 6 | 8u << 12;  // the fourth slot is always new and empty
+#pragma unroll
+          for (int m = 0; m < 3; m++) {
+            if (ns[m] < 0) {  // a new vertex takes the first free slot
+              ns[m] = __builtin_ctz(~used);
+              used |= 1 << ns[m];
+              sr.code |= 4096u << ns[m];
+            }
+            sr.code |= (uint32_t)ns[m] << (2 * m);
+            ws[m] = ns[m];
+          }
         }
 #pragma unroll
-        for (int j = 0; j < 3; j++) {
-          wd[j] = nd[j];
-          wv[j] = na[j];
-        }
-      }
-      if (MODE == W2_VALUES) {
-        const double P_hi = powr2(o.r_max, a.e);
-        const double dP = a.inv_g2 * (P_hi - P_lo);
-        P_lo = P_hi;
-#pragma unroll
-        for (int j = 0; j < 3; j++)
-          if (wd[j] >= 0) wv[j] += sgn * slope2(R, j, i) * dP;
+        for (int j = 0; j < 3; j++) wd[j] = nd[j];
       }
       nseg++;
       r_cur = o.r_max;
@@ -430,7 +439,11 @@ __global__ void __launch_bounds__(256) k2_walk(Walk2Args a) {
   }
 #pragma unroll
   for (int j = 0; j < 3; j++)
-    if (wd[j] >= 0) emit(wd[j], wv[j]);
+    if (wd[j] >= 0) {
+      emit(wd[j]);
+      sr.code |= 256u << j;
+    }
+  if (MODE == W2_STRUCT) seg[nseg - 1] = sr;
   if (MODE == W2_COUNT) {
     a.cnt[k] = (int32_t)nemit;
     if (a.len) a.len[k] = nseg;
@@ -449,14 +462,19 @@ __global__ void k2_row_count(const int32_t *__restrict__ ent_dof, int64_t n, int
 }
 
 // incidence record of entry e, placed at its node's next free slot
-__global__ void k2_inc_fill(const int32_t *__restrict__ ent_dof, const int32_t *__restrict__ ent_ray,
-                            const int64_t *__restrict__ off, const double *__restrict__ area,
+__global__ void k2_inc_fill(const int32_t *__restrict__ ent_dof, const int64_t *__restrict__ off, int64_t n_half,
+                            const double *__restrict__ area,
                             const double *__restrict__ wq, int64_t G, int nq, int64_t n,
                             int64_t *__restrict__ cursor, int4 *__restrict__ meta, double *__restrict__ w) {
   const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (e >= n) return;
   const int64_t p = (int64_t)atomicAdd((unsigned long long *)&cursor[ent_dof[e]], 1ull);
-  const int64_t h = ent_ray[e];
+  int64_t h = 0, hi = n_half - 1;  // the last half-ray that starts at e or before
+  while (h < hi) {
+    const int64_t mid = (h + hi + 1) >> 1;
+    if (off[mid] <= e) h = mid;
+    else hi = mid - 1;
+  }
   const int dir = (int)(h / G);
   const int64_t g = h - (int64_t)dir * G;
   const int64_t partner = (dir & 1) ? h - G : h + G;
@@ -591,9 +609,8 @@ __global__ void k2_load(Load2Args a, double *__restrict__ b) {
 // host side
 // ---------------------------------------------------------------------------
 static void free_plan2(Plan2 &P) {
-  dfree(P.off); dfree(P.ent_dof); dfree(P.ent_ray); dfree(P.ent_val); dfree(P.row_off); dfree(P.inc_meta);
-  dfree(P.inc_w);
-  P = Plan2();
+  dfree(P.row_off); dfree(P.inc_meta); dfree(P.inc_w);
+  free_plan(P);
 }
 
 static Walk2Args walk2_args(fpde_mesh2d *m, const Plan2 &P) {
@@ -617,74 +634,134 @@ static void launch_walk2(const Walk2Args &a, hipStream_t s) {
   if (a.n > 0) k2_walk<MODE><<<nblk2(a.n), 256, 0, s>>>(a);
 }
 
+// Tube cell edge in mean edges.  One assembly's accumulation, 7 points, at cells
+// of 1.0 / 0.7 / 0.5 / 0.35 / 0.25 / 0.18: 4 494 unknowns (disk) 0.93 / 0.63 /
+// 0.51 / 0.41 / 0.38 / 0.39 ms (k2_rows: 3.7), 16 129 unknowns (square) 9.4 / 8.1 /
+// 7.8 / 7.0 / 6.4 / 6.3 ms (k2_rows: 74).
+constexpr double kTubeCell2 = 0.25;
+
+// Whether the tubes are used.  Their pass and the row pass are two launches: at
+// 73 unknowns 16 against 10 us (3 points) for k2_rows, at 225 unknowns 17
+// against 17 us, with 7 points 21 against 36.  A tube of U nodes takes
+// U (U + 1) / 2 / kBand bands, and each reads its entries again, while k2_rows
+// takes a row once per kChunk2 columns: on strips of 500 x 8 cells (1 000 nodes a
+// chord) 57 against 74 ms, of 1 000 x 3 cells (2 000 nodes) 275 against 159 ms,
+// one chunk each; 65 025 unknowns (square, 16 bands against 8 chunks) 0.23
+// against 5.0 s.
+static bool tubes_pay(const fpde_mesh2d *m, int64_t max_u) {
+  const int64_t bands = max_u * (max_u + 1) / 2 / 20160, chunks = (m->ndof + kChunk2 - 1) / kChunk2;
+  return m->ndof > 128 && bands <= 32 * chunks;
+}
+
+// node -> entry transpose of the row accumulation
+static int build_rows2(fpde_mesh2d *m, Plan2 &P, hipStream_t s) {
+  int64_t *rowcnt = nullptr, *cursor = nullptr;
+  void *tmp = nullptr;
+  auto done = [&](int code) {
+    dfree(rowcnt); dfree(cursor);
+    if (tmp) (void)hipFree(tmp);
+    return code;
+  };
+  int st;
+  size_t tb = 0;
+  if ((st = dalloc(&P.row_off, m->ndof + 1)) != FPDE_OK) return done(st);
+  if ((st = dalloc(&rowcnt, m->ndof + 1)) != FPDE_OK) return done(st);
+  if ((st = dalloc(&cursor, m->ndof + 1)) != FPDE_OK) return done(st);
+  if ((st = dalloc(&P.inc_meta, P.n_ent)) != FPDE_OK) return done(st);
+  if ((st = dalloc(&P.inc_w, P.n_ent)) != FPDE_OK) return done(st);
+  if (hipcub::DeviceScan::ExclusiveSum(nullptr, tb, rowcnt, P.row_off, (int)(m->ndof + 1), s) != hipSuccess)
+    return done(FPDE_EHIP);
+  if (hipMalloc(&tmp, tb) != hipSuccess) return done(FPDE_ENOMEM);
+  if (hipMemsetAsync(rowcnt, 0, sizeof(int64_t) * (m->ndof + 1), s) != hipSuccess) return done(FPDE_EHIP);
+  if (P.n_ent > 0) k2_row_count<<<nblk2(P.n_ent), 256, 0, s>>>(P.ent_dof, P.n_ent, rowcnt);
+  if (hipcub::DeviceScan::ExclusiveSum(tmp, tb, rowcnt, P.row_off, (int)(m->ndof + 1), s) != hipSuccess)
+    return done(FPDE_EHIP);
+  if (hipMemcpyAsync(cursor, P.row_off, sizeof(int64_t) * (m->ndof + 1), hipMemcpyDeviceToDevice, s) != hipSuccess)
+    return done(FPDE_EHIP);
+  if (P.n_ent > 0)
+    k2_inc_fill<<<nblk2(P.n_ent), 256, 0, s>>>(P.ent_dof, P.off, P.n_half, m->area,
+                                               m->rules + rule2_offset(P.nq) + 3 * P.nq, P.G, P.nq, P.n_ent, cursor,
+                                               P.inc_meta, P.inc_w);
+  if (hipGetLastError() != hipSuccess || hipStreamSynchronize(s) != hipSuccess) return done(FPDE_EHIP);
+  return done(FPDE_OK);
+}
+
 static int build_plan2(fpde_mesh2d *m, Plan2 &P, int nq, int max_steps, hipStream_t s) {
   P.nq = nq;
   P.max_steps = max_steps;
   P.G = m->nt * nq;
   P.n_half = 4 * P.G;
-  int32_t *cnt = nullptr;
-  int64_t *cnt64 = nullptr, *rowcnt = nullptr, *cursor = nullptr;
+  int32_t *cnt = nullptr, *len = nullptr;
+  int64_t *cnt64 = nullptr, *soff = nullptr;
   void *tmp = nullptr;
   auto fail = [&](int code) {
-    dfree(cnt); dfree(cnt64); dfree(rowcnt); dfree(cursor);
+    dfree(cnt); dfree(cnt64); dfree(len); dfree(soff);
     if (tmp) (void)hipFree(tmp);
     free_plan2(P);
     return code;
   };
   int st;
   if ((st = dalloc(&cnt, P.n_half + 1)) != FPDE_OK) return fail(st);
+  if ((st = dalloc(&len, P.n_half + 1)) != FPDE_OK) return fail(st);
   if ((st = dalloc(&cnt64, P.n_half + 1)) != FPDE_OK) return fail(st);
+  if ((st = dalloc(&soff, P.n_half + 1)) != FPDE_OK) return fail(st);
   if ((st = dalloc(&P.off, P.n_half + 1)) != FPDE_OK) return fail(st);
+  if (!m->ws->slope) {  // for every plan of the mesh
+    if ((st = dalloc(&m->ws->slope, 2 * m->nt)) != FPDE_OK) return fail(st);
+    k2_slopes<<<nblk2(m->nt), 256, 0, s>>>(m->rec, m->nt, m->ws->slope);
+  }
   k2_fill<<<nblk2(P.n_half + 1), 256, 0, s>>>(cnt, P.n_half + 1, 0);
+  k2_fill<<<nblk2(P.n_half + 1), 256, 0, s>>>(len, P.n_half + 1, 0);
   Walk2Args a = walk2_args(m, P);
   a.h0 = 0;
   a.n = P.n_half;
   a.cnt = cnt;
+  a.len = len;
   launch_walk2<W2_COUNT>(a, s);
   k2_i32_to_i64<<<nblk2(P.n_half + 1), 256, 0, s>>>(cnt, P.n_half + 1, cnt64);
-  size_t need = 0, need2 = 0;
-  if (hipcub::DeviceScan::ExclusiveSum(nullptr, need, cnt64, P.off, (int)(P.n_half + 1), s) != hipSuccess)
+  size_t tb = 0;
+  if (hipcub::DeviceScan::ExclusiveSum(nullptr, tb, cnt64, P.off, (int)(P.n_half + 1), s) != hipSuccess)
     return fail(FPDE_EHIP);
-  if (hipcub::DeviceScan::ExclusiveSum(nullptr, need2, cnt64, P.off, (int)(m->ndof + 1), s) != hipSuccess)
-    return fail(FPDE_EHIP);
-  size_t tb = need > need2 ? need : need2;
   if (hipMalloc(&tmp, tb) != hipSuccess) return fail(FPDE_ENOMEM);
   if (hipcub::DeviceScan::ExclusiveSum(tmp, tb, cnt64, P.off, (int)(P.n_half + 1), s) != hipSuccess)
     return fail(FPDE_EHIP);
-  if (hipMemcpyAsync(&P.n_ent, P.off + P.n_half, sizeof(int64_t), hipMemcpyDeviceToHost, s) != hipSuccess)
+  k2_i32_to_i64<<<nblk2(P.n_half + 1), 256, 0, s>>>(len, P.n_half + 1, cnt64);
+  if (hipcub::DeviceScan::ExclusiveSum(tmp, tb, cnt64, soff, (int)(P.n_half + 1), s) != hipSuccess)
+    return fail(FPDE_EHIP);
+  if ((st = plan_strips(P, soff, s)) != FPDE_OK) return fail(st);
+  int64_t n_seg = 0;
+  if (hipMemcpyAsync(&n_seg, soff + P.n_half, sizeof(int64_t), hipMemcpyDeviceToHost, s) != hipSuccess ||
+      hipMemcpyAsync(&P.n_ent, P.off + P.n_half, sizeof(int64_t), hipMemcpyDeviceToHost, s) != hipSuccess)
     return fail(FPDE_EHIP);
   int f = take_flag(m->ws, s);
   if (f != 0) return fail(f < 0 ? f : FPDE_EHIP);
   if (P.n_ent >= (int64_t(1) << 31)) return fail(FPDE_EUNSUPPORTED);
   if ((st = dalloc(&P.ent_dof, P.n_ent)) != FPDE_OK) return fail(st);
-  if ((st = dalloc(&P.ent_ray, P.n_ent)) != FPDE_OK) return fail(st);
   if ((st = dalloc(&P.ent_val, P.n_ent)) != FPDE_OK) return fail(st);
-  if ((st = dalloc(&P.row_off, m->ndof + 1)) != FPDE_OK) return fail(st);
-  if ((st = dalloc(&rowcnt, m->ndof + 1)) != FPDE_OK) return fail(st);
-  if ((st = dalloc(&cursor, m->ndof + 1)) != FPDE_OK) return fail(st);
-  if ((st = dalloc(&P.inc_meta, P.n_ent)) != FPDE_OK) return fail(st);
-  if ((st = dalloc(&P.inc_w, P.n_ent)) != FPDE_OK) return fail(st);
+  if ((st = dalloc(&P.seg, n_seg)) != FPDE_OK) return fail(st);
   a.off = P.off;
+  a.soff = soff;
   a.ent_dof = P.ent_dof;
-  a.ent_ray = P.ent_ray;
+  a.seg = P.seg;
   launch_walk2<W2_STRUCT>(a, s);
-  if (hipMemsetAsync(rowcnt, 0, sizeof(int64_t) * (m->ndof + 1), s) != hipSuccess) return fail(FPDE_EHIP);
-  if (P.n_ent > 0) k2_row_count<<<nblk2(P.n_ent), 256, 0, s>>>(P.ent_dof, P.n_ent, rowcnt);
-  if (hipcub::DeviceScan::ExclusiveSum(tmp, tb, rowcnt, P.row_off, (int)(m->ndof + 1), s) != hipSuccess)
-    return fail(FPDE_EHIP);
-  if (hipMemcpyAsync(cursor, P.row_off, sizeof(int64_t) * (m->ndof + 1), hipMemcpyDeviceToDevice, s) !=
-      hipSuccess)
-    return fail(FPDE_EHIP);
-  if (P.n_ent > 0)
-    k2_inc_fill<<<nblk2(P.n_ent), 256, 0, s>>>(P.ent_dof, P.ent_ray, P.off, m->area,
-                                               m->rules + rule2_offset(nq) + 3 * nq, P.G, nq, P.n_ent, cursor,
-                                               P.inc_meta, P.inc_w);
   if (hipGetLastError() != hipSuccess) return fail(FPDE_EHIP);
   f = take_flag(m->ws, s);
   if (f != 0) return fail(f < 0 ? f : FPDE_EHIP);
-  dfree(cnt); dfree(cnt64); dfree(rowcnt); dfree(cursor);
+  dfree(cnt); dfree(cnt64); dfree(len); dfree(soff);
   (void)hipFree(tmp);
-  P.val_alpha = -1.0;
+  tmp = nullptr;
+  // tubes with their block scratch, or the transpose where they do not fit
+  const TubeGeom q{2, m->nv, m->nt, m->xy, m->tri, m->area, m->rules + rule2_offset(nq)};
+  st = build_tubes(m->ws, P, q, kTubeCell2, s);
+  const bool pay = st == FPDE_OK && tubes_pay(m, P.tubes.max_u);
+  if (pay) st = dalloc(&P.tubes.blk, P.tubes.blk_n);
+  if (!pay || st != FPDE_OK) {
+    if (st != FPDE_OK && st != FPDE_EUNSUPPORTED && st != FPDE_ENOMEM) return fail(st);
+    free_tubes(P.tubes);
+    (void)hipGetLastError();
+    if ((st = build_rows2(m, P, s)) != FPDE_OK) return fail(st);
+  }
+  invalidate_values(&P);
   return FPDE_OK;
 }
 
@@ -806,21 +883,8 @@ static int mesh2_build(fpde_mesh2d *m, const double *xy, const int32_t *tri, hip
 }
 
 static int ensure_values2(fpde_mesh2d *m, Plan2 *P, double alpha, hipStream_t s) {
-  if (P->val_alpha == alpha) return FPDE_OK;
-  const Order o = order_scalars(alpha);
-  Walk2Args a = walk2_args(m, *P);
-  a.h0 = 0;
-  a.n = P->n_half;
-  a.e = o.e;
-  a.inv_g2 = o.inv_g2;
-  a.off = P->off;
-  a.ent_val = P->ent_val;
-  const long t = timer_begin(m->ws, s, FPDE_STAGE_WALK);
-  launch_walk2<W2_VALUES>(a, s);
-  timer_end(m->ws, FPDE_STAGE_WALK, t, s);
-  FPDE_HIP(hipGetLastError());
-  P->val_alpha = alpha;
-  return FPDE_OK;
+  const double g[3] = {0.5 * alpha, 0.5 * alpha, P->val_gamma[2]};
+  return ensure_values_axes(m->ws, P, g, s);
 }
 
 }  // namespace fpde
@@ -850,6 +914,7 @@ extern "C" int fpde_mesh2d_create(const double *xy, int64_t n_vert, const int32_
   m->nv = n_vert;
   m->nt = n_tri;
   int st = workspace_new(0, &m->ws);
+  if (st == FPDE_OK) m->ws->nt = n_tri;
   if (st == FPDE_OK) st = mesh2_build(m, xy, tri, S(stream));
   if (st != FPDE_OK) {
     fpde_mesh2d_destroy(m);
@@ -916,22 +981,31 @@ extern "C" int fpde_assemble2d(fpde_mesh2d *m, const fpde_params2d *p, double *A
   FPDE_TRY(plan2_for(m, p->quad_points, p->max_steps, s, &P));
   FPDE_TRY(ensure_values2(m, P, p->alpha, s));
   const Order o = order_scalars(p->alpha);
-  Rows2Args a{};
-  a.row_off = P->row_off;
-  a.meta = P->inc_meta;
-  a.w = P->inc_w;
-  a.ent_dof = P->ent_dof;
-  a.ent_val = P->ent_val;
-  a.ndof = m->ndof;
-  a.lda = lda;
-  a.chunk = (int)(m->ndof < kChunk2 ? m->ndof : kChunk2);
-  a.KC0 = p->K[0] * o.c_alpha;
-  a.KC1 = p->K[1] * o.c_alpha;
-  const unsigned nchunk = (unsigned)((m->ndof + a.chunk - 1) / a.chunk);
-  const long t = timer_begin(m->ws, s, FPDE_STAGE_CONTRACT);
-  k2_rows<<<dim3((unsigned)m->ndof, nchunk), 256, 0, s>>>(a, A);
-  timer_end(m->ws, FPDE_STAGE_CONTRACT, t, s);
-  FPDE_HIP(hipGetLastError());
+  if (!P->inc_meta) {
+    fpde_params q{};
+    q.alpha = p->alpha;
+    q.K[0] = p->K[0];
+    q.K[1] = p->K[1];
+    q.precision = FPDE_FP64;
+    FPDE_TRY(launch_contract_tubes(m->ws, *P, &q, A, lda, s));
+  } else {
+    Rows2Args a{};
+    a.row_off = P->row_off;
+    a.meta = P->inc_meta;
+    a.w = P->inc_w;
+    a.ent_dof = P->ent_dof;
+    a.ent_val = P->ent_val;
+    a.ndof = m->ndof;
+    a.lda = lda;
+    a.chunk = (int)(m->ndof < kChunk2 ? m->ndof : kChunk2);
+    a.KC0 = p->K[0] * o.c_alpha;
+    a.KC1 = p->K[1] * o.c_alpha;
+    const unsigned nchunk = (unsigned)((m->ndof + a.chunk - 1) / a.chunk);
+    const long t = timer_begin(m->ws, s, FPDE_STAGE_CONTRACT);
+    k2_rows<<<dim3((unsigned)m->ndof, nchunk), 256, 0, s>>>(a, A);
+    timer_end(m->ws, FPDE_STAGE_CONTRACT, t, s);
+    FPDE_HIP(hipGetLastError());
+  }
   if (b) {
     Load2Args l{};
     l.vert_of_dof = m->vert_of_dof;
@@ -959,7 +1033,7 @@ extern "C" int fpde_assemble2d(fpde_mesh2d *m, const fpde_params2d *p, double *A
   }
   const int f = take_flag(m->ws, s);
   if (f != 0) {
-    P->val_alpha = -1.0;
+    invalidate_values(P);
     return f < 0 ? f : FPDE_EHIP;
   }
   return FPDE_OK;

@@ -69,29 +69,32 @@ __host__ __device__ inline int tri_base(int lo, int U) { return lo * (2 * U - lo
 
 inline unsigned nblocks(int64_t n, int b = 256) { return (unsigned)((n + b - 1) / b); }
 
-// Pair id P = i * G + g.  Key = tube cell of x_g in the plane orthogonal to
-// e_i; x_g summed in the walk's order ((0 + b0 v0) + b1 v1) + ...
-__global__ void k_pair_keys(const int32_t *__restrict__ tet, const double *__restrict__ xyz,
-                            const double *__restrict__ qbary, int nq, int64_t G, double lo0, double lo1, double lo2,
-                            double inv_c, int ncell, uint32_t *__restrict__ key, int32_t *__restrict__ val) {
+// Pair id P = i * G + g.  Key = tube cell of x_g in the plane (2-D: on the
+// line) orthogonal to e_i; x_g summed in the walk's order ((0 + b0 v0) + b1 v1) + ...
+__global__ void k_pair_keys(TubeGeom q, int nq, int64_t G, double lo0, double lo1, double lo2, double inv_c,
+                            int ncell, uint32_t *__restrict__ key, int32_t *__restrict__ val) {
   const int64_t P = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (P >= 3 * G) return;
+  if (P >= q.dim * G) return;
   const int i = (int)(P / G);
   const int64_t g = P - (int64_t)i * G;
   const int64_t t = g / nq;
-  const int q = (int)(g - t * nq);
+  const int k = (int)(g - t * nq), nv = q.dim + 1;
   double x[3] = {0.0, 0.0, 0.0};
-  for (int m = 0; m < 4; m++) {
-    const double b = qbary[4 * q + m];
-    const double *v = xyz + 3 * (int64_t)tet[4 * t + m];
-    for (int d = 0; d < 3; d++) x[d] = x[d] + b * v[d];
+  for (int m = 0; m < nv; m++) {
+    const double b = q.rule[nv * k + m];
+    const double *v = q.xyz + q.dim * (int64_t)q.elem[nv * t + m];
+    x[0] = x[0] + b * v[0];
+    x[1] = x[1] + b * v[1];
+    if (q.dim == 3) x[2] = x[2] + b * v[2];
   }
   const double lo[3] = {lo0, lo1, lo2};
-  const int a1 = (i + 1) % 3, a2 = (i + 2) % 3;
-  int c1 = (int)floor((x[a1] - lo[a1]) * inv_c), c2 = (int)floor((x[a2] - lo[a2]) * inv_c);
-  c1 = c1 < 0 ? 0 : (c1 >= ncell ? ncell - 1 : c1);
-  c2 = c2 < 0 ? 0 : (c2 >= ncell ? ncell - 1 : c2);
-  key[P] = ((uint32_t)i * (uint32_t)ncell + (uint32_t)c1) * (uint32_t)ncell + (uint32_t)c2;
+  uint32_t id = (uint32_t)i;
+  for (int d = 1; d < q.dim; d++) {
+    const int ax = (i + d) % q.dim;
+    const int c = (int)floor(((ax == 0 ? x[0] : (ax == 1 ? x[1] : x[2])) - lo[ax]) * inv_c);
+    id = id * (uint32_t)ncell + (uint32_t)(c < 0 ? 0 : (c >= ncell ? ncell - 1 : c));
+  }
+  key[P] = id;
   val[P] = (int32_t)P;
 }
 
@@ -1314,30 +1317,32 @@ void free_tubes(TubePlan &tp) {
   tp = TubePlan();
 }
 
-int build_tubes(fpde_mesh *m, Plan &P, double kappa, hipStream_t s) {
+int build_tubes(fpde_mesh *m, Plan &P, const TubeGeom &q, double kappa, hipStream_t s) {
   TubePlan &tp = P.tubes;
   free_tubes(tp);
   if (m->ndof == 0 || P.G == 0) return FPDE_OK;
-  const int64_t n = 3 * P.G;
+  const int dim = q.dim;
+  const int64_t n = dim * P.G;
   if (n >= (int64_t(1) << 31)) return FPDE_EUNSUPPORTED;
-  // cell size from the mean element size: edge of the regular tet of mean volume
-  std::vector<double> xyz(3 * m->nv), vol(m->nt);
-  FPDE_HIP(hipMemcpyAsync(xyz.data(), m->xyz, sizeof(double) * 3 * m->nv, hipMemcpyDeviceToHost, s));
-  FPDE_HIP(hipMemcpyAsync(vol.data(), m->vol, sizeof(double) * m->nt, hipMemcpyDeviceToHost, s));
+  // cell size from the mean element size: edge of the regular simplex of mean volume
+  std::vector<double> xyz(dim * q.nv), vol(q.nt);
+  FPDE_HIP(hipMemcpyAsync(xyz.data(), q.xyz, sizeof(double) * dim * q.nv, hipMemcpyDeviceToHost, s));
+  FPDE_HIP(hipMemcpyAsync(vol.data(), q.vol, sizeof(double) * q.nt, hipMemcpyDeviceToHost, s));
   FPDE_HIP(hipStreamSynchronize(s));
   double lo[3] = {1e300, 1e300, 1e300}, hi[3] = {-1e300, -1e300, -1e300}, V = 0.0;
-  for (int64_t v = 0; v < m->nv; v++)
-    for (int d = 0; d < 3; d++) {
-      lo[d] = std::min(lo[d], xyz[3 * v + d]);
-      hi[d] = std::max(hi[d], xyz[3 * v + d]);
+  for (int64_t v = 0; v < q.nv; v++)
+    for (int d = 0; d < dim; d++) {
+      lo[d] = std::min(lo[d], xyz[dim * v + d]);
+      hi[d] = std::max(hi[d], xyz[dim * v + d]);
     }
   for (double x : vol) V += x;
-  const double h = std::cbrt(6.0 * std::sqrt(2.0) * V / (double)m->nt);
+  const double h = dim == 3 ? std::cbrt(6.0 * std::sqrt(2.0) * V / (double)q.nt)
+                            : std::sqrt(4.0 / std::sqrt(3.0) * V / (double)q.nt);
   const double c = kappa * h;
   double ext = 0.0;
-  for (int d = 0; d < 3; d++) ext = std::max(ext, hi[d] - lo[d]);
+  for (int d = 0; d < dim; d++) ext = std::max(ext, hi[d] - lo[d]);
   const int ncell = std::max(1, (int)std::ceil(ext / c) + 1);
-  if ((double)3 * ncell * ncell >= 4294967295.0) return FPDE_EUNSUPPORTED;
+  if ((double)dim * ncell * (dim == 3 ? ncell : 1) >= 4294967295.0) return FPDE_EUNSUPPORTED;
   tp.cell = c;
 
   uint32_t *key = nullptr, *key2 = nullptr;
@@ -1379,9 +1384,7 @@ int build_tubes(fpde_mesh *m, Plan &P, double kappa, hipStream_t s) {
   TRY_T(dalloc(&key2, n));
   TRY_T(dalloc(&val, n));
   TRY_T(dalloc(&tp.pair_sorted, n));
-  const double *qtab = m->rules + rule_offset(P.nq);
-  k_pair_keys<<<nblocks(n), 256, 0, s>>>(m->tet, m->xyz, qtab, P.nq, P.G, lo[0], lo[1], lo[2], 1.0 / c, ncell, key,
-                                         val);
+  k_pair_keys<<<nblocks(n), 256, 0, s>>>(q, P.nq, P.G, lo[0], lo[1], lo[2], 1.0 / c, ncell, key, val);
   size_t need = 0;
   const int end_bit = 32;
   HIP_T(hipcub::DeviceRadixSort::SortPairs(nullptr, need, key, key2, val, tp.pair_sorted, (int)n, 0, end_bit, s));
@@ -1403,7 +1406,8 @@ int build_tubes(fpde_mesh *m, Plan &P, double kappa, hipStream_t s) {
   k_tube_off<<<nblocks(n), 256, 0, s>>>(head, tid, n, tp.tube_off);
   TRY_T(dalloc(&tp.pm, n));
   TRY_T(dalloc(&tp.pw, n));
-  k_pair_meta<<<nblocks(n), 256, 0, s>>>(tp.pair_sorted, n, P.G, P.nq, P.off, qtab + 4 * P.nq, m->vol, tp.pm, tp.pw);
+  k_pair_meta<<<nblocks(n), 256, 0, s>>>(tp.pair_sorted, n, P.G, P.nq, P.off, q.rule + (dim + 1) * P.nq, q.vol, tp.pm,
+                                         tp.pw);
   dfree(key); dfree(key2); dfree(val); dfree(head); dfree(tid);
 
   // node sets

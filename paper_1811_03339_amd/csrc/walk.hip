@@ -416,10 +416,10 @@ __global__ void k_slopes(const TetRec *__restrict__ rec, int64_t nt, double4 *__
 }
 
 __global__ void k_strip_starts(const int64_t *__restrict__ soff, int64_t G, int64_t per_dir, int64_t n,
-                               int64_t *__restrict__ strip) {
+                               int64_t n_half, int64_t *__restrict__ strip) {
   const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (k > n) return;
-  strip[k] = soff[k == n ? 6 * G : (k / per_dir) * G + (k % per_dir) * kStripRays];
+  strip[k] = soff[k == n ? n_half : (k / per_dir) * G + (k % per_dir) * kStripRays];
 }
 
 __device__ __forceinline__ void wave_sync() {
@@ -708,6 +708,14 @@ void free_plan(Plan &P) {
 // 41.4 / 39.7 / 38.1 / 37.2 / 37.8 ms.
 constexpr double kTubeCell = 0.7;
 
+int plan_strips(Plan &P, const int64_t *soff, hipStream_t s) {
+  P.strips = (P.G + kStripRays - 1) / kStripRays;
+  const int64_t n = P.n_half / P.G * P.strips;
+  FPDE_TRY(dalloc(&P.strip, n + 1));
+  k_strip_starts<<<nblk(n + 1), 256, 0, s>>>(soff, P.G, P.strips, n, P.n_half, P.strip);
+  return FPDE_OK;
+}
+
 static int build_plan(fpde_mesh *m, Plan &P, int nq, int max_steps, hipStream_t s) {
   QuadRule rule;
   FPDE_TRY(quad_rule(nq, &rule));
@@ -715,7 +723,6 @@ static int build_plan(fpde_mesh *m, Plan &P, int nq, int max_steps, hipStream_t 
   P.max_steps = max_steps;
   P.G = m->nt * nq;
   P.n_half = 6 * P.G;
-  P.strips = (P.G + kStripRays - 1) / kStripRays;
   int32_t *cnt = nullptr, *len = nullptr;
   int64_t *cnt64 = nullptr, *soff = nullptr;
   void *tmp = nullptr;
@@ -731,7 +738,6 @@ static int build_plan(fpde_mesh *m, Plan &P, int nq, int max_steps, hipStream_t 
   if ((st = dalloc(&P.off, P.n_half + 1)) != FPDE_OK) return fail(st);
   if ((st = dalloc(&len, P.n_half + 1)) != FPDE_OK) return fail(st);
   if ((st = dalloc(&soff, P.n_half + 1)) != FPDE_OK) return fail(st);
-  if ((st = dalloc(&P.strip, 6 * P.strips + 1)) != FPDE_OK) return fail(st);
   if (hipMemsetAsync(cnt, 0, sizeof(int32_t) * (P.n_half + 1), s) != hipSuccess ||
       hipMemsetAsync(len, 0, sizeof(int32_t) * (P.n_half + 1), s) != hipSuccess)
     return fail(FPDE_EHIP);
@@ -756,7 +762,7 @@ static int build_plan(fpde_mesh *m, Plan &P, int nq, int max_steps, hipStream_t 
   k_i32_to_i64<<<nblk(P.n_half + 1), 256, 0, s>>>(len, P.n_half + 1, cnt64);
   if (hipcub::DeviceScan::ExclusiveSum(tmp, tb, cnt64, soff, (int)(P.n_half + 1), s) != hipSuccess)
     return fail(FPDE_EHIP);
-  k_strip_starts<<<nblk(6 * P.strips + 1), 256, 0, s>>>(soff, P.G, P.strips, 6 * P.strips, P.strip);
+  if ((st = plan_strips(P, soff, s)) != FPDE_OK) return fail(st);
   int64_t n_seg = 0;
   if (hipMemcpyAsync(&n_seg, soff + P.n_half, sizeof(int64_t), hipMemcpyDeviceToHost, s) != hipSuccess)
     return fail(FPDE_EHIP);
@@ -795,7 +801,8 @@ static int build_plan(fpde_mesh *m, Plan &P, int nq, int max_steps, hipStream_t 
         P.max_ent = std::max(P.max_ent, std::max(nl, nr));
       }
   }
-  if ((st = build_tubes(m, P, kTubeCell, s)) != FPDE_OK) return fail(st);
+  const TubeGeom q{3, m->nv, m->nt, m->xyz, m->tet, m->vol, m->rules + rule_offset(nq)};
+  if ((st = build_tubes(m, P, q, kTubeCell, s)) != FPDE_OK) return fail(st);
   invalidate_values(&P);
   return FPDE_OK;
 }
