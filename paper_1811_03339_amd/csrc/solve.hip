@@ -449,8 +449,18 @@ static int potrf_batch_g(T *A, int64_t lda, int64_t sA, int64_t n, int count, T 
   // part's columns by the part's panels, and the trailing matrix beyond the
   // group once by the whole group (KD = 64 kGroup): the trailing matrix is
   // read and written once per kGroup panels.
+  // The last columns are one group however many panels they have, with the whole
+  // triangle updated by each panel: up to there that runs in the shadow of the
+  // next diagonal block, while a trailing update takes at least the 170 us of one
+  // tile 1024 deep.  FP64, tails of 0 / 2176 / 3200 / 4608 rows: N = 3 072, one
+  // system 1.38 / 1.24 / 1.16 / 1.15 ms, six 2.33 / 2.25 / 2.33 / 2.36 ms, sixteen
+  // 4.72 / 4.69 / 5.63 / 5.63 ms; N = 4 494 2.40 / 2.25 / 2.11 / 2.08 ms; 1 331 0.60 /
+  // 0.45 ms.  One line for every count, so that a system of a batch has the bits
+  // of the same system alone.
+  constexpr int64_t kTail = 2176;
   for (int64_t k0 = 0; k0 < n; k0 += kGroup * NB) {
-    for (int sp = 0; sp < kGroup; sp++) {
+    const bool tail = kPart == kGroup && n - k0 <= kTail;
+    for (int sp = 0; sp < kGroup || tail; sp++) {
       const int64_t ks = k0 + sp * NB;
       const int64_t rest = n - ks - NB;  // rows below panel sp
       if (rest <= 0) goto factored;      // the last diagonal block is factored
@@ -458,7 +468,7 @@ static int potrf_batch_g(T *A, int64_t lda, int64_t sA, int64_t n, int count, T 
       T *Ln = Lk + NB * NB, *LnT = LinvT + (ks / NB + 1) * NB * NB;
       k_panel<T><<<dim3(nblk(rest, 64), z), 256, 0, s>>>(A, lda, n, ks, Lk, sA, sL);
       const int64_t Tn = (rest + 63) / 64;              // block rows (and columns) below panel sp
-      const int inner = kPart - 1 - sp % kPart;  // block columns of the part after panel sp
+      const int64_t inner = tail ? Tn : kPart - 1 - sp % kPart;  // block columns of the part after panel sp
       if (Tn <= inner) {
         // the rest of the matrix lies inside the part: all of it, by this panel
         k_syrk<T, NB><<<(unsigned)(Tn * (Tn + 1) / 2 * count), 256, 0, s>>>(A, lda, n, ks, Ln, LnT, m->flag,
@@ -503,13 +513,13 @@ static int potrf_batch_g(T *A, int64_t lda, int64_t sA, int64_t n, int count, T 
           const int64_t mr = n - rb;
           if (std::is_same<T, float>::value && mr >= kTiles256From) {
             // 256 x 256 tiles of eight 128 x 64 wavefronts, one per CU
-            const int64_t work = syrk256_slots(mr) * count;
+            const int64_t work = lower_tiles(mr, T256) * count;
             k_syrk256<kGroup * NB><<<(unsigned)(8 * ((work + 7) / 8)), 512, 0, st>>>(
                 (float *)A, lda, n, k0, rb, factor, (float *)Ln, (float *)LnT, m->flag, aux, sA, sL, es, n, xq, sx,
                 count, work);
           } else {
             // 128 x 128 tiles
-            const int64_t work = syrk128_slots(mr) * count;
+            const int64_t work = lower_tiles(mr, T128) * count;
             k_syrk128<T, kGroup * NB><<<(unsigned)(8 * ((work + 7) / 8)), Syrk128Shape<T>::THREADS, 0, st>>>(
                 A, lda, n, k0, rb, 0, factor, Ln, LnT, m->flag, aux, sA, sL, es, n, xq, sx, count, work);
           }

@@ -29,13 +29,6 @@ struct Syrk256Smem {
   };
 };
 
-// work items of one system: super-blocks of the lower 256 x 256 tiles of a
-// trailing matrix of m rows
-__host__ __device__ inline int64_t syrk256_slots(int64_t m) {
-  const int64_t t2 = (m + T256 - 1) / T256, s2 = (t2 + kSuper256 - 1) / kSuper256;
-  return s2 * (s2 + 1) / 2 * kSuper256 * kSuper256;
-}
-
 // acc[x][y] (wavefront tile rows 16 x.., columns 16 y..) = X_I X_J^T over KD
 // columns from the split rows xi, xj (prow, qrow of them inside the matrix),
 // 512 threads: wavefront w holds rows 128 (w >> 2).., columns 64 (w & 3)...
@@ -113,9 +106,7 @@ __device__ __forceinline__ void product_split256(const _Float16 *__restrict__ xi
 // as split rows (xs, from k_row_split) with per-row exponents (escale); with
 // factor set, the workgroup of tile (0, 0) factors the 64 x 64 diagonal
 // block at base.  Tiles in super-blocks
-// of kSuper256 x kSuper256, in row-major lower-triangular order (items above
-// the diagonal of a diagonal super-block or past the matrix end are empty),
-// nwork = nz slots work items (item 0 of every system first, then system
+// of kSuper256 x kSuper256 (super_tile), nwork = nz slots work items (item 0 of every system first, then system
 // by system its other items); the grid is 8 ceil(nwork / 8) blocks
 // dealt to the XCDs in contiguous ranges of b (xcd_deal).  An XCD runs 32
 // workgroups at once, two super-blocks, which share their block rows of X.
@@ -141,12 +132,8 @@ __global__ void __launch_bounds__(512) k_syrk256(float *__restrict__ A, int64_t 
     x = 1 + (bw - nz) % (slots - 1);
   }
   constexpr int S = kSuper256;
-  const int64_t sb = x / (S * S), si = x % (S * S);
-  int64_t P = (int64_t)((sqrt(8.0 * (double)sb + 1.0) - 1.0) * 0.5);
-  while ((P + 1) * (P + 2) / 2 <= sb) P++;
-  while (P * (P + 1) / 2 > sb) P--;
-  const int64_t I = S * P + si / S, J = S * (sb - P * (P + 1) / 2) + si % S;
-  if (J > I || base + T256 * I >= n) return;  // an empty item
+  int64_t I, J;
+  super_tile<S>(x, (n - base + T256 - 1) / T256, I, J);
   A += z * sA;
   Linv_next += z * sL;
   LinvT_next += z * sL;
