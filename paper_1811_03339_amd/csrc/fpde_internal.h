@@ -159,7 +159,7 @@ struct fpde_mesh {
   void *hcg = nullptr;            // pinned host copies of that state
   hipEvent_t cev[2] = {};
   int64_t cg_n = 0;
-  int *tsync = nullptr;           // triangular solves: per-system block flags (2 nblk) and tickets (2)
+  int *tsync = nullptr;           // triangular solves: two tickets per system
   int tsync_n = 0;                // ints allocated
   int64_t *batch_aux = nullptr;   // device, kMaxBatch: failing column per system of a batched factorization
   int *escale = nullptr;          // device: per-row exponents of the split-FP16 trailing updates
@@ -167,7 +167,6 @@ struct fpde_mesh {
   int64_t escale_n = 0, xsplit_n = 0;  // entries allocated in escale, xsplit
   double *bvec = nullptr;         // device: intermediate vectors of a batched solve
   int64_t bvec_n = 0;
-  int tsync_epoch = 0;
   fpde::StageTimer timer;
   // batched assembly: a second stream for the walks and events ordering it
   // against the caller's stream (created on first use)

@@ -656,17 +656,15 @@ int lu_solve(fpde_mesh *m, const double *LU, int64_t lda, int64_t n, const doubl
   double *Linv, *LinvT, *UinvT;
   FPDE_TRY(lu_inverses(m, n, &Linv, &LinvT, &UinvT));
   const int nblk = (int)((n + NB - 1) / NB);
-  FPDE_TRY(ensure_trsv_sync(m, nblk, s));
-  const int epoch = ++m->tsync_epoch;
-  int *fflags = m->tsync, *bflags = m->tsync + nblk, *tickets = m->tsync + 2 * nblk;
+  FPDE_TRY(ensure_trsv_sync(m));
+  int *tickets = m->tsync;
   const long t = timer_begin(m, s, FPDE_STAGE_TRSV);
   k_lu_inverses<<<nblk, 256, 0, s>>>(LU, lda, n, LinvT, UinvT);
   if (u != b) k_copy_f64<<<blocks_of(n), 256, 0, s>>>(b, u, n);
-  FPDE_TRY(zero_ints(tickets, 2, s));
-  k_trsv_rows<double, false><<<nblk, 256, 0, s>>>(LU, lda, n, nblk, LinvT, u, xs, fflags, tickets, epoch, m->flag,
-                                                  BatchStrides{});
-  k_trsv_rows<double, true><<<nblk, 256, 0, s>>>(LU, lda, n, nblk, UinvT, xs, u, bflags, tickets + 1, epoch,
-                                                 m->flag, BatchStrides{});
+  FPDE_TRY(trsv_begin(tickets, xs, 0, n, 1, s));
+  k_trsv_rows<double, false><<<nblk, 256, 0, s>>>(LU, lda, n, nblk, LinvT, u, xs, tickets, m->flag, BatchStrides{});
+  k_trsv_rows<double, true><<<nblk, 256, 0, s>>>(LU, lda, n, nblk, UinvT, xs, u, tickets + 1, m->flag,
+                                                 BatchStrides{});
   timer_end(m, FPDE_STAGE_TRSV, t, s);
   FPDE_HIP(hipGetLastError());
   return FPDE_OK;

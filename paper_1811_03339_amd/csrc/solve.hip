@@ -12,7 +12,7 @@
 //           64 x 64 output tile.
 // Triangular solves use the stored inv(L_kk) and take one launch per
 // direction: block rows are handed out in dependency order by an atomic
-// ticket and wait for the blocks they need through per-block flags.  The same kernels are
+// ticket and wait for the entries they need (kUnset until they are stored).  The same kernels are
 // instantiated for FP32 storage, which the mixed-precision path factors and
 // then refines against FP64 residuals b - K u computed matrix-free from the
 // FP64 derivative vectors.
@@ -199,21 +199,20 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) k
 // workgroup only ever waits for block rows whose tickets were taken before
 // its own, by workgroups that are already running, and the first ticket
 // waits for nothing -- no deadlock whatever the residency.  Solved blocks are
-// published with a release store of the call's epoch into a per-block flag.
-// Every wave polls the flags it needs by itself (acquire loads, up to 64
-// flags per poll), so the loop over earlier blocks has no barrier; a poll
-// that exceeds kSpinLimit marks the call failed and every wave still exits.
+// published entry by entry over kUnset.  Every wave polls the entries it needs
+// by itself, so the loop over earlier blocks has no barrier; a poll that exceeds
+// kSpinLimit marks the call failed and every wave still exits.
 // backward: u_b = inv(L_bb)^T (x_b - sum_{c>b} L_cb^T u_c).  Lane = row of
 // the result block (column r0 + lane of L); wave w owns rows 16w..16w+15 of
 // block c.
 template <class T>
 __global__ void __launch_bounds__(256) k_trsv_bwd(const T *__restrict__ L, int64_t lda, int64_t n, int nblk,
                                                   const T *__restrict__ Linv, const double *__restrict__ x,
-                                                  double *__restrict__ u, int *flags, int *ticket, int epoch,
-                                                  int32_t *err, BatchStrides bs) {
+                                                  double *__restrict__ u, int *ticket, int32_t *err,
+                                                  BatchStrides bs) {
   __shared__ int sb, ok;
   __shared__ double rhs[NB];
-  __shared__ double red[4][NB];
+  __shared__ double red[4][NB], red2[4][NB];
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   {
     const int64_t z = blockIdx.y;
@@ -221,7 +220,6 @@ __global__ void __launch_bounds__(256) k_trsv_bwd(const T *__restrict__ L, int64
     Linv += z * bs.l;
     x += z * bs.x;
     u += z * bs.v;
-    flags += z * bs.f;
     ticket += z * bs.t;
   }
   if (tid == 0) {
@@ -240,13 +238,18 @@ __global__ void __launch_bounds__(256) k_trsv_bwd(const T *__restrict__ L, int64
   // only the last block can be partial, and it has no blocks below it, so
   // every block c > b read here has nbc rows and columns r0 + lane < n
   auto rows_of = [&](int c) { return (int)((n - (int64_t)c * NB) < NB ? (n - (int64_t)c * NB) : NB); };
-  double part = 0.0;
+  const double xv = tid < nb ? x[r0 + tid] : 0.0;
+  const int jl = 16 * w + (lane & 15);
+  // this lane's entry of block c (clamped into the matrix)
+  auto entry = [&](int c) { return (int64_t)c * NB + (jl < rows_of(c) ? jl : rows_of(c) - 1); };
+  double part = 0.0, un = 0.0;
   T cur[16];
 #pragma unroll
   for (int q = 0; q < 16; q++) cur[q] = (T)0;
   if (nblk - 1 > b) {  // the last block row lies below this block
     const int c = nblk - 1;
     const int nbc = rows_of(c);
+    un = ld_dev(&u[entry(c)]);
 #pragma unroll
     for (int q = 0; q < 16; q++) {
       const int j = 16 * w + q;
@@ -254,22 +257,16 @@ __global__ void __launch_bounds__(256) k_trsv_bwd(const T *__restrict__ L, int64
     }
   }
   bool good = true;
-  int ready = nblk;  // blocks [ready, nblk) known to be published
   for (int c = nblk - 1; c > b; c--) {
-    if (c < ready) {
-      const int k = poll_run(flags, c, -1, (c - b) < 64 ? (c - b) : 64, epoch);
-      if (k == 0) {
-        good = false;
-        break;
-      }
-      ready = c - k + 1;
+    double ub = un;
+    if (!wait_set(&u[entry(c)], true, ub)) {
+      good = false;
+      break;
     }
-    const int64_t c0 = (int64_t)c * NB;
-    const int nbc = rows_of(c);
-    const int jl = 16 * w + (lane & 15);
-    const double ub = jl < nbc ? ld_dev(&u[c0 + jl]) : 0.0;
+    if (jl >= rows_of(c)) ub = 0.0;
     const int cn = (c - 1 > b) ? c - 1 : c;
     const int nbn = rows_of(cn);
+    un = ld_dev(&u[entry(cn)]);
     T nxt[16];
 #pragma unroll
     for (int q = 0; q < 16; q++) {
@@ -285,17 +282,18 @@ __global__ void __launch_bounds__(256) k_trsv_bwd(const T *__restrict__ L, int64
   if (!good && lane == 0) ok = 0;
   red[w][lane] = part;
   __syncthreads();
-  if (tid < NB) rhs[tid] = (tid < nb) ? x[r0 + tid] - ((red[0][tid] + red[1][tid]) + (red[2][tid] + red[3][tid])) : 0.0;
+  if (tid < NB) rhs[tid] = (tid < nb) ? xv - ((red[0][tid] + red[1][tid]) + (red[2][tid] + red[3][tid])) : 0.0;
   __syncthreads();
-  double s = 0.0;
+  double s = 0.0, s2 = 0.0;
 #pragma unroll
-  for (int q = 0; q < 16; q++) s = fma(li[q], rhs[16 * w + q], s);
-  __syncthreads();  // red is reused
-  red[w][lane] = s;
+  for (int q = 0; q < 8; q++) {
+    s = fma(li[q], rhs[16 * w + q], s);
+    s2 = fma(li[q + 8], rhs[16 * w + q + 8], s2);
+  }
+  red2[w][lane] = s + s2;
   __syncthreads();
-  // written by wavefront 0 and published (as in the forward solve)
-  if (tid < nb) st_dev(&u[r0 + tid], (red[0][tid] + red[1][tid]) + (red[2][tid] + red[3][tid]));
-  publish_block(flags, b, epoch);
+  // written (published) by wavefront 0, as in the forward solve
+  if (tid < nb) st_dev(&u[r0 + tid], (red2[0][tid] + red2[1][tid]) + (red2[2][tid] + red2[3][tid]));
   if (tid == 0 && !ok) set_flag(err, FPDE_EHIP);
 }
 
@@ -311,9 +309,10 @@ __global__ void k_copy_strided(const double *__restrict__ b, double *__restrict_
   if (k < n) u[o + k] = b[o + k];
 }
 
-__global__ void k_zero_i32(int *p, int n) {
-  const int k = blockIdx.x * blockDim.x + threadIdx.x;
-  if (k < n) p[k] = 0;
+__global__ void k_trsv_begin(int *tickets, int nt, double *__restrict__ x, int64_t n, int64_t sx) {
+  const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (k < n) x[(int64_t)blockIdx.y * sx + k] = unset_value();
+  if (blockIdx.y == 0 && k < nt) tickets[k] = 0;
 }
 
 __global__ void k_axpy_copy(double *__restrict__ u, const double *__restrict__ c, int64_t n) {
@@ -577,22 +576,20 @@ static int potrf(T *A, int64_t lda, int64_t n, fpde_mesh *m, hipStream_t s) {
 // y (n) holds the right-hand side on entry and the solution on exit;
 // x (n) is scratch.  Two launches (forward, backward), each preceded by a
 // reset of its ticket counter.
-int zero_ints(int *p, int n, hipStream_t s) {
+int trsv_begin(int *tickets, double *x, int64_t sx, int64_t n, int count, hipStream_t s) {
   if (n <= 0) return FPDE_OK;
-  k_zero_i32<<<(n + 255) / 256, 256, 0, s>>>(p, n);
+  const int64_t k = n > 2 * count ? n : 2 * count;
+  k_trsv_begin<<<dim3(nblk(k), (unsigned)count), 256, 0, s>>>(tickets, 2 * count, x, n, sx);
   FPDE_HIP(hipGetLastError());
   return FPDE_OK;
 }
 
-int ensure_trsv_sync(fpde_mesh *m, int nblk, hipStream_t s, int count) {
-  const int cnt = count * (2 * nblk + 2);
-  if (m->tsync_n < cnt) {
+int ensure_trsv_sync(fpde_mesh *m, int count) {
+  if (m->tsync_n < 2 * count) {
     dfree(m->tsync);
     m->tsync_n = 0;
-    FPDE_TRY(dalloc(&m->tsync, (size_t)cnt));
-    k_zero_i32<<<(cnt + 255) / 256, 256, 0, s>>>(m->tsync, cnt);
-    m->tsync_n = cnt;
-    m->tsync_epoch = 0;  // every flag is below the next epoch
+    FPDE_TRY(dalloc(&m->tsync, (size_t)(2 * count)));
+    m->tsync_n = 2 * count;
   }
   return FPDE_OK;
 }
@@ -600,27 +597,23 @@ int ensure_trsv_sync(fpde_mesh *m, int nblk, hipStream_t s, int count) {
 // Forward and backward solves of `count` systems (strided batch, grid.y =
 // system): y + z sv holds system z's right-hand side on entry and its
 // solution on exit; x + z sx is scratch.
-// The launches of trsv_batch with its flags and tickets given: tsync holds
-// count x 2 nblk flags (below `epoch` on entry) then 2 count tickets.
+// The launches of trsv_batch with its 2 count tickets given.
 template <class T>
 static int trsv_batch_sync(const T *L, int64_t lda, int64_t sA, int64_t n, int count, const T *Linv, int64_t sL,
-                           double *y, int64_t sv, double *x, int64_t sx, int *tsync, int epoch, fpde_mesh *m,
-                           hipStream_t s) {
+                           double *y, int64_t sv, double *x, int64_t sx, int *tickets, fpde_mesh *m, hipStream_t s) {
   const int nblk = (int)((n + NB - 1) / NB);
-  int *fflags = tsync, *bflags = tsync + nblk, *tickets = tsync + (int64_t)count * 2 * nblk;
   const T *LinvT = Linv + (size_t)nblk * NB * NB;
   BatchStrides bs;
   bs.a = sA;
   bs.l = sL;
   bs.v = sv;
   bs.x = sx;
-  bs.f = 2 * nblk;
   bs.t = 2;
   const dim3 grid((unsigned)nblk, (unsigned)count);
   const long t = timer_begin(m, s, FPDE_STAGE_TRSV);
-  k_zero_i32<<<1, 64, 0, s>>>(tickets, 2 * count);
-  k_trsv_rows<T, false><<<grid, 256, 0, s>>>(L, lda, n, nblk, LinvT, y, x, fflags, tickets, epoch, m->flag, bs);
-  k_trsv_bwd<T><<<grid, 256, 0, s>>>(L, lda, n, nblk, Linv, x, y, bflags, tickets + 1, epoch, m->flag, bs);
+  FPDE_TRY(trsv_begin(tickets, x, sx, n, count, s));
+  k_trsv_rows<T, false><<<grid, 256, 0, s>>>(L, lda, n, nblk, LinvT, y, x, tickets, m->flag, bs);
+  k_trsv_bwd<T><<<grid, 256, 0, s>>>(L, lda, n, nblk, Linv, x, y, tickets + 1, m->flag, bs);
   timer_end(m, FPDE_STAGE_TRSV, t, s, count);
   FPDE_HIP(hipGetLastError());
   return FPDE_OK;
@@ -629,10 +622,8 @@ static int trsv_batch_sync(const T *L, int64_t lda, int64_t sA, int64_t n, int c
 template <class T>
 static int trsv_batch(const T *L, int64_t lda, int64_t sA, int64_t n, int count, const T *Linv, int64_t sL,
                       double *y, int64_t sv, double *x, int64_t sx, fpde_mesh *m, hipStream_t s) {
-  const int nblk = (int)((n + NB - 1) / NB);
-  FPDE_TRY(ensure_trsv_sync(m, nblk, s, count));
-  const int epoch = ++m->tsync_epoch;
-  return trsv_batch_sync<T>(L, lda, sA, n, count, Linv, sL, y, sv, x, sx, m->tsync, epoch, m, s);
+  FPDE_TRY(ensure_trsv_sync(m, count));
+  return trsv_batch_sync<T>(L, lda, sA, n, count, Linv, sL, y, sv, x, sx, m->tsync, m, s);
 }
 
 template <class T>
@@ -747,7 +738,7 @@ int dense_spd_solve(fpde_mesh *ws, double *A, int64_t lda, int64_t n, const doub
 // ---- Dense FP64 solve whose scratch is a static device array ----
 //
 // For callers that cannot allocate: the diagonal-block inverses (and their
-// transposes), the triangular solves' flags and tickets and the intermediate
+// transposes), the triangular solves' tickets and the intermediate
 // vector of fpde_solve's FP64 path live in `scratch`, one copy per device
 // (the library's code object is loaded on every device it runs on), sized
 // for kNoAllocMaxN unknowns.  Host code reaches the array through the device
@@ -757,7 +748,7 @@ constexpr int64_t kNoAllocMaxN = 8192;
 constexpr int64_t kNoAllocBlk = (kNoAllocMaxN + NB - 1) / NB;
 constexpr size_t kNoAllocLinv = 2 * (size_t)kNoAllocBlk * NB * NB;  // doubles
 constexpr size_t kNoAllocVec = (size_t)kNoAllocMaxN;                // doubles
-constexpr size_t kNoAllocInts = 2 * (size_t)kNoAllocBlk + 2;        // flags, tickets
+constexpr size_t kNoAllocInts = 2;                                  // tickets
 constexpr size_t kNoAllocBytes = (kNoAllocLinv + kNoAllocVec) * sizeof(double) + kNoAllocInts * sizeof(int);
 static __device__ __align__(256) unsigned char scratch[kNoAllocBytes];
 
@@ -798,15 +789,11 @@ extern "C" int fpde_solve_noalloc(fpde_mesh *m, double *A, int64_t lda, const do
   FPDE_TRY(scratch_address(dev, &base));
   double *lv = (double *)base;
   double *xs = lv + kNoAllocLinv;
-  int *tsync = (int *)(xs + kNoAllocVec);
-  const int nblk = (int)((n + NB - 1) / NB);
+  int *tickets = (int *)(xs + kNoAllocVec);
   hipStream_t s = S(stream);
-  // the flags and tickets keep the previous call's values: cleared by a
-  // kernel (no memset node if the caller captures a graph)
-  FPDE_TRY(zero_ints(tsync, 2 * nblk + 2, s));
   FPDE_TRY(potrf_batch<double>(A, lda, 0, n, 1, lv, 0, m->flag_aux, m, s));
   if (u != b) FPDE_HIP(hipMemcpyAsync(u, b, sizeof(double) * n, hipMemcpyDeviceToDevice, s));
-  FPDE_TRY(trsv_batch_sync<double>(A, lda, 0, n, 1, lv, 0, u, 0, xs, 0, tsync, 1, m, s));
+  FPDE_TRY(trsv_batch_sync<double>(A, lda, 0, n, 1, lv, 0, u, 0, xs, 0, tickets, m, s));
   int64_t col = -1;
   int f = take_flag(m, s, &col);
   if (f == FPDE_ENOTSPD && failed_pivot) *failed_pivot = col;
