@@ -401,8 +401,10 @@ __global__ void __launch_bounds__(256) k_trsv_rows(const T *__restrict__ A, int6
 int ensure_linv(fpde_mesh *m, int64_t n, size_t elem, int sets, void **out);
 // Two tickets per system for the solves.
 int ensure_trsv_sync(fpde_mesh *m, int count = 1);
-// Before the forward solve: the tickets are zero and x + z sx (z < count) is
-// unset (a kernel: no memset node when a caller captures a graph).
-int trsv_begin(int *tickets, double *x, int64_t sx, int64_t n, int count, hipStream_t s);
+// Before the forward solve: the tickets are zero, x + z sx (z < count) is unset
+// and, b not null, u + z sv = b + z sv (one kernel: no memset node when a caller
+// captures a graph).
+int trsv_begin(int *tickets, double *x, int64_t sx, int64_t n, int count, const double *b, double *u, int64_t sv,
+               hipStream_t s);
 
 }  // namespace fpde

@@ -129,6 +129,10 @@ struct StageTimer {
 
 }  // namespace fpde
 
+namespace fpde {
+constexpr int kResParts = 64;  // workgroups of a residual check
+}
+
 struct fpde_mesh {
   int device = 0;
   int64_t nv = 0, nt = 0, ndof = 0, nbf = 0;
@@ -147,7 +151,7 @@ struct fpde_mesh {
   int32_t *flag = nullptr;        // device status word (0 = ok)
   int64_t *flag_aux = nullptr;    // device: failing column / ray
   int64_t *flag_blk = nullptr;    // device block holding both: {flag (low word), flag_aux}
-  int64_t *hflag = nullptr;       // pinned host copy of flag_blk (one transfer per status check)
+  int64_t *hflag = nullptr;       // pinned: copy of flag_blk (2), sums of a residual check (2 kResParts doubles)
   fpde::Plan plan[2];             // rules with 4 and 11 points
   // solve scratch
   double *vec = nullptr;          // 4 ndof FP64

@@ -589,11 +589,6 @@ k_lu_update(double *__restrict__ A, int64_t lda, int64_t n, int64_t k0, int64_t 
 
 inline unsigned blocks_of(int64_t n, int b = 256) { return (unsigned)((n + b - 1) / b); }
 
-__global__ void k_copy_f64(const double *__restrict__ a, double *__restrict__ b, int64_t n) {
-  const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (k < n) b[k] = a[k];
-}
-
 }  // namespace
 
 // the three inverse sets of the LU blocks inside the mesh's buffer
@@ -660,8 +655,7 @@ int lu_solve(fpde_mesh *m, const double *LU, int64_t lda, int64_t n, const doubl
   int *tickets = m->tsync;
   const long t = timer_begin(m, s, FPDE_STAGE_TRSV);
   k_lu_inverses<<<nblk, 256, 0, s>>>(LU, lda, n, LinvT, UinvT);
-  if (u != b) k_copy_f64<<<blocks_of(n), 256, 0, s>>>(b, u, n);
-  FPDE_TRY(trsv_begin(tickets, xs, 0, n, 1, s));
+  FPDE_TRY(trsv_begin(tickets, xs, 0, n, 1, u != b ? b : nullptr, u, 0, s));
   k_trsv_rows<double, false><<<nblk, 256, 0, s>>>(LU, lda, n, nblk, LinvT, u, xs, tickets, m->flag, BatchStrides{});
   k_trsv_rows<double, true><<<nblk, 256, 0, s>>>(LU, lda, n, nblk, UinvT, xs, u, tickets + 1, m->flag,
                                                  BatchStrides{});

@@ -103,7 +103,7 @@ static int alloc_flags(fpde_mesh *m) {
   FPDE_TRY(dalloc(&m->flag_blk, 2));
   m->flag = reinterpret_cast<int32_t *>(m->flag_blk);
   m->flag_aux = m->flag_blk + 1;
-  if (hipHostMalloc((void **)&m->hflag, 2 * sizeof(int64_t), hipHostMallocDefault) != hipSuccess) {
+  if (hipHostMalloc((void **)&m->hflag, (2 + 2 * kResParts) * sizeof(int64_t), hipHostMallocDefault) != hipSuccess) {
     m->hflag = nullptr;
     return FPDE_ENOMEM;
   }

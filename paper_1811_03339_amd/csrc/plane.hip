@@ -566,8 +566,8 @@ struct Load2Args {
 
 __device__ __forceinline__ double mms_phi2(double s) { return s * s * (1.0 - s) * (1.0 - s); }
 __device__ __forceinline__ double mms_Phi2(double s, const Load2Args &a) {
-  return 2.0 * pow(s, 2.0 - a.alpha) * a.rg3 - 12.0 * pow(s, 3.0 - a.alpha) * a.rg4 +
-         24.0 * pow(s, 4.0 - a.alpha) * a.rg5;
+  const double p2 = pow(s, 2.0 - a.alpha), p3 = s * p2;
+  return 2.0 * p2 * a.rg3 - 12.0 * p3 * a.rg4 + 24.0 * (s * p3) * a.rg5;
 }
 
 __global__ void k2_load(Load2Args a, double *__restrict__ b) {

@@ -302,16 +302,13 @@ __global__ void k_fill_i64(int64_t *p, int n, int64_t v) {
   if (k < n) p[k] = v;
 }
 
-// u + z sv = b + z sv for the systems z = blockIdx.y of a batch
-__global__ void k_copy_strided(const double *__restrict__ b, double *__restrict__ u, int64_t n, int64_t sv) {
+__global__ void k_trsv_begin(int *tickets, int nt, double *__restrict__ x, int64_t n, int64_t sx,
+                             const double *__restrict__ b, double *__restrict__ u, int64_t sv) {
   const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int64_t o = (int64_t)blockIdx.y * sv;
-  if (k < n) u[o + k] = b[o + k];
-}
-
-__global__ void k_trsv_begin(int *tickets, int nt, double *__restrict__ x, int64_t n, int64_t sx) {
-  const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (k < n) x[(int64_t)blockIdx.y * sx + k] = unset_value();
+  if (k < n) {
+    x[(int64_t)blockIdx.y * sx + k] = unset_value();
+    if (b) u[(int64_t)blockIdx.y * sv + k] = b[(int64_t)blockIdx.y * sv + k];
+  }
   if (blockIdx.y == 0 && k < nt) tickets[k] = 0;
 }
 
@@ -319,23 +316,28 @@ __global__ void k_axpy_copy(double *__restrict__ u, const double *__restrict__ c
   const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (k < n) u[k] += c[k];
 }
-__global__ void k_sub(const double *__restrict__ b, const double *__restrict__ y, double *__restrict__ r, int64_t n) {
-  const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (k < n) r[k] = b[k] - y[k];
-}
-// sum of squares, per-block partials
-__global__ void __launch_bounds__(256) k_sumsq(const double *__restrict__ x, int64_t n, double *__restrict__ part) {
-  __shared__ double red[256];
-  double s = 0.0;
-  for (int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; k < n; k += (int64_t)gridDim.x * blockDim.x)
-    s += x[k] * x[k];
-  red[threadIdx.x] = s;
+// r = b - y (r may be null) and per-workgroup sums of r^2 and b^2
+__global__ void __launch_bounds__(256) k_residual(const double *__restrict__ b, const double *__restrict__ y,
+                                                  double *__restrict__ r, int64_t n, double *__restrict__ part) {
+  __shared__ double red[2][256];
+  double s = 0.0, t = 0.0;
+  for (int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; k < n; k += (int64_t)gridDim.x * blockDim.x) {
+    const double bk = b[k], d = bk - y[k];
+    if (r) r[k] = d;
+    s += d * d;
+    t += bk * bk;
+  }
+  red[0][threadIdx.x] = s;
+  red[1][threadIdx.x] = t;
   __syncthreads();
   for (int w = 128; w > 0; w >>= 1) {
-    if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
+    if ((int)threadIdx.x < w) {
+      red[0][threadIdx.x] += red[0][threadIdx.x + w];
+      red[1][threadIdx.x] += red[1][threadIdx.x + w];
+    }
     __syncthreads();
   }
-  if (threadIdx.x == 0) part[blockIdx.x] = red[0];
+  if (threadIdx.x < 2) part[2 * blockIdx.x + threadIdx.x] = red[threadIdx.x][0];
 }
 
 static inline unsigned nblk(int64_t n, int b = 256) { return (unsigned)((n + b - 1) / b); }
@@ -576,10 +578,11 @@ static int potrf(T *A, int64_t lda, int64_t n, fpde_mesh *m, hipStream_t s) {
 // y (n) holds the right-hand side on entry and the solution on exit;
 // x (n) is scratch.  Two launches (forward, backward), each preceded by a
 // reset of its ticket counter.
-int trsv_begin(int *tickets, double *x, int64_t sx, int64_t n, int count, hipStream_t s) {
+int trsv_begin(int *tickets, double *x, int64_t sx, int64_t n, int count, const double *b, double *u, int64_t sv,
+               hipStream_t s) {
   if (n <= 0) return FPDE_OK;
   const int64_t k = n > 2 * count ? n : 2 * count;
-  k_trsv_begin<<<dim3(nblk(k), (unsigned)count), 256, 0, s>>>(tickets, 2 * count, x, n, sx);
+  k_trsv_begin<<<dim3(nblk(k), (unsigned)count), 256, 0, s>>>(tickets, 2 * count, x, n, sx, b, u, sv);
   FPDE_HIP(hipGetLastError());
   return FPDE_OK;
 }
@@ -595,12 +598,13 @@ int ensure_trsv_sync(fpde_mesh *m, int count) {
 }
 
 // Forward and backward solves of `count` systems (strided batch, grid.y =
-// system): y + z sv holds system z's right-hand side on entry and its
-// solution on exit; x + z sx is scratch.
+// system): b + z sv (null: y + z sv) holds system z's right-hand side, y + z sv
+// its solution on exit; x + z sx is scratch.
 // The launches of trsv_batch with its 2 count tickets given.
 template <class T>
 static int trsv_batch_sync(const T *L, int64_t lda, int64_t sA, int64_t n, int count, const T *Linv, int64_t sL,
-                           double *y, int64_t sv, double *x, int64_t sx, int *tickets, fpde_mesh *m, hipStream_t s) {
+                           const double *b, double *y, int64_t sv, double *x, int64_t sx, int *tickets, fpde_mesh *m,
+                           hipStream_t s) {
   const int nblk = (int)((n + NB - 1) / NB);
   const T *LinvT = Linv + (size_t)nblk * NB * NB;
   BatchStrides bs;
@@ -611,7 +615,7 @@ static int trsv_batch_sync(const T *L, int64_t lda, int64_t sA, int64_t n, int c
   bs.t = 2;
   const dim3 grid((unsigned)nblk, (unsigned)count);
   const long t = timer_begin(m, s, FPDE_STAGE_TRSV);
-  FPDE_TRY(trsv_begin(tickets, x, sx, n, count, s));
+  FPDE_TRY(trsv_begin(tickets, x, sx, n, count, b, y, sv, s));
   k_trsv_rows<T, false><<<grid, 256, 0, s>>>(L, lda, n, nblk, LinvT, y, x, tickets, m->flag, bs);
   k_trsv_bwd<T><<<grid, 256, 0, s>>>(L, lda, n, nblk, Linv, x, y, tickets + 1, m->flag, bs);
   timer_end(m, FPDE_STAGE_TRSV, t, s, count);
@@ -621,15 +625,15 @@ static int trsv_batch_sync(const T *L, int64_t lda, int64_t sA, int64_t n, int c
 
 template <class T>
 static int trsv_batch(const T *L, int64_t lda, int64_t sA, int64_t n, int count, const T *Linv, int64_t sL,
-                      double *y, int64_t sv, double *x, int64_t sx, fpde_mesh *m, hipStream_t s) {
+                      const double *b, double *y, int64_t sv, double *x, int64_t sx, fpde_mesh *m, hipStream_t s) {
   FPDE_TRY(ensure_trsv_sync(m, count));
-  return trsv_batch_sync<T>(L, lda, sA, n, count, Linv, sL, y, sv, x, sx, m->tsync, m, s);
+  return trsv_batch_sync<T>(L, lda, sA, n, count, Linv, sL, b, y, sv, x, sx, m->tsync, m, s);
 }
 
 template <class T>
-static int trsv_pair(const T *L, int64_t lda, int64_t n, const T *Linv, double *y, double *x, fpde_mesh *m,
-                     hipStream_t s) {
-  return trsv_batch<T>(L, lda, 0, n, 1, Linv, 0, y, 0, x, 0, m, s);
+static int trsv_pair(const T *L, int64_t lda, int64_t n, const T *Linv, const double *b, double *y, double *x,
+                     fpde_mesh *m, hipStream_t s) {
+  return trsv_batch<T>(L, lda, 0, n, 1, Linv, 0, b, y, 0, x, 0, m, s);
 }
 
 static int ensure_vec(fpde_mesh *m) {
@@ -641,15 +645,23 @@ static int ensure_vec(fpde_mesh *m) {
   return FPDE_OK;
 }
 
-static int norm2(fpde_mesh *m, const double *x, double *out, hipStream_t s) {
-  const unsigned nb = 256;
-  k_sumsq<<<nb, 256, 0, s>>>(x, m->ndof, m->red);
-  double h[256];
-  FPDE_HIP(hipMemcpyAsync(h, m->red, sizeof(h), hipMemcpyDeviceToHost, s));
+// r = b - y (r may be null) and the norms of it and of b, in one kernel and one
+// transfer to pinned memory.  (As a subtraction and two norms, each read back by
+// itself, a solve of a few unknowns spent two of its four round trips here.)
+static int residual(fpde_mesh *m, const double *b, const double *y, double *r, double *rn, double *bn,
+                    hipStream_t s) {
+  static_assert(2 * kResParts <= 1024, "the sums' buffer");
+  k_residual<<<kResParts, 256, 0, s>>>(b, y, r, m->ndof, m->red);
+  double *h = (double *)(m->hflag + 2);
+  FPDE_HIP(hipMemcpyAsync(h, m->red, 2 * kResParts * sizeof(double), hipMemcpyDeviceToHost, s));
   FPDE_HIP(hipStreamSynchronize(s));
-  double t = 0.0;
-  for (unsigned k = 0; k < nb; k++) t += h[k];
-  *out = std::sqrt(t);
+  double rr = 0.0, bb = 0.0;
+  for (int k = 0; k < kResParts; k++) {
+    rr += h[2 * k];
+    bb += h[2 * k + 1];
+  }
+  *rn = std::sqrt(rr);
+  *bn = std::sqrt(bb);
   return FPDE_OK;
 }
 
@@ -666,17 +678,14 @@ static int solve_with_factor(fpde_mesh *m, const fpde_params *p, const void *L, 
   FPDE_TRY(ensure_vec(m));
   double *y = m->vec, *r = m->vec + n, *bb = m->vec + 2 * n, *xs = m->vec + 3 * n;
   if (p->precision == FPDE_FP64) {
-    if (u != b) FPDE_HIP(hipMemcpyAsync(u, b, sizeof(double) * n, hipMemcpyDeviceToDevice, s));
-    FPDE_TRY(trsv_pair<double>((const double *)L, lda, n, (const double *)Linv, u, xs, m, s));
+    FPDE_TRY(trsv_pair<double>((const double *)L, lda, n, (const double *)Linv, u != b ? b : nullptr, u, xs, m, s));
     if (info) {
       Plan *P = nullptr;
       FPDE_TRY(plan_for(m, p->quad_points, p->max_steps, s, &P));
       FPDE_TRY(ensure_values(m, P, p->alpha, s));
       FPDE_TRY(apply_matfree(m, P, p, u, y, s));
-      k_sub<<<nblk(n), 256, 0, s>>>(b, y, r, n);
       double rn = 0, bn = 0;
-      FPDE_TRY(norm2(m, r, &rn, s));
-      FPDE_TRY(norm2(m, b, &bn, s));
+      FPDE_TRY(residual(m, b, y, nullptr, &rn, &bn, s));
       info->final_rel_residual = bn > 0 ? rn / bn : rn;
     }
     return FPDE_OK;
@@ -685,23 +694,19 @@ static int solve_with_factor(fpde_mesh *m, const fpde_params *p, const void *L, 
   const double tol = p->ir_tol > 0 ? p->ir_tol : 1e-8;
   const int maxit = p->ir_max_iter > 0 ? p->ir_max_iter : 30;
   FPDE_HIP(hipMemcpyAsync(bb, b, sizeof(double) * n, hipMemcpyDeviceToDevice, s));
-  FPDE_HIP(hipMemcpyAsync(u, bb, sizeof(double) * n, hipMemcpyDeviceToDevice, s));
-  FPDE_TRY(trsv_pair<float>((const float *)L, lda, n, (const float *)Linv, u, xs, m, s));
+  FPDE_TRY(trsv_pair<float>((const float *)L, lda, n, (const float *)Linv, bb, u, xs, m, s));
   Plan *P = nullptr;
   FPDE_TRY(plan_for(m, p->quad_points, p->max_steps, s, &P));
   FPDE_TRY(ensure_values(m, P, p->alpha, s));
-  double bn = 0;
-  FPDE_TRY(norm2(m, bb, &bn, s));
   double rel = 0;
   int it = 0;
   for (;;) {
     FPDE_TRY(apply_matfree(m, P, p, u, y, s));
-    k_sub<<<nblk(n), 256, 0, s>>>(bb, y, r, n);
-    double rn = 0;
-    FPDE_TRY(norm2(m, r, &rn, s));
+    double rn = 0, bn = 0;
+    FPDE_TRY(residual(m, bb, y, r, &rn, &bn, s));
     rel = bn > 0 ? rn / bn : rn;
     if (rel <= tol || it >= maxit) break;
-    FPDE_TRY(trsv_pair<float>((const float *)L, lda, n, (const float *)Linv, r, xs, m, s));
+    FPDE_TRY(trsv_pair<float>((const float *)L, lda, n, (const float *)Linv, nullptr, r, xs, m, s));
     k_axpy_copy<<<nblk(n), 256, 0, s>>>(u, r, n);
     it++;
   }
@@ -729,8 +734,7 @@ int dense_spd_solve(fpde_mesh *ws, double *A, int64_t lda, int64_t n, const doub
     return f < 0 ? f : FPDE_EHIP;
   }
   FPDE_TRY(ensure_vec(ws));
-  if (u != b) FPDE_HIP(hipMemcpyAsync(u, b, sizeof(double) * n, hipMemcpyDeviceToDevice, s));
-  FPDE_TRY(trsv_pair<double>(A, lda, n, (const double *)ws->linv, u, ws->vec + 3 * n, ws, s));
+  FPDE_TRY(trsv_pair<double>(A, lda, n, (const double *)ws->linv, u != b ? b : nullptr, u, ws->vec + 3 * n, ws, s));
   f = take_flag(ws, s);
   return f < 0 ? f : (f > 0 ? FPDE_EHIP : FPDE_OK);
 }
@@ -792,8 +796,7 @@ extern "C" int fpde_solve_noalloc(fpde_mesh *m, double *A, int64_t lda, const do
   int *tickets = (int *)(xs + kNoAllocVec);
   hipStream_t s = S(stream);
   FPDE_TRY(potrf_batch<double>(A, lda, 0, n, 1, lv, 0, m->flag_aux, m, s));
-  if (u != b) FPDE_HIP(hipMemcpyAsync(u, b, sizeof(double) * n, hipMemcpyDeviceToDevice, s));
-  FPDE_TRY(trsv_batch_sync<double>(A, lda, 0, n, 1, lv, 0, u, 0, xs, 0, tickets, m, s));
+  FPDE_TRY(trsv_batch_sync<double>(A, lda, 0, n, 1, lv, 0, u != b ? b : nullptr, u, 0, xs, 0, tickets, m, s));
   int64_t col = -1;
   int f = take_flag(m, s, &col);
   if (f == FPDE_ENOTSPD && failed_pivot) *failed_pivot = col;
@@ -867,13 +870,10 @@ extern "C" int fpde_solve_batch(fpde_mesh *m, int count, double *A, int64_t lda,
   k_fill_i64<<<1, 64, 0, s>>>(m->batch_aux, count, -1);
   FPDE_TRY(potrf_batch<double>(A, lda, sA, n, count, (double *)lv, sL, m->batch_aux, m, s));
   // the solves follow at once: they finish whatever the factor holds (every
-  // block flag is published, every wait bounded), and one status check at
-  // the end covers both; a failed factorization reports no solution
-  if (u != b) {
-    k_copy_strided<<<dim3(nblk(n), (unsigned)count), 256, 0, s>>>(b, u, n, sv);
-    FPDE_HIP(hipGetLastError());
-  }
-  FPDE_TRY(trsv_batch<double>(A, lda, sA, n, count, (const double *)lv, sL, u, sv, m->bvec, n, m, s));
+  // entry is published, every wait bounded), and one status check at the end
+  // covers both; a failed factorization reports no solution
+  FPDE_TRY(trsv_batch<double>(A, lda, sA, n, count, (const double *)lv, sL, u != b ? b : nullptr, u, sv, m->bvec, n, m,
+                              s));
   int f = take_flag(m, s);
   if (f == FPDE_ENOTSPD) {
     int64_t col[kMaxBatch];
