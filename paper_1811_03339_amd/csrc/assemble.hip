@@ -24,6 +24,7 @@ struct LoadArgs {
 };
 
 __device__ inline double mms_phi(double s) { return s * s * (1.0 - s) * (1.0 - s); }
+
 // the powers 2 - alpha, 3 - alpha, 4 - alpha of s from one pow (a node's few
 // hundred points run one or two deep, so their 18 pows were the kernel: 19 us at
 // 27 unknowns, now 10)

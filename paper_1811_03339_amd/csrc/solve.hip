@@ -16,6 +16,7 @@
 // instantiated for FP32 storage, which the mixed-precision path factors and
 // then refines against FP64 residuals b - K u computed matrix-free from the
 // FP64 derivative vectors.
+#include <algorithm>
 #include <cmath>
 #include <mutex>
 #include <type_traits>
@@ -371,7 +372,7 @@ static void group_part_update(T *A, int64_t lda, int64_t sA, int64_t n, int coun
   const int ntc = KD / T128;
   const int64_t work = syrk128_strip_slots(n - hb, ntc) * count;
   k_syrk128<T, KD><<<(unsigned)(8 * ((work + 7) / 8)), Syrk128Shape<T>::THREADS, 0, s>>>(
-      A, lda, n, kx, hb, ntc, 1, Ln, LnT, flag, aux, sA, sL, es, n, xq, sx, count, work);
+      A, lda, n, kx, hb, ntc, 1, Ln, LnT, flag, aux, sA, sL, es, n, xq, sx, count, work, 0);
 }
 
 // Factor `count` matrices of a strided batch (A + z sA, z < count) with one
@@ -407,6 +408,15 @@ static int potrf_batch_g(T *A, int64_t lda, int64_t sA, int64_t n, int count, T 
   // columns; the FP32 split rows alternate between two sets, so that a
   // group's split does not overwrite the rows that the previous (b) reads.
   constexpr int64_t kLookaheadFrom = 16384;
+  // FP32: (b) goes in launches of one workgroup (128 x 128 tiles: two) for each of
+  // 224 CUs, so that 32 are left to the chain; beside one launch of all tiles a
+  // panel took 57 us instead of 7, a strip 71 instead of 16, each waiting for
+  // tiles of 170 us to end.  Factorization at N = 25 177 with 0 / 16 / 32 / 64 / 96
+  // CUs left: 27.4 / 27.0 / 25.5 / 26.3 / 27.6 ms; up to this many rows, beyond which
+  // (b) outlasts the chain by more than it gains (N = 35 937: slices up to 16 384 /
+  // 20 480 / 28 672 / all rows 63.4 / 62.5 / 61.3 / 61.5 ms, none 64.5).  FP64 loses
+  // (N = 35 937: 271 against 295 ms).
+  constexpr int64_t kSliceCus = 224, kSliceRows = 28672;
   const bool la = n >= kLookaheadFrom;
   if (la) {
     if (!m->side && hipStreamCreateWithFlags(&m->side, hipStreamNonBlocking) != hipSuccess) {
@@ -510,19 +520,23 @@ static int potrf_batch_g(T *A, int64_t lda, int64_t sA, int64_t n, int count, T 
               (const float *)A, lda, n, base, k0, es, xq, sA, n, sx);
         // update of the region from rb on (lower tiles), X = the group's
         // columns; factor: its tile (0, 0) factors the diagonal block at rb
+        auto slots_of = [](int64_t items) { return (unsigned)(8 * ((items + 7) / 8)); };
         auto region = [&](int64_t rb, int factor, hipStream_t st) {
           const int64_t mr = n - rb;
+          const bool sliced = !factor && std::is_same<T, float>::value && mr <= kSliceRows;
           if (std::is_same<T, float>::value && mr >= kTiles256From) {
             // 256 x 256 tiles of eight 128 x 64 wavefronts, one per CU
-            const int64_t work = lower_tiles(mr, T256) * count;
-            k_syrk256<kGroup * NB><<<(unsigned)(8 * ((work + 7) / 8)), 512, 0, st>>>(
-                (float *)A, lda, n, k0, rb, factor, (float *)Ln, (float *)LnT, m->flag, aux, sA, sL, es, n, xq, sx,
-                count, work);
+            const int64_t work = lower_tiles(mr, T256) * count, slice = sliced ? kSliceCus : work;
+            for (int64_t first = 0; first < work; first += slice)
+              k_syrk256<kGroup * NB><<<slots_of(std::min(slice, work - first)), 512, 0, st>>>(
+                  (float *)A, lda, n, k0, rb, factor, (float *)Ln, (float *)LnT, m->flag, aux, sA, sL, es, n, xq, sx,
+                  count, work, first);
           } else {
-            // 128 x 128 tiles
-            const int64_t work = lower_tiles(mr, T128) * count;
-            k_syrk128<T, kGroup * NB><<<(unsigned)(8 * ((work + 7) / 8)), Syrk128Shape<T>::THREADS, 0, st>>>(
-                A, lda, n, k0, rb, 0, factor, Ln, LnT, m->flag, aux, sA, sL, es, n, xq, sx, count, work);
+            // 128 x 128 tiles, two per CU
+            const int64_t work = lower_tiles(mr, T128) * count, slice = sliced ? 2 * kSliceCus : work;
+            for (int64_t first = 0; first < work; first += slice)
+              k_syrk128<T, kGroup * NB><<<slots_of(std::min(slice, work - first)), Syrk128Shape<T>::THREADS, 0, st>>>(
+                  A, lda, n, k0, rb, 0, factor, Ln, LnT, m->flag, aux, sA, sL, es, n, xq, sx, count, work, first);
           }
         };
         if (!la) {
@@ -533,7 +547,7 @@ static int potrf_batch_g(T *A, int64_t lda, int64_t sA, int64_t n, int count, T 
           const int ntc = kGroup * NB / T128;
           const int64_t work = syrk128_strip_slots(n - base, ntc) * count;
           k_syrk128<T, kGroup * NB><<<(unsigned)(8 * ((work + 7) / 8)), Syrk128Shape<T>::THREADS, 0, s>>>(
-              A, lda, n, k0, base, ntc, 1, Ln, LnT, m->flag, aux, sA, sL, es, n, xq, sx, count, work);
+              A, lda, n, k0, base, ntc, 1, Ln, LnT, m->flag, aux, sA, sL, es, n, xq, sx, count, work, 0);
           if (n - base > kGroup * NB) {
             // (b) after the split rows (and everything before them on s)
             FPDE_HIP(hipEventRecord(m->lev[0], s));

@@ -408,9 +408,9 @@ __attribute__((amdgpu_waves_per_eu(std::is_same<T, double>::value ? 4 : 1)))
 k_syrk128(T *__restrict__ A, int64_t lda, int64_t n, int64_t k0, int64_t base, int ntc, int factor,
           T *__restrict__ Linv_next, T *__restrict__ LinvT_next, int32_t *flag, int64_t *aux, int64_t sA,
           int64_t sL, const int *__restrict__ escale, int64_t se, const _Float16 *__restrict__ xs, int64_t sx,
-          int nz, int64_t nwork) {
+          int nz, int64_t nwork, int64_t first) {
   constexpr bool F32 = std::is_same<T, float>::value;
-  const int64_t bw = xcd_deal(blockIdx.x, gridDim.x);
+  const int64_t bw = first + xcd_deal(blockIdx.x, gridDim.x);
   if (bw >= nwork) return;
   // the tiles (0, 0) of all systems first (they factor the next diagonal
   // blocks, on which the next panel waits), then each system's other items

@@ -117,8 +117,8 @@ __global__ void __launch_bounds__(512) k_syrk256(float *__restrict__ A, int64_t 
                                                  int32_t *flag, int64_t *aux, int64_t sA, int64_t sL,
                                                  const int *__restrict__ escale, int64_t se,
                                                  const _Float16 *__restrict__ xs, int64_t sx, int nz,
-                                                 int64_t nwork) {
-  const int64_t bw = xcd_deal(blockIdx.x, gridDim.x);
+                                                 int64_t nwork, int64_t first) {
+  const int64_t bw = first + xcd_deal(blockIdx.x, gridDim.x);
   if (bw >= nwork) return;
   // the tiles (0, 0) of all systems first (they factor the next diagonal
   // blocks, on which the next panel waits), then each system's other items
