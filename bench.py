@@ -4,21 +4,21 @@
 Headline workload (synthetic, seeded): the convex hull of 2000 random points
 in the ellipsoid with semi-axes (1, 0.7, 0.4), filled with a jittered
 body-centred-cubic lattice (~400k elements, ~67k nodes), Riesz order
-alpha = 1.3 (the timed passes alternate 1.30 / 1.31 so every pass walks its
-paths again instead of reusing the previous pass's derivative values),
+alpha = 1.3 (the timed passes alternate 1.30 / 1.31 so every pass computes its
+derivative values anew instead of reusing the previous pass's),
 K = (1, 1, 1), the 11-point element rule.
 
-One step = one mixed-precision assembly + solve pass on that mesh: path walk
-and closed-form derivatives (FP64), accumulation of the dense stiffness
+One step = one mixed-precision assembly + solve pass on that mesh: closed-form
+derivatives along every path (FP64), accumulation of the dense stiffness
 matrix stored in FP32 (~18 GB), load vector, FP32 Cholesky, then refinement
 with FP64 residuals from the matrix-free product until ||b - K u|| / ||b||
 <= 1e-8.  Inputs are resident on the device when the timed region starts;
-the mesh set-up and the symbolic plan (built once per mesh and rule) happen
-before it and are reported apart.
+the mesh set-up and the symbolic plan (the path walk, built once per mesh and
+rule) happen before it and are reported apart.
 
 value = Gauss-point paths per second of the whole step (6 half-rays per
 Gauss point divided by the step time).  Beside it on the single JSON line:
-assembly+solve seconds per step, paths/s of walk+eval alone, the FP64 arm on
+assembly+solve seconds per step, paths/s of the derivative values alone, the FP64 arm on
 the same mesh (FP64 matrix, ~36 GB, FP64 Cholesky) with the mixed/FP64
 speedup and the distance between the two solutions, the per-stage times, the
 roofline of the step's dominant kernel (launch durations measured over the
@@ -110,7 +110,7 @@ def bench_mixed_large(F, torch, dev, reps=3):
     """FP64 against the mixed arm where the factorization dominates: the
     convex-hull mesh of 400 sphere points with ~150k elements (~25k
     unknowns), 11-point rule, K = (1, 1, 1), alpha alternating 1.70 / 1.69
-    so that every pass re-walks.  Per pass and arm: assembly + solve (FP64:
+    so that every pass has new values.  Per pass and arm: assembly + solve (FP64:
     FP64 matrix, Cholesky, two triangular solves; mixed: FP32 matrix, FP32
     Cholesky, refinement with FP64 matrix-free residuals to 1e-8).  Median of
     `reps` passes after one warm-up pass of each arm."""
@@ -179,10 +179,10 @@ def bench_mixed_large(F, torch, dev, reps=3):
 def bench_sec3(F, torch, dev, reps=4):
     """The divergence-form problem of Sec. 3 on the finest mesh of Table 3
     (ball |x| < 0.5, largest element diameter 0.0757): per pass the Sec. 3
-    assembly (walk values at the pass's orders, row accumulation, closed-form
+    assembly (derivative values at the pass's orders, row accumulation, closed-form
     source), the LU factorization and the two triangular solves.  Passes
-    alternate the two order sets of Table 3, so the walk re-evaluates the
-    axes whose order changed."""
+    alternate the two order sets of Table 3, so the values of the
+    axes whose order changed are computed anew."""
     import numpy as np
     from fpde_inputs import workload_mesh
     mesh = workload_mesh(SEC3_WORKLOAD)
@@ -289,7 +289,7 @@ FORM_BETA = (0.9, 0.4, 0.7)
 def bench_form(F, torch, gm, info4, reps=3):
     """The general uniform form (c D^alpha u, D^beta v) with per-axis orders
     on the bench mesh (4-point rule), constant coefficients: both value sets
-    re-walked every pass (the orders alternate), the two products of every
+    computed anew every pass (the orders alternate), the two products of every
     pair accumulated by tubes (k_tube_form), then the row pass of K."""
     n = gm.n_dof
     A = torch.empty((n, n), dtype=torch.float64, device="cuda")
@@ -326,9 +326,9 @@ PLANE_WORKLOAD = "disk4k"
 
 def bench_plane(F, torch, reps=3):
     """The two-dimensional variant on the disk (4654 nodes), 7-point rule:
-    per pass the walk at the pass's order, the row accumulation, the load
+    per pass the values at the pass's order, the accumulation, the load
     vector and the dense Cholesky solve (orders alternate so every pass
-    re-walks)."""
+    has new values)."""
     from fpde_inputs import workload_mesh
     mesh = workload_mesh(PLANE_WORKLOAD)
     g2 = F.Mesh2D(mesh.xyz, mesh.tet)
@@ -373,7 +373,7 @@ def bench_adjoint(F, torch, dev):
     J = ||u_h - u_obs||^2 at alpha = 1.4, K = (1, 1, 1) (4-point rule), u_obs
     from alpha = 1.6, K = (1.2, 0.8, 1.0) plus N(0, 1e-3^2) noise (seed 40).
     One forward (assembly + FP64 solve) and backward (adjoint solve with the
-    stored factor + the adjoint kernel re-walking every path), timed, and the
+    stored factor + the adjoint sums over every path), timed, and the
     gradient against central differences with h = 1e-6."""
     import numpy as np
     from fpde_inputs import workload_mesh
@@ -429,9 +429,9 @@ def bench_adjoint(F, torch, dev):
 def bench_c2(F, torch, dev, steps=20, warmup=2):
     """The six-system batch on the ~20k-element sphere hull (3 alphas x 2
     rules, K = (1, 0.5, 2)): per step the six systems are assembled as one
-    batch (walks beside the accumulations) and factored and solved as one
+    batch (values beside the accumulations) and factored and solved as one
     batch.  Also the mixed arm at this size (alpha alternating so that every
-    pass walks again), the template CSR / CG and the general-form sections."""
+    pass has new values), the template CSR / CG and the general-form sections."""
     from fpde_inputs import workload_mesh
     mesh = workload_mesh(C2_WORKLOAD)
     gm = F.Mesh(mesh.xyz, mesh.tet)
@@ -481,7 +481,7 @@ def bench_c2(F, torch, dev, steps=20, warmup=2):
                              "achieved": fl / t / 1e12, "peak": FP64_PEAK / 1e12, "unit": "TFLOP/s",
                              "frac": fl / t / FP64_PEAK,
                              "note": "4 |L| |R| flops per (g, i): both products W (R L^T + L R^T)"}
-    # mixed arm at this size, alpha alternating so every pass walks again
+    # mixed arm at this size, alpha alternating so every pass has new values
     p64s = [F.params(a, KCOEF, quad_points=11) for a in (1.5, 1.51)]
     pmxs = [F.params(a, KCOEF, quad_points=11, precision=F.FPDE_MIXED, ir_tol=1e-8) for a in (1.5, 1.51)]
     A32 = torch.empty((n, n), dtype=torch.float32, device=dev)
@@ -711,7 +711,7 @@ def main():
         ts = []
         gm.timing(True)
         # pass 0 (untimed) warms the FP64 scratch; the timed passes 1 and 2
-        # each take the alpha the previous pass did not (so both walk), and
+        # each take the alpha the previous pass did not (so both have new values), and
         # the last is the mixed solution's
         mi = HEAD_ALPHAS.index(alpha_mixed)
         seq = [p64[mi], p64[1 - mi], p64[mi]]

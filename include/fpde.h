@@ -170,7 +170,7 @@ int fpde_ray_values(fpde_mesh *m, int quad_points, double alpha, int dir, int64_
  *   b: dev, n_dof FP64, b_j = sum_g w_g f(x_g) psi_j(x_g); may be NULL.
  *   f_gauss: dev, n_tet * quad_points FP64 source values at the Gauss points
  *      (index element * quad_points + q) for FPDE_SRC_USER, else ignored.
- * Synchronises `stream` (walk status).
+ * Synchronises `stream` (status).
  * Errors: FPDE_EINVAL, FPDE_EALPHA, FPDE_EPATH, FPDE_ENOMEM, FPDE_EHIP.
  */
 int fpde_assemble(fpde_mesh *m, const fpde_params *p, void *A, int64_t lda, double *b,
@@ -184,12 +184,12 @@ int fpde_assemble(fpde_mesh *m, const fpde_params *p, void *A, int64_t lda, doub
  * its load vector to b + z stride_b (stride_b >= n_dof).  The systems'
  * kernels are enqueued back to back; the caller of a batch solve
  * (fpde_solve_batch) assembles with this and synchronises twice per batch
- * instead of once per system.  The walks (derivative values) run on a
+ * instead of once per system.  The derivative values are computed on a
  * second stream owned by the mesh handle, each beside the previous
  * system's accumulation when that one uses the other quadrature rule;
  * events order them after the work already on `stream` and before the
  * accumulations on `stream`, so on return all of it is complete.
- * Synchronises `stream`.  Errors: as fpde_assemble; on a walk failure
+ * Synchronises `stream`.  Errors: as fpde_assemble; on a failure
  * every touched value set is invalidated and no system is to be used.
  */
 int fpde_assemble_batch(fpde_mesh *m, int count, const fpde_params *p, void *A, int64_t lda, int64_t stride_A,
@@ -252,7 +252,7 @@ int fpde_solve_batch(fpde_mesh *m, int count, double *A, int64_t lda, int64_t st
  * path of fpde_solve without its residual -- A (dev, n_dof x lda FP64, from
  * fpde_assemble) is overwritten by its Cholesky factor and u = K^{-1} b
  * (b, u: dev, n_dof FP64, may alias) -- with every scratch buffer (the
- * diagonal-block inverses, the triangular solves' flags and tickets, one
+ * diagonal-block inverses, the triangular solves' tickets, one
  * intermediate vector; 8.4 MB) in a static device array of the library
  * instead of the handle: no hipMalloc, hipFree or allocating library call.
  * Limit: n_dof <= 8192.  Each device holds one copy of the array for the
@@ -274,7 +274,7 @@ int fpde_solve_noalloc(fpde_mesh *m, double *A, int64_t lda, const double *b, do
  *   dJ/dalpha = -sum_i K_i (c'_alpha S_i + c_alpha T_i)
  *   S_i = sum_g w_g [(lam.R)(L.u) + (lam.L)(R.u)]
  *   T_i = sum_g w_g [(lam.R')(L.u) + (lam.R)(L'.u) + (lam.L')(R.u) + (lam.L)(R'.u)]
- * (' = d/dalpha).  The paths are walked again (recomputed, not stored).
+ * (' = d/dalpha), summed over the plan's segments.
  *   u, lam: dev, n_dof FP64.  grad_alpha, grad_K: host (1 and 3 FP64).
  * Synchronises `stream`.  Errors: FPDE_EINVAL, FPDE_EALPHA, FPDE_EPATH.
  */
@@ -284,7 +284,7 @@ int fpde_adjoint(fpde_mesh *m, const fpde_params *p, const double *u, const doub
 /*
  * Stage timing with HIP events recorded on the caller's stream around each
  * stage launch (no extra synchronisation while recording).
- * Stages: walk + closed-form evaluation, accumulation (both tube passes),
+ * Stages: closed-form evaluation (FPDE_STAGE_WALK), accumulation (both tube passes),
  * load vector, Cholesky factorisation (all panels), triangular solves,
  * matrix-free product, symbolic plan, adjoint sums, the tube products
  * pass timed again on its own inside CONTRACT, for the problem of Sec. 3

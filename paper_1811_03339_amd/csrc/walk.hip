@@ -575,6 +575,22 @@ __global__ void __launch_bounds__(64 * kValWaves) k_values(ValArgs a) {
   }
 }
 
+// a.x b0 + .. + a.w b3 as if in twice the precision (compensated dot product by
+// Ogita, Rump and Oishi): the terms cancel to the element's size over the
+// domain's, and every ray through the element shares the result's rounding.
+__device__ __forceinline__ double dot4_comp(const double4 &a, const double (&b)[4]) {
+  const double c[4] = {a.x, a.y, a.z, a.w};
+  double p = c[0] * b[0], e = fma(c[0], b[0], -p);
+#pragma unroll
+  for (int j = 1; j < 4; j++) {
+    const double h = c[j] * b[j], l = fma(c[j], b[j], -h);
+    const double t = p + h, z = t - p;
+    e += ((p - (t - z)) + (h - z)) + l;
+    p = t;
+  }
+  return p + e;
+}
+
 // derivatives of u and lam along the axes, per element
 __global__ void k_elem_grad(const TetRec *__restrict__ rec, const double4 *__restrict__ slope, int64_t nt,
                             const double *__restrict__ u, const double *__restrict__ lam,
@@ -591,8 +607,7 @@ __global__ void k_elem_grad(const TetRec *__restrict__ rec, const double4 *__res
 #pragma unroll
   for (int i = 0; i < 3; i++) {
     const double4 c = slope[i * nt + t];
-    grad[i * nt + t] = make_double2(((c.x * uu[0] + c.y * uu[1]) + c.z * uu[2]) + c.w * uu[3],
-                                    ((c.x * ll[0] + c.y * ll[1]) + c.z * ll[2]) + c.w * ll[3]);
+    grad[i * nt + t] = make_double2(dot4_comp(c, uu), dot4_comp(c, ll));
   }
 }
 
