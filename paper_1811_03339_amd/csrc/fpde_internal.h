@@ -251,10 +251,10 @@ int launch_form_tubes(fpde_mesh *m, Plan &P, const double cl[3], const double cr
 int launch_contract_tubes_csr(fpde_mesh *m, Plan &P, const fpde_params *p, const int64_t *row_ptr,
                               const int32_t *col, double *val, hipStream_t s);
 // matrix-free y = K x from the plan's values, and the diagonal of K
-// (done: device flag that turns the product off once set, or null; dot: with
-// x.y as op_blocks(ndof, true) partial sums, or null)
+// (cg: as a step of the conjugate gradients, or null)
+struct CgStep;
 int apply_matfree(fpde_mesh *m, Plan *P, const fpde_params *p, const double *x, double *y, hipStream_t s,
-                  const int32_t *done = nullptr, double *dot = nullptr);
+                  const CgStep *cg = nullptr);
 // workgroups (four rows each) of the row pass of an operator; at most
 // kOpParts, striding over the rows, when it leaves partial sums
 constexpr int kOpParts = 1024;

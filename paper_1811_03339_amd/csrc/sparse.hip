@@ -23,6 +23,7 @@
 #include <cmath>
 #include <vector>
 
+#include "cg.h"
 #include "fpde_internal.h"
 
 namespace fpde {
@@ -90,30 +91,34 @@ __global__ void __launch_bounds__(256) k_tpl_fill(const double *__restrict__ box
   }
 }
 
-// y = K x, one wavefront per row (4 rows per workgroup and step).  With dot
-// not null, dot[block] = the workgroup's part of x.y; nothing is done once
-// *done is set.
+// y = K x, one wavefront per row (4 rows per workgroup and step); c as in CgStep
 __global__ void __launch_bounds__(256) k_csr_apply(const int64_t *__restrict__ row_ptr,
                                                    const int32_t *__restrict__ col, const double *__restrict__ val,
                                                    const double *__restrict__ x, int64_t n, double *__restrict__ y,
-                                                   double *__restrict__ dot, const int32_t *__restrict__ done) {
+                                                   CgStep c) {
   __shared__ double red[4];
-  if (done && *done) return;
+  double be = 0.0;
+  if (c.st && cg_ended(c, be, red, blockIdx.x == 0)) return;
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   double xy = 0.0;
   for (int64_t j = (int64_t)blockIdx.x * 4 + w; j < n; j += (int64_t)gridDim.x * 4) {
     double s = 0.0;
-    for (int64_t q = row_ptr[j] + lane; q < row_ptr[j + 1]; q += 64) s = fma(val[q], x[col[q]], s);
+    for (int64_t q = row_ptr[j] + lane; q < row_ptr[j + 1]; q += 64) s = fma(val[q], cg_entry(c, be, x, col[q]), s);
     for (int o = 32; o > 0; o >>= 1) s += __shfl_down(s, o, 64);
     if (lane == 0) {
       y[j] = s;
-      if (dot) xy = fma(s, x[j], xy);
+      if (c.st) {
+        const double pj = cg_entry(c, be, x, j);
+        c.pn[j] = pj;
+        xy = fma(s, pj, xy);
+      }
     }
   }
-  if (!dot) return;
+  if (!c.st) return;
+  __syncthreads();  // red
   if (lane == 0) red[w] = xy;
   __syncthreads();
-  if (threadIdx.x == 0) dot[blockIdx.x] = (red[0] + red[1]) + (red[2] + red[3]);
+  if (threadIdx.x == 0) c.dot[blockIdx.x] = (red[0] + red[1]) + (red[2] + red[3]);
 }
 
 // d_j = K_jj from the CSR row (binary search of the sorted columns)
@@ -141,29 +146,13 @@ __global__ void k_csr_diag(const int64_t *__restrict__ row_ptr, const int32_t *_
 // The scalars of the iteration stay on the device: a kernel leaves partial
 // sums, one per workgroup, and every workgroup of the next kernel adds them up
 // itself, in the same order, so that all agree without a launch in between.
-// An iteration is three launches (product with p.q, update with r.r and r.z,
-// direction).  The host queues iterations a few at a time and looks at the
+// An iteration is two launches (direction and product with p.q; update with r.r
+// and r.z; matrix-free one more, the row pass).  The host queues iterations a few at a time and looks at the
 // state of the chunk before; what is queued past the end finds `done` set and
 // does nothing.  (With three dot products per iteration read back by the host
-// an iteration took 200 us around a product of 12 us; now 50 us.)
-struct CgState {
-  double rz[2];        // r.z of the even and of the odd iterations
-  double bn2, rr, rt;  // b.b; r.r; true residual squared
-  int32_t done;        // 0: running, 1: ended (converged or not a number), 2: not positive definite
-  int32_t it;
-};
+// an iteration took 200 us around a product of 12 us, with a launch of its own
+// for the direction 21 us; now 20 us.)
 constexpr int kCgParts = 256;  // workgroups of the vector kernels at most
-
-// sum of part[0 .. n) (stride ld), n <= 1024, in every thread; 256 threads
-__device__ __forceinline__ double sum_parts(const double *__restrict__ part, int n, int ld, double *red) {
-  double s = 0.0;
-  for (int k = threadIdx.x; k < n; k += 256) s += part[(int64_t)k * ld];
-  for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
-  __syncthreads();  // red may still be read from the sum before
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
-  __syncthreads();
-  return (red[0] + red[1]) + (red[2] + red[3]);
-}
 
 // two sums over the workgroup's threads to part[2 blockIdx.x], [.. + 1]
 __device__ __forceinline__ void put_parts(double a, double b, double *__restrict__ part, double *red) {
@@ -249,25 +238,11 @@ __global__ void __launch_bounds__(256) k_cg_update(double *__restrict__ u, doubl
   put_parts(rr, rz, part, red);
 }
 
-// the end of iteration `it`: |r| / |b| <= tol ends the loop, else p = z + (r.z / old r.z) p
-__global__ void __launch_bounds__(256) k_cg_dir(double *__restrict__ p, const double *__restrict__ z, int64_t n,
-                                                CgState *st, int it, double tol, const double *__restrict__ part,
-                                                int np) {
+// one workgroup: the end of the last iteration that may be taken
+__global__ void __launch_bounds__(256) k_cg_last(CgStep c) {
   __shared__ double red[4];
-  if (st->done) return;
-  const int odd = it & 1;
-  const double rr = sum_parts(part, np, 2, red), rz = sum_parts(part + 1, np, 2, red);
-  const double be = rz / st->rz[odd];
-  const bool end = !(sqrt(rr) / sqrt(st->bn2) > tol);
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
-    st->rr = rr;
-    st->it = it + 1;
-    st->rz[odd ^ 1] = rz;
-    if (end) st->done = 1;
-  }
-  if (end) return;
-  for (int64_t k = (int64_t)blockIdx.x * 256 + threadIdx.x; k < n; k += (int64_t)gridDim.x * 256)
-    p[k] = fma(be, p[k], z[k]);
+  double be;
+  (void)cg_ended(c, be, red, true);
 }
 
 // parts of |b - q|^2, and their sum to st->rt (one workgroup)
@@ -289,10 +264,10 @@ __global__ void __launch_bounds__(256) k_cg_end(CgState *st, const double *__res
 
 inline unsigned blocks_of(int64_t n, int b = 256) { return (unsigned)((n + b - 1) / b); }
 
-// CG scratch in the mesh handle: r, z, p, q, d, dinv (6 N), partial sums of
+// CG scratch in the mesh handle: r, z, two p, q, d, dinv (7 N), partial sums of
 // the product and of the vector kernels, the state
 struct CgWork {
-  double *r, *z, *p, *q, *d, *dinv, *op_part, *part;
+  double *r, *z, *p[2], *q, *d, *dinv, *op_part, *part;
   CgState *st, *host;  // host: two pinned copies
 };
 
@@ -300,7 +275,7 @@ struct CgWork {
 
 static int ensure_cg(fpde_mesh *m, CgWork *w) {
   const int64_t n = m->ndof > 0 ? m->ndof : 1;
-  const int64_t need = 6 * n + kOpParts + 2 * kCgParts + (int64_t)(sizeof(CgState) / sizeof(double));
+  const int64_t need = 7 * n + kOpParts + 2 * kCgParts + (int64_t)(sizeof(CgState) / sizeof(double));
   static_assert(sizeof(CgState) % sizeof(double) == 0, "the state follows the sums");
   if (m->cg_n < need) {
     dfree(m->cg);
@@ -319,8 +294,9 @@ static int ensure_cg(fpde_mesh *m, CgWork *w) {
     }
   w->r = m->cg;
   w->z = w->r + n;
-  w->p = w->z + n;
-  w->q = w->p + n;
+  w->p[0] = w->z + n;
+  w->p[1] = w->p[0] + n;
+  w->q = w->p[1] + n;
   w->d = w->q + n;
   w->dinv = w->d + n;
   w->op_part = w->dinv + n;
@@ -410,7 +386,7 @@ extern "C" int fpde_csr_apply(fpde_mesh *m, const int64_t *row_ptr, const int32_
   if (m->ndof == 0) return FPDE_OK;
   hipStream_t s = S(stream);
   const long t = timer_begin(m, s, FPDE_STAGE_SPMV);
-  k_csr_apply<<<op_blocks(m->ndof, false), 256, 0, s>>>(row_ptr, col, val, x, m->ndof, y, nullptr, nullptr);
+  k_csr_apply<<<op_blocks(m->ndof, false), 256, 0, s>>>(row_ptr, col, val, x, m->ndof, y, CgStep{});
   timer_end(m, FPDE_STAGE_SPMV, t, s);
   FPDE_HIP(hipGetLastError());
   return FPDE_OK;
@@ -440,17 +416,15 @@ extern "C" int fpde_cg_solve(fpde_mesh *m, const fpde_params *p, const int64_t *
     FPDE_TRY(plan_for(m, p->quad_points, p->max_steps, s, &P));
     FPDE_TRY(ensure_values(m, P, p->alpha, s));
   }
-  // y = K x; inside the loop with the parts of x.y, and off once the loop ended
-  auto op = [&](const double *x, double *y, bool loop) -> int {
-    const int32_t *done = loop ? &w.st->done : nullptr;
-    double *dot = loop ? w.op_part : nullptr;
+  // y = K x, plain or as a step of the loop
+  auto op = [&](const double *x, double *y, const CgStep &c) -> int {
     if (csr) {
       const long t = timer_begin(m, s, FPDE_STAGE_SPMV);
-      k_csr_apply<<<op_blocks(n, loop), 256, 0, s>>>(row_ptr, col, val, x, n, y, dot, done);
+      k_csr_apply<<<op_blocks(n, c.st != nullptr), 256, 0, s>>>(row_ptr, col, val, x, n, y, c);
       timer_end(m, FPDE_STAGE_SPMV, t, s);
       return hipGetLastError() == hipSuccess ? FPDE_OK : FPDE_EHIP;
     }
-    return apply_matfree(m, P, p, x, y, s, done, dot);
+    return apply_matfree(m, P, p, x, y, s, c.st ? &c : nullptr);
   };
   const unsigned vb = (unsigned)std::min<int64_t>(blocks_of(n), kCgParts);
   const long t_all = timer_begin(m, s, FPDE_STAGE_CG);
@@ -461,17 +435,29 @@ extern "C" int fpde_cg_solve(fpde_mesh *m, const fpde_params *p, const int64_t *
     FPDE_TRY(matfree_diagonal(m, P, p, w.d, s));
   }
   k_cg_clear<<<1, 1, 0, s>>>(w.st);
-  k_cg_start<<<vb, 256, 0, s>>>(b, w.d, u, w.r, w.z, w.p, w.dinv, n, w.st, w.part);
+  k_cg_start<<<vb, 256, 0, s>>>(b, w.d, u, w.r, w.z, w.p[0], w.dinv, n, w.st, w.part);
   k_cg_begin<<<1, 256, 0, s>>>(w.st, tol, w.part, (int)vb);
   // chunks of iterations, the next one queued before the state of the last is read
   constexpr int kChunk = 4;
   int queued = 0;
+  CgStep c;
+  c.st = w.st;
+  c.z = w.z;
+  c.part = w.part;
+  c.np = (int)vb;
+  c.dot = w.op_part;
+  c.tol = tol;
   auto chunk = [&](int slot) -> int {
     for (int k = 0; k < kChunk && queued < max_iter; k++, queued++) {
-      FPDE_TRY(op(w.p, w.q, true));
-      k_cg_update<<<vb, 256, 0, s>>>(u, w.r, w.z, w.p, w.q, w.dinv, n, w.st, queued & 1, w.op_part,
+      c.it = queued;
+      c.pn = w.p[(queued + 1) & 1];
+      FPDE_TRY(op(w.p[queued & 1], w.q, c));
+      k_cg_update<<<vb, 256, 0, s>>>(u, w.r, w.z, c.pn, w.q, w.dinv, n, w.st, queued & 1, w.op_part,
                                      (int)op_blocks(n, true), w.part);
-      k_cg_dir<<<vb, 256, 0, s>>>(w.p, w.z, n, w.st, queued, tol, w.part, (int)vb);
+    }
+    if (queued == max_iter) {
+      c.it = queued;
+      k_cg_last<<<1, 256, 0, s>>>(c);
     }
     FPDE_HIP(hipGetLastError());
     FPDE_HIP(hipMemcpyAsync(&w.host[slot], w.st, sizeof(CgState), hipMemcpyDeviceToHost, s));
@@ -493,7 +479,7 @@ extern "C" int fpde_cg_solve(fpde_mesh *m, const fpde_params *p, const int64_t *
     return FPDE_ENOTSPD;
   }
   // the true residual b - K u of the result, not the recursively updated one
-  FPDE_TRY(op(u, w.q, false));
+  FPDE_TRY(op(u, w.q, CgStep{}));
   k_cg_residual<<<vb, 256, 0, s>>>(b, w.q, n, w.part);
   k_cg_end<<<1, 256, 0, s>>>(w.st, w.part, (int)vb);
   FPDE_HIP(hipGetLastError());

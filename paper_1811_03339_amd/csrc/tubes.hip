@@ -36,6 +36,7 @@
 #include <cmath>
 #include <vector>
 
+#include "cg.h"
 #include "fpde_internal.h"
 
 namespace fpde {
@@ -935,7 +936,7 @@ struct ApplyArgs {
   double *part;
   double KC0, KC1, KC2;
   int max_u;
-  const int32_t *done;     // not null: nothing is done once it is set
+  CgStep cg;
 };
 
 template <int ctrl>
@@ -997,14 +998,18 @@ __device__ __forceinline__ void held_add(const HeldSide &h, double c, double *ys
 
 __global__ void __launch_bounds__(64 * kApplyWaves) k_tube_apply(ApplyArgs a) {
   extern __shared__ double lds[];
-  if (a.done && *a.done) return;
+  double be = 0.0;
+  if (a.cg.st) {
+    if (cg_ended(a.cg, be, lds, blockIdx.x == 0)) return;
+    __syncthreads();  // the sums' LDS is free
+  }
   const int4 it = a.items[blockIdx.x];
   const int64_t u0 = a.u_off[it.x];
   const int U = (int)(a.u_off[it.x + 1] - u0);
   const int wave = threadIdx.x >> 6, grp = threadIdx.x >> 4;
   double *xs = lds, *ys = lds + (int64_t)(1 + wave) * a.max_u;
   for (int j = threadIdx.x; j < U; j += blockDim.x) {
-    xs[j] = a.x[a.tube_u[u0 + j]];
+    xs[j] = cg_entry(a.cg, be, a.x, a.tube_u[u0 + j]);
 #pragma unroll
     for (int v = 0; v < kApplyWaves; v++) lds[(int64_t)(1 + v) * a.max_u + j] = 0.0;
   }
@@ -1085,16 +1090,16 @@ __global__ void k_tube_diag(ApplyArgs a) {
 }
 
 // y_j = the sum of node j's places in the segments' parts; one wavefront per
-// node, four nodes per workgroup and step.  With dot not null, dot[block] = the
-// workgroup's part of x.y.
+// node, four nodes per workgroup and step.  As a step of the conjugate gradients
+// it also leaves the direction and its part of its product with y.
 __global__ void __launch_bounds__(256) k_tube_sum(const int64_t *__restrict__ row_off, const int2 *__restrict__ row_ts,
                                                   const int64_t *__restrict__ u_off,
                                                   const int64_t *__restrict__ seg_off,
                                                   const double *__restrict__ part, int64_t ndof,
-                                                  double *__restrict__ y, const double *__restrict__ x,
-                                                  double *__restrict__ dot, const int32_t *__restrict__ done) {
+                                                  double *__restrict__ y, const double *__restrict__ x, CgStep c) {
   __shared__ double red[4];
-  if (done && *done) return;
+  if (c.st && c.st->done) return;
+  const double be = c.st ? c.st->be : 0.0;  // by k_tube_apply
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   double xy = 0.0;
   for (int64_t j = (int64_t)blockIdx.x * 4 + wave; j < ndof; j += (int64_t)gridDim.x * 4) {
@@ -1107,13 +1112,17 @@ __global__ void __launch_bounds__(256) k_tube_sum(const int64_t *__restrict__ ro
     for (int o = 32; o > 0; o >>= 1) s += __shfl_down(s, o, 64);
     if (lane == 0) {
       y[j] = s;
-      if (dot) xy = fma(s, x[j], xy);
+      if (c.st) {
+        const double pj = cg_entry(c, be, x, j);
+        c.pn[j] = pj;
+        xy = fma(s, pj, xy);
+      }
     }
   }
-  if (!dot) return;
+  if (!c.st) return;
   if (lane == 0) red[wave] = xy;
   __syncthreads();
-  if (threadIdx.x == 0) dot[blockIdx.x] = (red[0] + red[1]) + (red[2] + red[3]);
+  if (threadIdx.x == 0) c.dot[blockIdx.x] = (red[0] + red[1]) + (red[2] + red[3]);
 }
 
 struct TubeMfmaArgs {
@@ -1698,7 +1707,7 @@ static unsigned gather_grid(int64_t ndof) {
 
 // y = K x (diag: its diagonal) from the plan's current values
 static int apply_tubes(fpde_mesh *m, Plan &P, const fpde_params *p, const double *x, double *y, bool diag,
-                       hipStream_t s, const int32_t *done, double *dot) {
+                       hipStream_t s, const CgStep *cg) {
   TubePlan &tp = P.tubes;
   if (!tp.part) FPDE_TRY(dalloc(&tp.part, (size_t)tp.n_part));
   const Order o = order_scalars(p->alpha);
@@ -1717,7 +1726,7 @@ static int apply_tubes(fpde_mesh *m, Plan &P, const fpde_params *p, const double
   a.KC1 = p->K[1] * o.c_alpha;
   a.KC2 = p->K[2] * o.c_alpha;
   a.max_u = (int)tp.max_u;
-  a.done = done;
+  if (cg) a.cg = *cg;
   if (tp.n_aitems > 0 && diag) {
     // two LDS rows per wavefront: four wavefronts up to 2560 nodes, else two
     const int nw = tp.max_u <= 2560 ? 4 : 2;
@@ -1726,8 +1735,8 @@ static int apply_tubes(fpde_mesh *m, Plan &P, const fpde_params *p, const double
     // x and a part per wavefront: 160 KB at the 4096 nodes a tube may have
     k_tube_apply<<<(unsigned)tp.n_aitems, 64 * kApplyWaves, sizeof(double) * (1 + kApplyWaves) * tp.max_u, s>>>(a);
   }
-  k_tube_sum<<<op_blocks(m->ndof, dot != nullptr), 256, 0, s>>>(tp.row_off, tp.row_ts, tp.u_off, tp.seg_off, tp.part,
-                                                                m->ndof, y, x, dot, done);
+  k_tube_sum<<<op_blocks(m->ndof, cg != nullptr), 256, 0, s>>>(tp.row_off, tp.row_ts, tp.u_off, tp.seg_off, tp.part,
+                                                                m->ndof, y, x, a.cg);
   FPDE_HIP(hipGetLastError());
   return FPDE_OK;
 }
@@ -1738,16 +1747,16 @@ static int apply_tubes(fpde_mesh *m, Plan &P, const fpde_params *p, const double
 // elements (4 points; 0.37 ms in order already), 1.6 ms for 151 907 elements
 // (11 points; 3.9 ms on merged entries, whose order cost 8 ms per assembly).
 int apply_matfree(fpde_mesh *m, Plan *P, const fpde_params *p, const double *x, double *y, hipStream_t s,
-                  const int32_t *done, double *dot) {
+                  const CgStep *cg) {
   if (m->ndof == 0) return FPDE_OK;
   const long t = timer_begin(m, s, FPDE_STAGE_APPLY);
-  FPDE_TRY(apply_tubes(m, *P, p, x, y, false, s, done, dot));
+  FPDE_TRY(apply_tubes(m, *P, p, x, y, false, s, cg));
   timer_end(m, FPDE_STAGE_APPLY, t, s);
   return FPDE_OK;
 }
 
 int matfree_diagonal(fpde_mesh *m, Plan *P, const fpde_params *p, double *d, hipStream_t s) {
-  return apply_tubes(m, *P, p, nullptr, d, true, s, nullptr, nullptr);
+  return apply_tubes(m, *P, p, nullptr, d, true, s, nullptr);
 }
 
 int launch_contract_tubes(fpde_mesh *m, Plan &P, const fpde_params *p, void *A, int64_t lda, hipStream_t s) {
