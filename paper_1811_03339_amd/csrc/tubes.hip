@@ -979,11 +979,14 @@ __device__ __forceinline__ void held_load(HeldSide &h, int e0, int n, const int3
 
 __device__ __forceinline__ double held_dot(const HeldSide &h, const double *xs, const int32_t *__restrict__ slot,
                                            const double *__restrict__ val) {
+  const int gl = threadIdx.x & 15;
   double d = 0.0;
 #pragma unroll
-  for (int j = 0; j < kApplyHeld; j++) d = fma(h.v[j], xs[h.s[j]], d);
-  for (int e = 16 * kApplyHeld + (int)(threadIdx.x & 15); e < h.n; e += 16)
-    d = fma(val[h.e0 + e], xs[slot[h.e0 + e]], d);
+  for (int j = 0; j < kApplyHeld; j++) {
+    const double x = xs[h.s[j]];  // without an entry: slot 0, whose x may be infinite
+    d = fma(h.v[j], 16 * j + gl < h.n ? x : 0.0, d);
+  }
+  for (int e = 16 * kApplyHeld + gl; e < h.n; e += 16) d = fma(val[h.e0 + e], xs[slot[h.e0 + e]], d);
   return group_sum(d);
 }
 
