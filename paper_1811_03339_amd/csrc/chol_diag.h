@@ -18,10 +18,10 @@ struct DiagSmem {
 };
 
 // 1 / sqrt(x) from the hardware's estimate and one third-order step of the
-// series of (1 - t)^(-1/2), t = 1 - x y^2; NaN for x < 0
+// series of (1 - t)^(-1/2), t = 1 - x y^2; NaN for x < 0, 0 for infinite x
 __device__ __forceinline__ double rsqrt_step(double x) {
   const double y = __builtin_amdgcn_rsq(x);
-  const double t = fma(-(x * y), y, 1.0);
+  const double t = fma(-((x < INFINITY ? x : 0.0) * y), y, 1.0);
   return fma(y * t, fma(t, 0.375, 0.5), y);
 }
 
@@ -95,9 +95,10 @@ __device__ __forceinline__ void diag_store_panel(const DiagSmem &sm, int p, int 
 //      same in both) and half of the 64 other rows (lanes 16..47), one row
 //      per lane and the 16 columns in registers, and run the pivots two at a
 //      time without touching LDS: the multipliers L[k][j] are read from lane k
-//      with readlane, and the two reciprocal square roots of a pair, of a and of
-//      a c - b^2 for the pivot block [a b; b c] (scaled by a's power of two, so
-//      that no product leaves the range), do not wait for each other;
+//      with readlane, and the second pivot c - (b / sqrt(a))^2 of a pivot block
+//      [a b; b c] is formed beside the first one's column, from the same rounded
+//      numbers that the column holds (from a c - b^2, which does not wait for the
+//      first root, the error of L L^T grew with the pair's condition);
 //   3. beside them wavefronts 2 and 3 apply panel cb - 1 to the columns right
 //      of the panel and write its outputs.
 // One wavefront factoring a 16-column block at a time through LDS and four
@@ -134,14 +135,11 @@ __device__ __forceinline__ void diag_factor(DiagSmem &sm, int nb, T *__restrict_
       double a = read_lane(v[0], 0), b = read_lane(v[0], 1), c = read_lane(v[1], 1);
 #pragma unroll
       for (int j = 0; j < 16; j += 2) {
-        const int e = __builtin_amdgcn_frexp_exp(a);
-        const double as = ldexp(a, -e), bs = ldexp(b, -e), cs = ldexp(c, -e);
-        const double det = fma(as, cs, -(bs * bs));
-        good = good && a > 0.0 && det > 0.0;
-        const double ra = rsqrt_step(a), rd = rsqrt_step(det);
-        const double l21 = b * ra, i22 = ldexp((a * ra) * rd, -e);  // 1 / L[j+1][j+1]
+        const double ra = rsqrt_step(a), l21 = b * ra, a2 = fma(-l21, l21, c);
+        good = good && a > 0.0 && a2 > 0.0;
+        const double rd = rsqrt_step(a2);  // 1 / L[j+1][j+1]
         v[j] *= ra;
-        v[j + 1] = fma(-v[j], l21, v[j + 1]) * i22;
+        v[j + 1] = fma(-v[j], l21, v[j + 1]) * rd;
 #pragma unroll
         for (int k = j + 2; k < 16; k++) {
           v[k] = fma(-v[j + 1], read_lane(v[j + 1], k), fma(-v[j], read_lane(v[j], k), v[k]));
