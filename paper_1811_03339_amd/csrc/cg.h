@@ -10,9 +10,17 @@ struct CgState {
   double rz[2];        // r.z of the even and of the odd iterations
   double be;           // r.z over the one before, of the running iteration
   double bn2, rr, rt;  // b.b; r.r; true residual squared
-  int32_t done;        // 0: running, 1: ended (converged or not a number), 2: not positive definite
+  int64_t end;         // number of the launch that ended the loop, INT64_MAX: it runs
+  int32_t done;        // how: 1: converged or not a number, 2: not positive definite
   int32_t it;
 };
+
+// Launches are numbered: 2 it is iteration it's product, 2 it + 1 what follows it.
+// One that decides the end leaves its own number; a launch has nothing to do when
+// an earlier one has ended the loop.  So whether a wavefront reads the word before
+// or after a decision of its own launch makes no difference, and every wavefront
+// of the launch goes the same way.
+__device__ __forceinline__ bool cg_over(const CgState *st, int64_t launch) { return st->end < launch; }
 
 // The product of iteration `it` of the loop (st null: a plain product y = K x).
 // x is the direction of the iteration before; the new one, z + be x, is taken on
@@ -42,7 +50,7 @@ __device__ __forceinline__ double sum_parts(const double *__restrict__ part, int
 // In every thread of a workgroup of 256 (red: 4 doubles); the first workgroup
 // leaves it in the state.
 __device__ __forceinline__ bool cg_ended(const CgStep &c, double &be, double *red, bool first_block) {
-  if (c.st->done) return true;
+  if (cg_over(c.st, 2 * (int64_t)c.it)) return true;
   be = 0.0;
   if (c.it == 0) return false;
   const int odd = (c.it - 1) & 1;
@@ -54,7 +62,10 @@ __device__ __forceinline__ bool cg_ended(const CgStep &c, double &be, double *re
     c.st->it = c.it;
     c.st->rz[odd ^ 1] = rz;
     c.st->be = be;
-    if (end) c.st->done = 1;
+    if (end) {
+      c.st->done = 1;
+      c.st->end = 2 * (int64_t)c.it;
+    }
   }
   return end;
 }

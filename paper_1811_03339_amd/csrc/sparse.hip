@@ -148,7 +148,7 @@ __global__ void k_csr_diag(const int64_t *__restrict__ row_ptr, const int32_t *_
 // itself, in the same order, so that all agree without a launch in between.
 // An iteration is two launches (direction and product with p.q; update with r.r
 // and r.z; matrix-free one more, the row pass).  The host queues iterations a few at a time and looks at the
-// state of the chunk before; what is queued past the end finds `done` set and
+// state of the chunk before; what is queued past the end finds it in the state and
 // does nothing.  (With three dot products per iteration read back by the host
 // an iteration took 200 us around a product of 12 us, with a launch of its own
 // for the direction 21 us; now 20 us.)
@@ -173,6 +173,7 @@ __device__ __forceinline__ void put_parts(double a, double b, double *__restrict
 }
 
 __global__ void k_cg_clear(CgState *st) {
+  st->end = INT64_MAX;
   st->done = 0;
   st->it = 0;
 }
@@ -209,6 +210,7 @@ __global__ void __launch_bounds__(256) k_cg_begin(CgState *st, double tol, const
     st->rz[0] = rz;
     st->rr = bb;
     if (st->done == 0 && !(bb > 0.0 && 1.0 > tol)) st->done = 1;
+    if (st->done) st->end = -1;
   }
 }
 
@@ -216,16 +218,20 @@ __global__ void __launch_bounds__(256) k_cg_begin(CgState *st, double tol, const
 __global__ void __launch_bounds__(256) k_cg_update(double *__restrict__ u, double *__restrict__ r,
                                                    double *__restrict__ z, const double *__restrict__ p,
                                                    const double *__restrict__ q, const double *__restrict__ dinv,
-                                                   int64_t n, CgState *st, int odd, const double *__restrict__ pq_part,
+                                                   int64_t n, CgState *st, int it, const double *__restrict__ pq_part,
                                                    int npq, double *__restrict__ part) {
   __shared__ double red[8];
-  if (st->done) return;
+  const int64_t launch = 2 * (int64_t)it + 1;
+  if (cg_over(st, launch)) return;
   const double pq = sum_parts(pq_part, npq, 1, red);
   if (!(pq > 0.0)) {  // the same in every workgroup
-    if (blockIdx.x == 0 && threadIdx.x == 0) st->done = 2;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+      st->done = 2;
+      st->end = launch;
+    }
     return;
   }
-  const double al = st->rz[odd] / pq;
+  const double al = st->rz[it & 1] / pq;
   double rr = 0.0, rz = 0.0;
   for (int64_t k = (int64_t)blockIdx.x * 256 + threadIdx.x; k < n; k += (int64_t)gridDim.x * 256) {
     u[k] = fma(al, p[k], u[k]);
@@ -452,7 +458,7 @@ extern "C" int fpde_cg_solve(fpde_mesh *m, const fpde_params *p, const int64_t *
       c.it = queued;
       c.pn = w.p[(queued + 1) & 1];
       FPDE_TRY(op(w.p[queued & 1], w.q, c));
-      k_cg_update<<<vb, 256, 0, s>>>(u, w.r, w.z, c.pn, w.q, w.dinv, n, w.st, queued & 1, w.op_part,
+      k_cg_update<<<vb, 256, 0, s>>>(u, w.r, w.z, c.pn, w.q, w.dinv, n, w.st, queued, w.op_part,
                                      (int)op_blocks(n, true), w.part);
     }
     if (queued == max_iter) {

@@ -1101,7 +1101,7 @@ __global__ void __launch_bounds__(256) k_tube_sum(const int64_t *__restrict__ ro
                                                   const double *__restrict__ part, int64_t ndof,
                                                   double *__restrict__ y, const double *__restrict__ x, CgStep c) {
   __shared__ double red[4];
-  if (c.st && c.st->done) return;
+  if (c.st && cg_over(c.st, 2 * (int64_t)c.it + 1)) return;
   const double be = c.st ? c.st->be : 0.0;  // by k_tube_apply
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   double xy = 0.0;
