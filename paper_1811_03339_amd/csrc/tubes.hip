@@ -135,7 +135,9 @@ __global__ void k_pair_meta(const int32_t *__restrict__ pair_sorted, int64_t n, 
 __device__ __forceinline__ unsigned hash_slot(int32_t d) { return ((uint32_t)d * 2654435761u) >> (32 - 13); }
 
 // insert every node of the tube's entries into the LDS hash; returns through
-// `cnt` the number of distinct nodes (kMaxU + 1 on overflow)
+// `cnt` the number of distinct nodes, or more than kMaxU as soon as there are:
+// the table stays about half full (a full one would be probed all round by every
+// further node: minutes on a strip of 4 200 x 3 cells, whose chords have 8 400)
 __device__ void tube_insert(int32_t *hk, int *cnt, const int4 *__restrict__ pm, int64_t k0, int64_t k1,
                             const int32_t *__restrict__ ent_dof) {
   for (int j = threadIdx.x; j < kHash; j += blockDim.x) hk[j] = -1;
@@ -146,6 +148,10 @@ __device__ void tube_insert(int32_t *hk, int *cnt, const int4 *__restrict__ pm, 
     const int4 m = pm[k];
     const int nl = m.z, nr = m.w & 0x3fffffff;
     for (int e = lane; e < nl + nr; e += 64) {
+      if (*(volatile int *)cnt > kMaxU) {
+        k = k1;
+        break;
+      }
       const int32_t d = ent_dof[e < nl ? m.x + e : m.y + (e - nl)];
       unsigned h = hash_slot(d);
       for (int probe = 0; probe < kHash; probe++) {
