@@ -29,6 +29,7 @@
 //   solve         the dense FP64 Cholesky of the 3-D path.
 #include <hipcub/hipcub.hpp>
 
+#include <algorithm>
 #include <cmath>
 #include <vector>
 
@@ -456,6 +457,18 @@ __global__ void k2_i32_to_i64(const int32_t *__restrict__ a, int64_t n, int64_t 
   if (k < n) b[k] = a[k];
 }
 
+// v[n] (0 on entry) = the largest of v[0 .. n)
+__global__ void __launch_bounds__(256) k2_max(int32_t *__restrict__ v, int64_t n) {
+  int32_t x = 0;
+  for (int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; k < n; k += (int64_t)gridDim.x * blockDim.x)
+    x = v[k] > x ? v[k] : x;
+  for (int o = 32; o > 0; o >>= 1) {
+    const int32_t y = __shfl_xor(x, o, 64);
+    x = y > x ? y : x;
+  }
+  if ((threadIdx.x & 63) == 0) atomicMax(&v[n], x);
+}
+
 __global__ void k2_row_count(const int32_t *__restrict__ ent_dof, int64_t n, int64_t *__restrict__ cnt) {
   const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (e < n) atomicAdd((unsigned long long *)&cnt[ent_dof[e]], 1ull);
@@ -647,7 +660,9 @@ constexpr double kTubeCell2 = 0.25;
 // takes a row once per kChunk2 columns: on strips of 500 x 8 cells (1 000 nodes a
 // chord) 57 against 74 ms, of 1 000 x 3 cells (2 000 nodes) 275 against 159 ms,
 // one chunk each; 65 025 unknowns (square, 16 bands against 8 chunks) 0.23
-// against 5.0 s.
+// against 5.0 s.  Asked before the tubes are built too, with the entries of the
+// longest half-ray, about as many as nodes that are its tube's at least: tubes that
+// were then not used took 47 of the 125 ms of the first assembly of 1 000 x 3 cells.
 static bool tubes_pay(const fpde_mesh2d *m, int64_t max_u) {
   const int64_t bands = max_u * (max_u + 1) / 2 / 20160, chunks = (m->ndof + kChunk2 - 1) / kChunk2;
   return m->ndof > 128 && bands <= 32 * chunks;
@@ -719,6 +734,7 @@ static int build_plan2(fpde_mesh2d *m, Plan2 &P, int nq, int max_steps, hipStrea
   a.len = len;
   launch_walk2<W2_COUNT>(a, s);
   k2_i32_to_i64<<<nblk2(P.n_half + 1), 256, 0, s>>>(cnt, P.n_half + 1, cnt64);
+  k2_max<<<nblk2(std::min<int64_t>(P.n_half, 1 << 18)), 256, 0, s>>>(cnt, P.n_half);
   size_t tb = 0;
   if (hipcub::DeviceScan::ExclusiveSum(nullptr, tb, cnt64, P.off, (int)(P.n_half + 1), s) != hipSuccess)
     return fail(FPDE_EHIP);
@@ -730,7 +746,9 @@ static int build_plan2(fpde_mesh2d *m, Plan2 &P, int nq, int max_steps, hipStrea
     return fail(FPDE_EHIP);
   if ((st = plan_strips(P, soff, s)) != FPDE_OK) return fail(st);
   int64_t n_seg = 0;
-  if (hipMemcpyAsync(&n_seg, soff + P.n_half, sizeof(int64_t), hipMemcpyDeviceToHost, s) != hipSuccess ||
+  int32_t longest = 0;
+  if (hipMemcpyAsync(&longest, cnt + P.n_half, sizeof(int32_t), hipMemcpyDeviceToHost, s) != hipSuccess ||
+      hipMemcpyAsync(&n_seg, soff + P.n_half, sizeof(int64_t), hipMemcpyDeviceToHost, s) != hipSuccess ||
       hipMemcpyAsync(&P.n_ent, P.off + P.n_half, sizeof(int64_t), hipMemcpyDeviceToHost, s) != hipSuccess)
     return fail(FPDE_EHIP);
   int f = take_flag(m->ws, s);
@@ -752,8 +770,11 @@ static int build_plan2(fpde_mesh2d *m, Plan2 &P, int nq, int max_steps, hipStrea
   tmp = nullptr;
   // tubes with their block scratch, or the transpose where they do not fit
   const TubeGeom q{2, m->nv, m->nt, m->xy, m->tri, m->area, m->rules + rule2_offset(nq)};
-  st = build_tubes(m->ws, P, q, kTubeCell2, s);
-  const bool pay = st == FPDE_OK && tubes_pay(m, P.tubes.max_u);
+  bool pay = tubes_pay(m, longest);
+  if (pay) {
+    st = build_tubes(m->ws, P, q, kTubeCell2, s);
+    pay = st == FPDE_OK && tubes_pay(m, P.tubes.max_u);
+  }
   if (pay) st = dalloc(&P.tubes.blk, P.tubes.blk_n);
   if (!pay || st != FPDE_OK) {
     if (st != FPDE_OK && st != FPDE_EUNSUPPORTED && st != FPDE_ENOMEM) return fail(st);

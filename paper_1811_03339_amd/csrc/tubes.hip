@@ -168,7 +168,11 @@ __device__ void tube_insert(int32_t *hk, int *cnt, const int4 *__restrict__ pm, 
   __syncthreads();
 }
 
-__global__ void __launch_bounds__(256) k_tube_count(const int64_t *__restrict__ tube_off, const int4 *__restrict__ pm,
+// threads of a tube's count and fill: few tubes of many nodes leave the chip to
+// one workgroup per tube
+constexpr int kPlanThreads = 1024;
+
+__global__ void __launch_bounds__(kPlanThreads) k_tube_count(const int64_t *__restrict__ tube_off, const int4 *__restrict__ pm,
                                                     const int32_t *__restrict__ ent_dof, int64_t *__restrict__ u_cnt,
                                                     int32_t *flag) {
   __shared__ int32_t hk[kHash];
@@ -182,7 +186,7 @@ __global__ void __launch_bounds__(256) k_tube_count(const int64_t *__restrict__ 
 }
 
 // U_T sorted, the slot of every entry, and per-row counts of (tube, slot) places
-__global__ void __launch_bounds__(256) k_tube_fill(const int64_t *__restrict__ tube_off, const int4 *__restrict__ pm,
+__global__ void __launch_bounds__(kPlanThreads) k_tube_fill(const int64_t *__restrict__ tube_off, const int4 *__restrict__ pm,
                                                    const int32_t *__restrict__ ent_dof,
                                                    const int64_t *__restrict__ u_off, int32_t *__restrict__ tube_u,
                                                    int32_t *__restrict__ ent_slot, int64_t *__restrict__ row_cnt) {
@@ -1432,7 +1436,7 @@ int build_tubes(fpde_mesh *m, Plan &P, const TubeGeom &q, double kappa, hipStrea
   TRY_T(dalloc(&u_cnt, nT + 1));
   TRY_T(dalloc(&tp.u_off, nT + 1));
   HIP_T(hipMemsetAsync(u_cnt, 0, sizeof(int64_t) * (nT + 1), s));
-  k_tube_count<<<(unsigned)nT, 256, 0, s>>>(tp.tube_off, tp.pm, P.ent_dof, u_cnt, m->flag);
+  k_tube_count<<<(unsigned)nT, kPlanThreads, 0, s>>>(tp.tube_off, tp.pm, P.ent_dof, u_cnt, m->flag);
   int f = take_flag(m, s);
   if (f != 0) return fail(f < 0 ? f : FPDE_EHIP);
   HIP_T(hipcub::DeviceScan::ExclusiveSum(nullptr, need, u_cnt, tp.u_off, (int)(nT + 1), s));
@@ -1444,7 +1448,7 @@ int build_tubes(fpde_mesh *m, Plan &P, const TubeGeom &q, double kappa, hipStrea
   TRY_T(dalloc(&tp.ent_slot, P.n_ent));
   TRY_T(dalloc(&row_cnt, m->ndof + 1));
   HIP_T(hipMemsetAsync(row_cnt, 0, sizeof(int64_t) * (m->ndof + 1), s));
-  k_tube_fill<<<(unsigned)nT, 256, 0, s>>>(tp.tube_off, tp.pm, P.ent_dof, tp.u_off, tp.tube_u, tp.ent_slot, row_cnt);
+  k_tube_fill<<<(unsigned)nT, kPlanThreads, 0, s>>>(tp.tube_off, tp.pm, P.ent_dof, tp.u_off, tp.tube_u, tp.ent_slot, row_cnt);
   TRY_T(dalloc(&tp.row_off, m->ndof + 1));
   HIP_T(hipcub::DeviceScan::ExclusiveSum(nullptr, need, row_cnt, tp.row_off, (int)(m->ndof + 1), s));
   TRY_T(scratch(need));
