@@ -40,7 +40,7 @@ inline int rule_offset(int nq) { return nq == 4 ? 0 : 4 * 5; }
 // x_g in the plane orthogonal to e_i; U_T = the tube's nodes (sorted).
 struct TubePlan {
   double cell = 0.0;              // cell edge
-  int64_t n_tubes = 0, n_u = 0, n_items = 0, blk_n = 0, max_u = 0;
+  int64_t n_tubes = 0, n_u = 0, n_items = 0, n_fitems = 0, blk_n = 0, max_u = 0;
   int32_t *pair_sorted = nullptr; // 3 G pair ids i * G + g, tube by tube
   int4 *pm = nullptr;             // per sorted pair {l first entry, r first entry, |l|, |r| | axis << 30}
   double *pw = nullptr;           // per sorted pair: w_g
@@ -51,6 +51,7 @@ struct TubePlan {
   int64_t *row_off = nullptr;     // n_dof + 1 into row_ts
   int2 *row_ts = nullptr;         // n_u: (tube, slot) places of each node, grouped by node
   int4 *items = nullptr;          // pass-1 work: {tube, first block row, rows, |U_T|}
+  int4 *fitems = nullptr;         // the same for the general form, full rows all of them
   int64_t *blk_off = nullptr;     // n_tubes + 1: offsets (doubles) of the |U_T|^2 blocks
   double *blk = nullptr;          // blk_n doubles of block scratch, allocated on first use
   int32_t *cstart = nullptr;      // row pass: per tube, the first U_T position of every column chunk

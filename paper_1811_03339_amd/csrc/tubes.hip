@@ -20,8 +20,9 @@
 //     to a scratch block in HBM.  The block is symmetric, B = S + S^T with
 //     S = sum w l r^T, so each product of S is added once, at (min, max), and
 //     expanded as it is written: in the full square for |U_T| <= 141, the
-//     packed upper triangle for |U_T| <= 200, else bands of rows of that
-//     triangle.  Two assemblies of 82 924 elements (4 points, chords of 44
+//     packed upper triangle for |U_T| <= 200, else a few bands of rows of that
+//     triangle; larger blocks, and those of few heavy tubes, go in bands of full
+//     rows that take both products.  Two assemblies of 82 924 elements (4 points, chords of 44
 //     entries, up to 240 nodes a tube) took 9.5 ms with one row entry per lane
 //     and larger tubes in bands of full rows that took both products, and take
 //     3.0 ms; of 19 672 elements (11 points, 25 entries) 1.96 and 0.64 ms;
@@ -52,6 +53,19 @@ constexpr int kMaxU = kHash / 2;    // largest node set a tube may have
 // 0.85 ms against 0.81 ms on 19 672 (11 points), two assemblies each.
 constexpr int kBand = 20160;
 constexpr int kAccumThreads = 1024;
+// Work items of the two pass-1 kernels.  A block goes in bands of the triangle (each
+// product once, but every band meets all of them) up to kTriBands bands, and in
+// bands of full rows (both products, but a band collects its own rows first) beyond,
+// or when its tube has more of the whole work than one of kShares CUs: then in as
+// many bands as it has shares, of at least kMinRows rows.  A tube's work is taken as
+// pairs x nodes^2; tubes of kSplitFrom nodes are too little to split.
+// Triangle against rows, one assembly: many tubes of 312 nodes (64 000 cubes, 3
+// bands) 29.7 / 30.8 ms, 408 (52 x 24 x 24 cubes, 5 bands) 10.0 / 10.6 ms; few of 792
+// (100 x 8 x 8) 6.2 / 4.1 ms, 1 596 (3 x 3 x 400) 64 / 12.8 ms.  Bars of 3 x 3 x 60 /
+// 150 cells: one item per band 0.59 / 4.5 ms, with the shares 0.28 / 1.30 ms (kShares
+// 128 / 512: 1.47 / 1.57 ms); general form 1.7 / 54 ms, now 0.35 / 1.8 ms.
+constexpr int kShares = 256, kMinRows = 8, kSplitFrom = 64;
+constexpr int64_t kTriBands = 5;
 
 // row stride of a band in LDS: odd, so the rows of one column fall in distinct bank pairs
 __host__ __device__ inline int band_stride(int U) { return U | 1; }
@@ -63,6 +77,7 @@ inline int band_rows(int U, int r0, int band) {
   while (r0 + R < U && room >= U - r0 - R) room -= U - r0 - R++;
   return R;
 }
+constexpr int kFullRows = 1 << 30;  // item: full rows (with R in z), not rows of the triangle
 
 // position of (lo, hi), lo <= hi, in the row-packed upper triangle of a
 // U x U block: tri_base(lo, U) + hi
@@ -417,8 +432,8 @@ struct Band {
   int U, Up, r0, R, off;  // off: bytes of the triangle before row r0
 };
 
-// tile column t of a step with NI chunks of 16 rows, then the next one
-template <int LAYOUT, int NI, int t>
+// tile column t of a step with NCH chunks of 16 rows, then the next one
+template <int LAYOUT, int NCH, int t>
 __device__ __forceinline__ void step_columns(const Band &b, const PairStep &p, double cvw) {
   if (4 * t >= p.nc) return;
   const int lane = threadIdx.x & 63;
@@ -426,7 +441,7 @@ __device__ __forceinline__ void step_columns(const Band &b, const PairStep &p, d
   const double cv = group_lane<t>(cvw);
   const bool cok = 4 * t + (lane >> 4) < p.nc;
 #pragma unroll
-  for (int i = 0; i < NI; i++) {
+  for (int i = 0; i < NCH; i++) {
     const int x = p.rs[i];
     bool ok = cok && 16 * i + (lane & 15) < p.nr;
     int at;
@@ -445,7 +460,7 @@ __device__ __forceinline__ void step_columns(const Band &b, const PairStep &p, d
     }
     if (ok) atomicAdd((double *)(b.acc + at), p.rv[i] * cv);
   }
-  if constexpr (t < 15) step_columns<LAYOUT, NI, t + 1>(b, p, cvw);
+  if constexpr (t < 15) step_columns<LAYOUT, NCH, t + 1>(b, p, cvw);
 }
 
 template <int LAYOUT>
@@ -495,29 +510,127 @@ __device__ __forceinline__ void band_products(double *acc, int U, int Up, int r0
   }
 }
 
+// lane q + rank of the set lanes gets the rank-th set lane's v (all 64 lanes take
+// part: the others follow behind, so that to[] is a permutation of the wavefront)
+__device__ __forceinline__ int push_lane(int to, int v) { return __builtin_amdgcn_ds_permute(4 * to, v); }
+__device__ __forceinline__ double push_lane(int to, double v) {
+  return __hiloint2double(push_lane(to, __double2hiint(v)), push_lane(to, __double2loint(v)));
+}
+
+// Every pair of [k0, k1) into block rows [r0, r0 + R), both products: the entries
+// of a half-ray that stand in these rows are collected first, up to 64 in the
+// wavefront's registers, then multiplied by every entry of the other side.  For
+// bands of few rows: bound by the products (LDS updates); with every product tried
+// against the band, as band_products does, 3 x 3 x 400 cells took 200 times as long.
+__device__ __forceinline__ void row_products(double *acc, int U, int Up, int r0, int R, const AccumArgs &a,
+                                             const double *__restrict__ vrow, const double *__restrict__ vcol,
+                                             double kc0, double kc1, int64_t k0, int64_t k1) {
+  const int lane = threadIdx.x & 63, nw = blockDim.x >> 6;
+  const int32_t *__restrict__ slot = a.ent_slot;
+  const Band b = {(char *)acc, U, Up, r0, R, 0};
+  for (int64_t k = k0 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); k < k1; k += nw) {
+    const int4 m = a.pm[k];
+    const int nl = pair_nl(m), nr = pair_nr(m);
+    double w0 = a.pw[k] * kc0, w1 = a.pw[k] * kc1;
+    if (a.coef) {
+      const int64_t id = a.pair[k];
+      w0 *= a.coef[a.ncoef + id];
+      w1 *= a.coef[id];
+    }
+#pragma unroll 1
+    for (int role = 0; role < 2; role++) {
+      const int erow = role ? m.y : m.x, ecol = role ? m.x : m.y;
+      const int nrow = role ? nr : nl, ncol = role ? nl : nr;
+      if (ncol == 0) continue;
+      const double w = role ? w1 : w0;
+      int qn = 0, qs = 0;  // the rows collected: lanes 0 .. qn - 1
+      double qv = 0.0;
+      auto flush = [&]() {
+        PairStep p;
+        p.nr = qn;
+#pragma unroll
+        for (int i = 0; i < 4; i++) {
+          p.rs[i] = __shfl(qs, 16 * i + (lane & 15), 64) * 8;
+          p.rv[i] = __shfl(qv, 16 * i + (lane & 15), 64);
+        }
+        const int at = 4 * (lane & 15) + (lane >> 4);
+        int ec = side_entry(ecol, ncol, at);
+        int cs = slot[ec];
+        double cv = vcol[ec];
+        for (int cb = 0; cb < ncol; cb += kStep) {
+          p.nc = ncol - cb < kStep ? ncol - cb : kStep;
+          p.cs = cs * 8;
+          p.cv = cv;
+          p.w = w;
+          ec = side_entry(ecol, ncol, cb + kStep + at);
+          cs = slot[ec];
+          cv = vcol[ec];
+          step_products<kFull>(b, p);
+        }
+      };
+      int sn = slot[side_entry(erow, nrow, lane)];
+      for (int j0 = 0; j0 < nrow; j0 += 64) {
+        const int s = sn;
+        sn = slot[side_entry(erow, nrow, j0 + 64 + lane)];
+        const bool in = j0 + lane < nrow && (unsigned)(s - r0) < (unsigned)R;
+        const uint64_t bal = __ballot(in);
+        if (bal == 0) continue;
+        const double v = vrow[side_entry(erow, nrow, j0 + lane)];
+        const int cnt = __popcll(bal);
+        const int rank = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(bal >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)bal, 0u));
+        const int to = (in ? qn + rank : qn + cnt + lane - rank) & 63;
+        const int ms = push_lane(to, s);
+        const double mv = push_lane(to, v);
+        if (lane >= qn) {
+          qs = ms;
+          qv = mv;
+        }
+        qn += cnt;
+        if (qn >= 64) {
+          const int over = qn - 64;
+          qn = 64;
+          flush();
+          qn = over;  // the rest came round to the first lanes
+          qs = ms;
+          qv = mv;
+        }
+      }
+      if (qn > 0) flush();
+    }
+  }
+}
+
 __global__ void __launch_bounds__(kAccumThreads) k_tube_accum(AccumArgs a) {
   extern __shared__ double acc[];
   const int4 it = a.items[blockIdx.x];
   const int64_t T = it.x;
-  const int r0 = it.y, R = it.z, U = it.w, Up = band_stride(U);
+  const int r0 = it.y, R = it.z & ~kFullRows, U = it.w, Up = band_stride(U);
   // B = S + S^T with S = sum_p w_p l_p r_p^T: each product of S once, at
   // (min, max), half the LDS updates of the two products, in the full square
   // when it fits (no bank conflicts and the cheaper address), else in the
-  // packed triangle or rows of it
-  const bool square = R == U && U * Up <= kBand;
-  const int tri0 = tri_base(r0, U) + r0, nacc = square ? U * Up : tri_base(r0 + R, U) + r0 + R - tri0;
+  // packed triangle or half of it; larger blocks by full rows
+  const bool full = it.z & kFullRows, square = R == U && U * Up <= kBand;
+  const int tri0 = tri_base(r0, U) + r0;
+  const int nacc = square || full ? R * Up : tri_base(r0 + R, U) + r0 + R - tri0;
   for (int j = threadIdx.x; j < nacc; j += blockDim.x) acc[j] = 0.0;
   __syncthreads();
   const int64_t k0 = a.tube_off[T], k1 = a.tube_off[T + 1];
   const int axis = (int)((unsigned)a.pm[k0].w >> 30);  // a tube has at least one pair
   const double kc = axis == 0 ? a.KC0 : (axis == 1 ? a.KC1 : a.KC2);
-  if (square) band_products<kSquare>(acc, U, Up, r0, R, a, a.ent_val, a.ent_val, kc, kc, k0, k1);
+  if (full && 3 * R >= U) band_products<kFull>(acc, U, Up, r0, R, a, a.ent_val, a.ent_val, kc, kc, k0, k1);
+  else if (full) row_products(acc, U, Up, r0, R, a, a.ent_val, a.ent_val, kc, kc, k0, k1);
+  else if (square) band_products<kSquare>(acc, U, Up, r0, R, a, a.ent_val, a.ent_val, kc, kc, k0, k1);
   else if (R == U) band_products<kTri>(acc, U, Up, r0, R, a, a.ent_val, a.ent_val, kc, kc, k0, k1);
   else band_products<kTriBand>(acc, U, Up, r0, R, a, a.ent_val, a.ent_val, kc, kc, k0, k1);
   __syncthreads();
-  // every entry whose smaller index lies in the band, one wavefront per row
   const int lane = threadIdx.x & 63;
   double *blk = a.blk + a.blk_off[T];
+  if (full) {
+    for (int i = threadIdx.x >> 6; i < R; i += blockDim.x >> 6)
+      for (int t = lane; t < U; t += 64) blk[(int64_t)(r0 + i) * U + t] = acc[i * Up + t];
+    return;
+  }
+  // every entry whose smaller index lies in the band, one wavefront per row
   for (int i = r0 + (threadIdx.x >> 6); i < U; i += blockDim.x >> 6) {
     double *out = blk + (int64_t)i * U;
     const int t1 = i < r0 + R ? U : r0 + R;
@@ -535,32 +648,25 @@ __global__ void __launch_bounds__(kAccumThreads) k_tube_accum(AccumArgs a) {
 // values at orders beta (a.val_b),
 //   B[k][l] += w cl_i r_beta[k] l_alpha[l] + w cr_i l_beta[k] r_alpha[l]
 // (rows: test node, columns: trial node).  Not symmetric, so both products
-// of every pair go into full rows; an item is processed in row bands that
-// fit the square layout, the pairs re-read per band.
+// of every pair go into full rows.
 __global__ void __launch_bounds__(kAccumThreads) k_tube_form(AccumArgs a) {
   extern __shared__ double acc[];
   const int4 it = a.items[blockIdx.x];
   const int64_t T = it.x;
   const int r0 = it.y, R = it.z, U = it.w, Up = band_stride(U);
-  const int Rsq = kBand / Up;  // rows of one square band
-  const int lane = threadIdx.x & 63;
   const int64_t k0 = a.tube_off[T], k1 = a.tube_off[T + 1];
   // role 0: rows l (beta), columns r (alpha, cr); role 1: rows r, columns l (cl)
   const int axis = (int)((unsigned)a.pm[k0].w >> 30);
   const double kc0 = a.coef ? 1.0 : (axis == 0 ? a.cr0 : (axis == 1 ? a.cr1 : a.cr2));
   const double kc1 = a.coef ? 1.0 : (axis == 0 ? a.cl0 : (axis == 1 ? a.cl1 : a.cl2));
-  for (int rb = r0; rb < r0 + R; rb += Rsq) {
-    const int Rb = (r0 + R - rb) < Rsq ? (r0 + R - rb) : Rsq;
-    for (int j = threadIdx.x; j < Rb * Up; j += blockDim.x) acc[j] = 0.0;
-    __syncthreads();
-    band_products<kFull>(acc, U, Up, rb, Rb, a, a.val_b, a.ent_val, kc0, kc1, k0, k1);
-    __syncthreads();
-    for (int i = threadIdx.x >> 6; i < Rb; i += blockDim.x >> 6) {
-      double *out = a.blk + a.blk_off[T] + (int64_t)(rb + i) * U;
-      for (int t = lane; t < U; t += 64) out[t] = acc[i * Up + t];
-    }
-    __syncthreads();  // the band is written before the next one is cleared
-  }
+  for (int j = threadIdx.x; j < R * Up; j += blockDim.x) acc[j] = 0.0;
+  __syncthreads();
+  if (3 * R >= U) band_products<kFull>(acc, U, Up, r0, R, a, a.val_b, a.ent_val, kc0, kc1, k0, k1);
+  else row_products(acc, U, Up, r0, R, a, a.val_b, a.ent_val, kc0, kc1, k0, k1);
+  __syncthreads();
+  double *out = a.blk + a.blk_off[T] + (int64_t)r0 * U;
+  for (int i = threadIdx.x >> 6; i < R; i += blockDim.x >> 6)
+    for (int t = threadIdx.x & 63; t < U; t += 64) out[(int64_t)i * U + t] = acc[i * Up + t];
 }
 
 struct GatherArgs {
@@ -1331,7 +1437,7 @@ __global__ void __launch_bounds__(kTubeThreads) k_tube_mfma(TubeMfmaArgs a, cons
 
 void free_tubes(TubePlan &tp) {
   dfree(tp.pair_sorted); dfree(tp.pm); dfree(tp.pw); dfree(tp.tube_off); dfree(tp.u_off); dfree(tp.tube_u); dfree(tp.ent_slot);
-  dfree(tp.row_off); dfree(tp.row_ts); dfree(tp.items); dfree(tp.blk_off); dfree(tp.blk);
+  dfree(tp.row_off); dfree(tp.row_ts); dfree(tp.items); dfree(tp.fitems); dfree(tp.blk_off); dfree(tp.blk);
   dfree(tp.mitems); dfree(tp.texp);
   dfree(tp.mk_pair); dfree(tp.mk_meta); dfree(tp.mk_val); dfree(tp.mg_idx); dfree(tp.pk_tube);
   dfree(tp.cstart);
@@ -1480,21 +1586,37 @@ int build_tubes(fpde_mesh *m, Plan &P, const TubeGeom &q, double kappa, hipStrea
     std::stable_sort(order.begin(), order.end(), [&](int64_t x, int64_t y) {
       return (to[x + 1] - to[x]) * (uo[x + 1] - uo[x]) > (to[y + 1] - to[y]) * (uo[y + 1] - uo[y]);
     });
-    std::vector<int4> items;
+    double work = 0.0;
+    auto weight = [&](int64_t T) {
+      const double U = (double)(uo[T + 1] - uo[T]);
+      return (double)(to[T + 1] - to[T]) * U * U;
+    };
+    for (int64_t T = 0; T < nT; T++) work += weight(T);
+    std::vector<int4> items, fitems;
     for (const int64_t T : order) {
       const int U = (int)(uo[T + 1] - uo[T]);
+      if (U == 0) continue;
+      const int64_t bands = ((int64_t)U * (U + 1) / 2 + kBand - 1) / kBand;
+      const double share = U <= kSplitFrom ? 0.0 : weight(T) * kShares / work;
+      const int parts = std::max(1, (int)share);
+      const int R = std::min({U, kBand / band_stride(U), std::max(kMinRows, (U + parts - 1) / parts)});
+      for (int r0 = 0; r0 < U; r0 += R) fitems.push_back(make_int4((int)T, r0, std::min(R, U - r0), U));
+      const bool full = bands > kTriBands || (bands > 1 && share >= 1.0) || share >= 4.0;
       for (int r0 = 0; r0 < U;) {
-        const int R = band_rows(U, r0, kBand);
-        items.push_back(make_int4((int)T, r0, R, U));
-        r0 += R;
+        const int r = full ? std::min(R, U - r0) : band_rows(U, r0, kBand);
+        items.push_back(make_int4((int)T, r0, full ? r | kFullRows : r, U));
+        r0 += r;
       }
     }
-    tp.n_items = (int64_t)items.size();
-    TRY_T(dalloc(&tp.items, items.size() > 0 ? items.size() : 1));
-    if (!items.empty()) {
-      HIP_T(hipMemcpyAsync(tp.items, items.data(), sizeof(int4) * items.size(), hipMemcpyHostToDevice, s));
-      HIP_T(hipStreamSynchronize(s));
-    }
+    auto upload = [&](const std::vector<int4> &v, int4 **p, int64_t *count) -> int {
+      *count = (int64_t)v.size();
+      FPDE_TRY(dalloc(p, v.size()));
+      if (!v.empty()) FPDE_HIP(hipMemcpyAsync(*p, v.data(), sizeof(int4) * v.size(), hipMemcpyHostToDevice, s));
+      FPDE_HIP(hipStreamSynchronize(s));
+      return FPDE_OK;
+    };
+    TRY_T(upload(items, &tp.items, &tp.n_items));
+    TRY_T(upload(fitems, &tp.fitems, &tp.n_fitems));
   }
   // Segments of the matrix-free product: at most kSegMax pairs, fewer on small
   // meshes so that there are a few thousand, in multiples of the 16 groups of
@@ -1803,7 +1925,7 @@ int launch_form_tubes(fpde_mesh *m, Plan &P, const double cl[3], const double cr
   a.tube_off = tp.tube_off;
   a.pm = tp.pm;
   a.pw = tp.pw;
-  a.items = tp.items;
+  a.items = tp.fitems;
   a.ent_slot = tp.ent_slot;
   a.ent_val = P.ent_val;
   a.val_b = P.ent_val2;
@@ -1818,7 +1940,7 @@ int launch_form_tubes(fpde_mesh *m, Plan &P, const double cl[3], const double cr
   a.pair = tp.pair_sorted;
   a.coef = coef;
   a.ncoef = 3 * P.G;
-  if (tp.n_items > 0) k_tube_form<<<(unsigned)tp.n_items, kAccumThreads, sizeof(double) * kBand, s>>>(a);
+  if (tp.n_fitems > 0) k_tube_form<<<(unsigned)tp.n_fitems, kAccumThreads, sizeof(double) * kBand, s>>>(a);
   GatherArgs gch;
   FPDE_TRY(gather_args(m, P, lda, s, gch));
   k_tube_gather<double><<<gather_grid(m->ndof), 256, sizeof(double) * gch.chunk, s>>>(gch, A);
