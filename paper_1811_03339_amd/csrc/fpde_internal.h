@@ -36,6 +36,8 @@ int quad_rule(int nq, QuadRule *out);  // FPDE_OK or FPDE_EINVAL
 // offset of the nq-point table inside fpde_mesh::rules
 inline int rule_offset(int nq) { return nq == 4 ? 0 : 4 * 5; }
 
+constexpr int kMaxTube = 4096;  // nodes that a tube may have
+
 // Tubes of the accumulation: pairs (g, i) grouped by axis i and the cell of
 // x_g in the plane orthogonal to e_i; U_T = the tube's nodes (sorted).
 struct TubePlan {

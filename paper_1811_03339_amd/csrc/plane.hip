@@ -653,20 +653,14 @@ static void launch_walk2(const Walk2Args &a, hipStream_t s) {
 // 7.8 / 7.0 / 6.4 / 6.3 ms (k2_rows: 74).
 constexpr double kTubeCell2 = 0.25;
 
-// Whether the tubes are used.  Their pass and the row pass are two launches: at
+// Whether the tubes are tried.  Their pass and the row pass are two launches: at
 // 73 unknowns 16 against 10 us (3 points) for k2_rows, at 225 unknowns 17
-// against 17 us, with 7 points 21 against 36.  A tube of U nodes takes
-// U (U + 1) / 2 / kBand bands, and each reads its entries again, while k2_rows
-// takes a row once per kChunk2 columns: on strips of 500 x 8 cells (1 000 nodes a
-// chord) 57 against 74 ms, of 1 000 x 3 cells (2 000 nodes) 275 against 159 ms,
-// one chunk each; 65 025 unknowns (square, 16 bands against 8 chunks) 0.23
-// against 5.0 s.  Asked before the tubes are built too, with the entries of the
-// longest half-ray, about as many as nodes that are its tube's at least: tubes that
-// were then not used took 47 of the 125 ms of the first assembly of 1 000 x 3 cells.
-static bool tubes_pay(const fpde_mesh2d *m, int64_t max_u) {
-  const int64_t bands = max_u * (max_u + 1) / 2 / 20160, chunks = (m->ndof + kChunk2 - 1) / kChunk2;
-  return m->ndof > 128 && bands <= 32 * chunks;
-}
+// against 17 us, with 7 points 21 against 36.  Beyond, they are faster wherever they
+// fit (one assembly): 4 x 250 cells (7 points) 1 against 6 ms, 8 x 500 11 against
+// 74 ms, 3 x 2 000 (3 points, 3 998 nodes a chord) 116 against 439 ms, 200 x 200
+// (7 points) 51 against 1 184 ms.  The entries of the longest half-ray are about as
+// many nodes, which its tube has at least.
+static bool tubes_pay(const fpde_mesh2d *m, int64_t longest) { return m->ndof > 128 && longest <= kMaxTube; }
 
 // node -> entry transpose of the row accumulation
 static int build_rows2(fpde_mesh2d *m, Plan2 &P, hipStream_t s) {
@@ -770,12 +764,9 @@ static int build_plan2(fpde_mesh2d *m, Plan2 &P, int nq, int max_steps, hipStrea
   tmp = nullptr;
   // tubes with their block scratch, or the transpose where they do not fit
   const TubeGeom q{2, m->nv, m->nt, m->xy, m->tri, m->area, m->rules + rule2_offset(nq)};
-  bool pay = tubes_pay(m, longest);
-  if (pay) {
-    st = build_tubes(m->ws, P, q, kTubeCell2, s);
-    pay = st == FPDE_OK && tubes_pay(m, P.tubes.max_u);
-  }
-  if (pay) st = dalloc(&P.tubes.blk, P.tubes.blk_n);
+  const bool pay = tubes_pay(m, longest);
+  if (pay) st = build_tubes(m->ws, P, q, kTubeCell2, s);
+  if (pay && st == FPDE_OK) st = dalloc(&P.tubes.blk, P.tubes.blk_n);
   if (!pay || st != FPDE_OK) {
     if (st != FPDE_OK && st != FPDE_EUNSUPPORTED && st != FPDE_ENOMEM) return fail(st);
     free_tubes(P.tubes);

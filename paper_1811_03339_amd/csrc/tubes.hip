@@ -44,8 +44,8 @@ namespace fpde {
 
 namespace {
 
-constexpr int kHash = 8192;         // LDS hash slots per tube (int32 keys)
-constexpr int kMaxU = kHash / 2;    // largest node set a tube may have
+constexpr int kHash = 2 * kMaxTube;  // LDS hash slots per tube (int32 keys)
+static_assert(kHash == 1 << 13, "hash_slot");
 // Pass 1: LDS doubles of a band (157.5 KB: the packed triangle of |U_T| <= 200)
 // and threads of its workgroup, one per CU.  The pass waits on its entry loads,
 // so what counts is wavefronts per band: bands of 79 KB, two workgroups of 512
@@ -150,7 +150,7 @@ __global__ void k_pair_meta(const int32_t *__restrict__ pair_sorted, int64_t n, 
 __device__ __forceinline__ unsigned hash_slot(int32_t d) { return ((uint32_t)d * 2654435761u) >> (32 - 13); }
 
 // insert every node of the tube's entries into the LDS hash; returns through
-// `cnt` the number of distinct nodes, or more than kMaxU as soon as there are:
+// `cnt` the number of distinct nodes, or more than kMaxTube as soon as there are:
 // the table stays about half full (a full one would be probed all round by every
 // further node: minutes on a strip of 4 200 x 3 cells, whose chords have 8 400)
 __device__ void tube_insert(int32_t *hk, int *cnt, const int4 *__restrict__ pm, int64_t k0, int64_t k1,
@@ -163,7 +163,7 @@ __device__ void tube_insert(int32_t *hk, int *cnt, const int4 *__restrict__ pm, 
     const int4 m = pm[k];
     const int nl = m.z, nr = m.w & 0x3fffffff;
     for (int e = lane; e < nl + nr; e += 64) {
-      if (*(volatile int *)cnt > kMaxU) {
+      if (*(volatile int *)cnt > kMaxTube) {
         k = k1;
         break;
       }
@@ -196,7 +196,7 @@ __global__ void __launch_bounds__(kPlanThreads) k_tube_count(const int64_t *__re
   tube_insert(hk, &cnt, pm, tube_off[T], tube_off[T + 1], ent_dof);
   if (threadIdx.x == 0) {
     u_cnt[T] = cnt;
-    if (cnt > kMaxU) set_flag(flag, FPDE_EUNSUPPORTED);
+    if (cnt > kMaxTube) set_flag(flag, FPDE_EUNSUPPORTED);
   }
 }
 
@@ -206,7 +206,7 @@ __global__ void __launch_bounds__(kPlanThreads) k_tube_fill(const int64_t *__res
                                                    const int64_t *__restrict__ u_off, int32_t *__restrict__ tube_u,
                                                    int32_t *__restrict__ ent_slot, int64_t *__restrict__ row_cnt) {
   __shared__ int32_t hk[kHash];
-  __shared__ int32_t su[kMaxU];
+  __shared__ int32_t su[kMaxTube];
   __shared__ int cnt, cnt2;
   const int64_t T = blockIdx.x;
   const int64_t k0 = tube_off[T], k1 = tube_off[T + 1];
