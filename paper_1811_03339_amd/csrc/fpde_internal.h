@@ -41,7 +41,6 @@ constexpr int kMaxTube = 4096;  // nodes that a tube may have
 // Tubes of the accumulation: pairs (g, i) grouped by axis i and the cell of
 // x_g in the plane orthogonal to e_i; U_T = the tube's nodes (sorted).
 struct TubePlan {
-  double cell = 0.0;              // cell edge
   int64_t n_tubes = 0, n_u = 0, n_items = 0, n_fitems = 0, blk_n = 0, max_u = 0;
   int32_t *pair_sorted = nullptr; // 3 G pair ids i * G + g, tube by tube
   int4 *pm = nullptr;             // per sorted pair {l first entry, r first entry, |l|, |r| | axis << 30}
@@ -231,7 +230,7 @@ inline void invalidate_values(Plan *P) {
 }
 int check_params(const fpde_mesh *m, const fpde_params *p);
 void free_plan(Plan &P);
-// tube plan of a rule whose entries exist (cell edge = kappa x mean element edge)
+// tube plan of a rule whose entries exist (cell edges = kappa x mean element edge)
 // Mesh and rule of a plan's pairs (all device): vertex coordinates, elements of
 // dim + 1 vertices, their volumes, and the rule's nq x (dim + 1) barycentric
 // coordinates followed by its weights.

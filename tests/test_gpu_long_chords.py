@@ -28,9 +28,12 @@ def strip(nx, ny):
 
 @pytest.mark.parametrize("cells", [100, 150])
 def test_plan_of_a_tube_with_too_many_nodes_is_refused(cells):
-    """Cells 1 000 times as long as wide: a tube takes in 8 x 8 rows of interior nodes."""
+    """Eight thin rows of cells beside a wide one in both directions across the
+    chords: a cell of the mean size takes in 8 x 8 rows of interior nodes."""
     xyz, tet = bar(cells, 9, 9)
-    gm = F.Mesh(xyz * np.array([1.0, 1e-3, 1e-3]), tet)
+    t = np.round(4.0 * xyz[:, 1:])
+    xyz[:, 1:] = 0.25 * np.where(t <= 8.0, 1e-3 * t, 8e-3 + 9.0 * (t - 8.0))
+    gm = F.Mesh(xyz, tet)
     with pytest.raises(F.FpdeError) as e:
         gm.plan(4)
     assert e.value.status == -11
