@@ -550,8 +550,9 @@ int fpde_paths2d(fpde_mesh2d *m, int quad_points, int dir, int64_t g0, int64_t c
 /*
  * K (dev, n_dof x lda FP64, leading block written) and b (dev, n_dof, may be
  * NULL); f_gauss: dev, n_tri * quad_points for FPDE_SRC_USER.  The symbolic
- * plan (paths, entry counts, node -> entry transpose) is built on first use
- * per rule.  Synchronises `stream`.
+ * plan (paths, entry counts, tubes or, for few unknowns or chords that do not
+ * fit them, the node -> entry transpose) is built on first use per rule.
+ * Synchronises `stream`.
  * Errors: FPDE_EINVAL, FPDE_EALPHA, FPDE_EPATH, FPDE_ENOMEM, FPDE_EHIP.
  */
 int fpde_assemble2d(fpde_mesh2d *m, const fpde_params2d *p, double *A, int64_t lda, double *b,

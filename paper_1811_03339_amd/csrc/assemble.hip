@@ -174,10 +174,10 @@ extern "C" int fpde_assemble_batch(fpde_mesh *m, int count, const fpde_params *p
   const size_t elem = p[0].precision == FPDE_MIXED ? sizeof(float) : sizeof(double);
   Plan *used[16] = {};
   for (int z = 0; z < count; z++) FPDE_TRY(plan_for(m, p[z].quad_points, p[z].max_steps, s, &used[z]));
-  // The walks run on a second stream: the walk of a system overlaps the
+  // The value passes run on a second stream: that of a system overlaps the
   // accumulation of the previous one when that one belongs to the other
   // rule (another plan, another value buffer).  Systems are taken with the
-  // rules alternating; a walk waits for the caller's earlier work and for
+  // rules alternating; a value pass waits for the caller's earlier work and for
   // the last accumulation that read its plan's values, an accumulation for
   // its values (events; they are computed anew only when the orders
   // changed, as in fpde_assemble).
@@ -214,7 +214,7 @@ extern "C" int fpde_assemble_batch(fpde_mesh *m, int count, const fpde_params *p
     if (m->side) FPDE_HIP(hipEventRecord(m->bev[2 * z + 1], s));
     last_acc[pl] = z;
   }
-  int f = take_flag(m, s);  // every walk is ordered before an accumulation on s
+  int f = take_flag(m, s);  // every value pass is ordered before an accumulation on s
   if (f != 0) {
     for (int z = 0; z < count; z++) invalidate_values(used[z]);
     return f < 0 ? f : FPDE_EHIP;

@@ -1,7 +1,7 @@
 // Dense 64-wide building blocks shared by the Cholesky (SPD) and LU
 // (non-symmetric) factorizations and their triangular solves: the tile
 // product staged through LDS, wavefront helpers, and the block-row
-// triangular solve with ticket ordering and per-block flags.
+// triangular solve with ticket ordering, whose entries are their own flags.
 #pragma once
 
 #include "fpde_internal.h"
@@ -304,7 +304,7 @@ __global__ void __launch_bounds__(256) k_trsv_rows(const T *__restrict__ A, int6
   __shared__ double red[4][NB];
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   {
-    const int64_t z = blockIdx.y;  // system z of a strided batch (its own tickets and flags)
+    const int64_t z = blockIdx.y;  // system z of a strided batch (its own tickets)
     A += z * bs.a;
     DinvT += z * bs.l;
     y += z * bs.v;

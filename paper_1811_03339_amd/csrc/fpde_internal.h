@@ -174,7 +174,7 @@ struct fpde_mesh {
   double *bvec = nullptr;         // device: intermediate vectors of a batched solve
   int64_t bvec_n = 0;
   fpde::StageTimer timer;
-  // batched assembly: a second stream for the walks and events ordering it
+  // batched assembly: a second stream for the value passes and events ordering it
   // against the caller's stream (created on first use)
   hipStream_t side = nullptr;
   hipEvent_t bev[33] = {};

@@ -21,7 +21,7 @@
 //   values        from the segments, as in three dimensions (the fourth volume
 //                 coordinate's slope is zero);
 //   accumulation  tube blocks and the row pass of the three-dimensional path;
-//                 where a chord has too many nodes for that, k2_rows: one
+//                 for few unknowns, or chords that do not fit a tube, k2_rows: one
 //                 workgroup per (row, column chunk): row j adds, for each
 //                 incidence of node j, W value times the partner half-ray's
 //                 vector into an LDS row chunk (16 lanes per vector); the
@@ -224,7 +224,7 @@ int bits2(uint64_t v) {
 }
 
 // ---------------------------------------------------------------------------
-// walk + closed-form derivatives
+// walk
 // ---------------------------------------------------------------------------
 enum Walk2Mode { W2_COUNT = 0, W2_STRUCT = 1 };
 

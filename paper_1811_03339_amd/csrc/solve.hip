@@ -589,9 +589,7 @@ static int potrf(T *A, int64_t lda, int64_t n, fpde_mesh *m, hipStream_t s) {
   return potrf_batch<T>(A, lda, 0, n, 1, (T *)lv, 0, m->flag_aux, m, s);
 }
 
-// y (n) holds the right-hand side on entry and the solution on exit;
-// x (n) is scratch.  Two launches (forward, backward), each preceded by a
-// reset of its ticket counter.
+// What precedes the forward solve, as declared in dense.h.
 int trsv_begin(int *tickets, double *x, int64_t sx, int64_t n, int count, const double *b, double *u, int64_t sv,
                hipStream_t s) {
   if (n <= 0) return FPDE_OK;
@@ -613,8 +611,7 @@ int ensure_trsv_sync(fpde_mesh *m, int count) {
 
 // Forward and backward solves of `count` systems (strided batch, grid.y =
 // system): b + z sv (null: y + z sv) holds system z's right-hand side, y + z sv
-// its solution on exit; x + z sx is scratch.
-// The launches of trsv_batch with its 2 count tickets given.
+// its solution on exit; x + z sx is scratch, tickets 2 count of them.
 template <class T>
 static int trsv_batch_sync(const T *L, int64_t lda, int64_t sA, int64_t n, int count, const T *Linv, int64_t sL,
                            const double *b, double *y, int64_t sv, double *x, int64_t sx, int *tickets, fpde_mesh *m,

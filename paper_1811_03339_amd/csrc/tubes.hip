@@ -847,10 +847,9 @@ struct TubeMfmaSmem {
 // occurrence (l's first, then r's).  COUNT: cnt[k] = the pair's merged
 // entries.  FILL: for every entry its merged index within the pair (midx),
 // and per merged entry slot | (inner column << 16), the column being
-// 2 (pair mod 16) + side, its node and its pair; the pair's tube into
-// pk_tube.  Slots must be
-// below kMergeSlots; COUNT also takes into *maxc (zero on entry) the
-// largest count above kMergeMax.
+// 2 (pair mod 16) + side; the pair's tube into pk_tube.  Slots must be below
+// kMergeSlots; COUNT also takes into *maxc (zero on entry) the largest count
+// above kMergeMax.
 template <bool FILL>
 __global__ void __launch_bounds__(64) k_merge_pairs(const int64_t *__restrict__ tube_off, int64_t n_tubes,
                                                     const int4 *__restrict__ pm, int64_t n_pairs,
@@ -923,9 +922,7 @@ __device__ __forceinline__ void wave_lds_sync() {
 }
 
 // The merged values (every assembly): each entry's value added in FP64 into
-// its merged entry (LDS), kept in FP64 (mk_val64) and, times w_g, at its
-// node-order position mpos (mwv) for the matrix-free product (when mwv is
-// not null), and rounded to FP32 (mk_val, for the tube blocks); and per tube the
+// its merged entry (LDS) and rounded to FP32 (mk_val); and per tube the
 // largest binary exponents of X (W_p |v|) and of Y (|v|) over the merged
 // values: texp must hold {INT_MIN, INT_MIN} per tube on entry and receives
 // atomic maxima (ilogb is monotone, so the maximum of the exponents is the
