@@ -677,9 +677,10 @@ def main():
         cand.append((live["potrf"][0], {
             "bound": "mfma", "achieved": fl / t_f / 1e12, "peak": peak / 1e12, "unit": "TFLOP/s",
             "frac": fl / t_f / peak, "traffic": read_traffic("factorization_fp32_c5"),
-            "kernel": "FP32 Cholesky of the n x n matrix: per group of sixteen 64-column panels k_panel and the "
-                      "k_syrk<float, 64> strip update of the group's later block columns, then k_row_split<1024> "
-                      "and k_syrk256<1024> on the trailing matrix (256 x 256 tiles)",
+            "kernel": "FP32 Cholesky of the n x n matrix: per group of 32 64-column panels k_panel and "
+                      "k_syrk<float, 64> strips inside four-panel parts, k_row_split and k_syrk128<float> at a "
+                      "part's end, then k_row_split<2048> and k_syrk256<2048> on the trailing matrix (256 x 256 "
+                      "tiles; k_syrk128<float, 2048> on the next group's columns and below 16 384 rows)",
             "peak_note": "dense FP16 matrix-core peak (2.5 PFLOP/s) / 3: each FP32 product of the trailing "
                          "update is hi*hi + hi*lo + lo*hi on v_mfma_f32_16x16x32_f16",
             "avg_launch_ms": t_f * 1e3, "flops_per_unit": fl,
