@@ -298,13 +298,21 @@ __device__ __forceinline__ void lu_diag_factor(LuSmem &sm, int nb, double *__res
 #pragma unroll
       for (int j = 0; j < 16; j++) {
         good = good && fabs(piv) > 0.0 && fabs(piv) < INFINITY;
-        const double t = v[j] * rcp_step(piv);
+        // L = v[j] / pivot here, row j's entries / pivot there: from an entry of
+        // the block both problems take the product of the same two numbers, so
+        // that they agree in every bit.  (With v[j] / pivot in both, the pivots,
+        // and so L U, were off by the rounding times the condition of the
+        // unknowns before them.)
+        const double r = rcp_step(piv);
+        if (s == 0) {
+          v[j] *= r;
 #pragma unroll
-        for (int k = j + 1; k < 16; k++) {
-          v[k] = fma(-t, read_lane(v[k], j), v[k]);
-          if (k == j + 1) piv = read_lane(v[k], k);
+          for (int k = j + 1; k < 16; k++) v[k] = fma(-v[j], read_lane(v[k], j), v[k]);
+        } else {
+#pragma unroll
+          for (int k = j + 1; k < 16; k++) v[k] = fma(-v[j], read_lane(v[k], j) * r, v[k]);
         }
-        if (s == 0) v[j] = t;  // L is scaled by the pivot, U^T is not
+        if (j < 15) piv = read_lane(v[j + 1], j + 1);
       }
       if (lane >= 48 || (lane < 16 && half)) {
         row = &sm.none[lane];
