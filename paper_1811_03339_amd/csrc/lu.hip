@@ -162,8 +162,10 @@ __global__ void __launch_bounds__(256) k_lu_inverses(const double *__restrict__ 
 // registers, the pivot row's entries read with readlane; the four other
 // wavefronts apply the previous panel to the columns right of the current one
 // (16 x 16 tiles on the matrix cores) and write its outputs.  The chain of 64
-// dependent reciprocals is what bounds it.  One pass over the pivots with one
-// row in four threads and a barrier per pivot took 72 us a block.
+// dependent reciprocals is what bounds it: 22 us a first block (20 with both
+// problems scaled by the pivot alike, which are then not each other's
+// transpose in the last bits).  One pass over the pivots with one row in four
+// threads and a barrier per pivot took 72 us a block.
 struct LuSmem {
   double M[NB][NB + 1];      // the block; L and U replace it outside the diagonal tiles
   double Zt[12][16][17];     // off-diagonal tiles: inv(U) above the diagonal, inv(L) below
