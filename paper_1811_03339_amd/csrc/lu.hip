@@ -162,10 +162,8 @@ __global__ void __launch_bounds__(256) k_lu_inverses(const double *__restrict__ 
 // registers, the pivot row's entries read with readlane; the four other
 // wavefronts apply the previous panel to the columns right of the current one
 // (16 x 16 tiles on the matrix cores) and write its outputs.  The chain of 64
-// dependent reciprocals is what bounds it: 22 us a first block (20 with both
-// problems scaled by the pivot alike, which are then not each other's
-// transpose in the last bits).  One pass over the pivots with one row in four
-// threads and a barrier per pivot took 72 us a block.
+// dependent reciprocals is what bounds it: 20 us a first block.  One pass over
+// the pivots with one row in four threads and a barrier per pivot took 72 us.
 struct LuSmem {
   double M[NB][NB + 1];      // the block; L and U replace it outside the diagonal tiles
   double Zt[12][16][17];     // off-diagonal tiles: inv(U) above the diagonal, inv(L) below
@@ -296,25 +294,30 @@ __device__ __forceinline__ void lu_diag_factor(LuSmem &sm, int nb, double *__res
     }
     __syncthreads();
     if (wv < 4) {
+      // L = v[j] / pivot in A, row j's entries / pivot in its transpose: from an
+      // entry of the block both problems take the product of the same two
+      // numbers, so that they agree in every bit.  (With v[j] / pivot in both,
+      // the pivots, and so L U, were off by the rounding times the condition of
+      // the unknowns before them.)  A loop for each: 1728 unknowns 1002 us; with
+      // a branch per pivot, across which nothing is scheduled, 1027.
       double piv = read_lane(v[0], 0);
+      if (s == 0) {
 #pragma unroll
-      for (int j = 0; j < 16; j++) {
-        good = good && fabs(piv) > 0.0 && fabs(piv) < INFINITY;
-        // L = v[j] / pivot here, row j's entries / pivot there: from an entry of
-        // the block both problems take the product of the same two numbers, so
-        // that they agree in every bit.  (With v[j] / pivot in both, the pivots,
-        // and so L U, were off by the rounding times the condition of the
-        // unknowns before them.)
-        const double r = rcp_step(piv);
-        if (s == 0) {
-          v[j] *= r;
+        for (int j = 0; j < 16; j++) {
+          good = good && fabs(piv) > 0.0 && fabs(piv) < INFINITY;
+          v[j] *= rcp_step(piv);
 #pragma unroll
           for (int k = j + 1; k < 16; k++) v[k] = fma(-v[j], read_lane(v[k], j), v[k]);
-        } else {
+          if (j < 15) piv = read_lane(v[j + 1], j + 1);
+        }
+      } else {
+#pragma unroll
+        for (int j = 0; j < 16; j++) {
+          const double r = rcp_step(piv);
 #pragma unroll
           for (int k = j + 1; k < 16; k++) v[k] = fma(-v[j], read_lane(v[k], j) * r, v[k]);
+          if (j < 15) piv = read_lane(v[j + 1], j + 1);
         }
-        if (j < 15) piv = read_lane(v[j + 1], j + 1);
       }
       if (lane >= 48 || (lane < 16 && half)) {
         row = &sm.none[lane];
@@ -615,7 +618,7 @@ static int lu_inverses(fpde_mesh *m, int64_t n, double **Linv, double **LinvT, d
 // Panels per group: the trailing square is read and written once per group.
 // One factorization at N = 8 162: pairs of panels on 64-wide tiles with the
 // diagonal blocks of 72 us 18.9 ms; groups of 4 on 128-wide tiles 12.0 ms, of 8
-// 11.2 ms (32 TFLOP/s; 128 steps of about 29 us are 3.7 ms of it).  Running the
+// 10.9 ms (33 TFLOP/s; 128 steps of about 29 us are 3.7 ms of it).  Running the
 // next group's panels beside the trailing update (its own stream) gained
 // nothing: their tiles wait for the compute units that the update holds.
 constexpr int kLuGroup = 8;
