@@ -618,7 +618,7 @@ static int lu_inverses(fpde_mesh *m, int64_t n, double **Linv, double **LinvT, d
 // Panels per group: the trailing square is read and written once per group.
 // One factorization at N = 8 162: pairs of panels on 64-wide tiles with the
 // diagonal blocks of 72 us 18.9 ms; groups of 4 on 128-wide tiles 12.0 ms, of 8
-// 10.9 ms (33 TFLOP/s; 128 steps of about 29 us are 3.7 ms of it).  Running the
+// 11.2 ms, now 10.9 (33 TFLOP/s; 128 steps of about 29 us are 3.7 ms of it).  Running the
 // next group's panels beside the trailing update (its own stream) gained
 // nothing: their tiles wait for the compute units that the update holds.
 constexpr int kLuGroup = 8;
